@@ -26,6 +26,7 @@
 #include <cstring>
 #include <new>
 
+#include "dense_rows.hpp"
 #include "fft_core.hpp"
 #include "loss.hpp"
 #include "plan.hpp"
@@ -399,22 +400,26 @@ __global__ void __launch_bounds__(NT) dense_epi2_kernel(const DenseArgs a) {
   }
 }
 
-// inv[p] = 1/sqrt(sum_t part[p][t])  (fixed order)
-__global__ void inv_norms_kernel(const float* __restrict__ part, int ld, int cnt, int nb, float* inv) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= nb) return;
+// One wave per signal sums its cnt partials: strided per-lane sums in index
+// order, then a fixed tree.  (One thread per signal took the latency of every
+// load in turn, 15 us for 256 partials.)
+__device__ __forceinline__ double wave_row_sum(const float* __restrict__ part, int cnt) {
   double acc = 0.0;
-  for (int t = 0; t < cnt; ++t) acc += (double)part[(long long)p * ld + t];
-  inv[p] = (float)(1.0 / sqrt(acc));
+  for (int t = threadIdx.x; t < cnt; t += 64) acc += (double)part[t];
+  return block_sum_t<64, double>(acc, nullptr);
 }
 
-// out[p * stride] = sum_t part[p][t]  (fixed order)
-__global__ void sum_rows_kernel(const float* __restrict__ part, int ld, int cnt, int nb, float* out, int stride) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= nb) return;
-  double acc = 0.0;
-  for (int t = 0; t < cnt; ++t) acc += (double)part[(long long)p * ld + t];
-  out[(long long)p * stride] = (float)acc;
+// inv[p] = 1/sqrt(sum_t part[p][t])
+__global__ void __launch_bounds__(64) inv_norms_kernel(const float* __restrict__ part, int ld, int cnt, float* inv) {
+  const double s = wave_row_sum(part + (long long)blockIdx.x * ld, cnt);
+  if (threadIdx.x == 0) inv[blockIdx.x] = (float)(1.0 / sqrt(s));
+}
+
+// out[p * stride] = sum_t part[p][t]
+__global__ void __launch_bounds__(64) sum_rows_kernel(const float* __restrict__ part, int ld, int cnt, float* out,
+                                                      int stride) {
+  const double s = wave_row_sum(part + (long long)blockIdx.x * ld, cnt);
+  if (threadIdx.x == 0) out[(long long)blockIdx.x * stride] = (float)s;
 }
 
 // per-signal sum of y (one workgroup per signal, fixed order)
@@ -626,13 +631,29 @@ size_t dense_split_floats(int m, int n, int nb) {
   plan_split(((2 * n + BT - 1) / BT) * st, m, &S2, &kc);
   const size_t f1 = (size_t)S1 * m * 64 * st;
   const size_t f2 = (size_t)S2 * 2 * n * 64 * st;
-  return std::max(f1, f2);
+  RowsShape rs;
+  const size_t f3 = rows_shape(m, n, nb, &rs) ? 2 * (size_t)rs.G * nb * n : 0;  // the row kernels' partials of A^H r
+  return std::max(std::max(f1, f2), f3);
+}
+
+// Whether a plan's products run on the row kernels: their shape, with room
+// for the per-signal partial sums of a solve.
+static bool rows_plan(const sr_plan_s* p) {
+  RowsShape s;
+  const Geo& g = p->geo[0];
+  const int nb = (int)p->geo.size();
+  if (g.m > (1 << 30) || g.n > 4096 || !rows_shape((int)g.m, (int)g.n, nb, &s)) return false;
+  return (long long)nb * std::max(s.G, rows_update_groups((int)g.n)) <= 2LL * p->part_cap;
 }
 
 // Scratch layout for dense plans: bufA holds R (nb x m complex); fscratch
 // holds per-signal scalars; part holds per-signal partials.
 sr_status dense_lib_setup(sr_plan_s* p) {
   const char* force = std::getenv("SR_DENSE_GEMM");
+  if (force == nullptr && rows_plan(p)) {  // every product runs on the row kernels: nothing to time
+    p->dense_rows = true;
+    return SR_OK;
+  }
   if (force != nullptr && std::strcmp(force, "own") == 0) return SR_OK;
   DenseArgs a = base(p);
   const uint64_t q = 64 * (uint64_t)signal_tiles(a), m = (uint64_t)a.m, n2 = 2 * (uint64_t)a.n;
@@ -743,7 +764,29 @@ sr_status dense_lib_setup(sr_plan_s* p) {
   return SR_OK;
 }
 
+// The row kernels' arguments and split for this plan.
+static RowsArgs rows_base(const sr_plan_s* p, RowsShape* s) {
+  RowsArgs a{};
+  a.A = (const float*)p->dense_A;
+  a.m = (int)p->geo[0].m;
+  a.n = (int)p->geo[0].n;
+  a.nb = (int)p->geo.size();
+  rows_shape(a.m, a.n, a.nb, s);
+  a.rows = s->rows;
+  a.part = (float2*)p->dsplit;
+  return a;
+}
+
 sr_status dense_forward(sr_plan_s* p, const float2* x, float2* z, float* y) {
+  if (p->dense_rows) {
+    RowsShape s;
+    RowsArgs r = rows_base(p, &s);
+    r.x = x;
+    r.z_out = z;
+    r.y_out = y;
+    DN_HIP(launch_rows(ROWS_FWD, s, r, p->stream));
+    return SR_OK;
+  }
   DenseArgs a = base(p);
   a.src = x;
   a.z_out = z;
@@ -753,6 +796,14 @@ sr_status dense_forward(sr_plan_s* p, const float2* x, float2* z, float* y) {
 }
 
 sr_status dense_adjoint(sr_plan_s* p, const float2* r, float2* x) {
+  if (p->dense_rows) {
+    RowsShape s;
+    RowsArgs q = rows_base(p, &s);
+    q.r = r;
+    DN_HIP(launch_rows(ROWS_ADJ, s, q, p->stream));
+    DN_HIP(launch_rows_update(ROWS_STORE, s, q, x, 1.f, nullptr, 0, nullptr, p->stream));
+    return SR_OK;
+  }
   DenseArgs a = base(p);
   a.src = r;
   a.x = x;
@@ -765,6 +816,26 @@ sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const flo
   DenseArgs a = base(p);
   for (int i = 1; i < a.nb; ++i)
     if (eta[i] != eta[0]) return fail(SR_E_UNSUPPORTED, "dense plans take one step size for all signals");
+  if (p->dense_rows) {  // one read of A per iteration
+    RowsShape s;
+    RowsArgs r = rows_base(p, &s);
+    r.x = x;
+    r.y = y;
+    r.loss = p->loss;
+    r.loss_eps = p->loss_eps;
+    r.loss_part = loss_trace ? p->part : nullptr;
+    r.loss_ld = s.G;
+    for (int it = 0; it < iters; ++it) {
+      DN_HIP(launch_rows(ROWS_GD, s, r, p->stream));
+      if (loss_trace) {
+        hipLaunchKernelGGL(sum_rows_kernel, dim3(a.nb), dim3(64), 0, p->stream, p->part, s.G, s.G,
+                           loss_trace + it, iters);
+        DN_HIP(hipGetLastError());
+      }
+      DN_HIP(launch_rows_update(ROWS_UPDATE_GD, s, r, x, eta[0] / (float)a.m, nullptr, 0, a.nf, p->stream));
+    }
+    return SR_OK;
+  }
   const int t1 = row_tiles_g1(a);
   if ((long long)a.nb * t1 > 2LL * p->part_cap) return fail(SR_E_NOMEM, "partial buffer too small");
   for (int it = 0; it < iters; ++it) {
@@ -778,7 +849,7 @@ sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const flo
     g1.loss_eps = p->loss_eps;
     DN_HIP((gemm<1, E1_GD>(g1, p->dsplit, p->stream, p->dense_lib)));
     if (loss_trace) {
-      hipLaunchKernelGGL(sum_rows_kernel, dim3((a.nb + 63) / 64), dim3(64), 0, p->stream, p->part, t1, t1, a.nb,
+      hipLaunchKernelGGL(sum_rows_kernel, dim3(a.nb), dim3(64), 0, p->stream, p->part, t1, t1,
                          loss_trace + it, iters);
       DN_HIP(hipGetLastError());
     }
@@ -793,7 +864,7 @@ sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const flo
 
 sr_status dense_spectral(sr_plan_s* p, const float* y, const float2* v0, int iters, float lam, float2* x0) {
   DenseArgs a = base(p);
-  const int t2 = row_tiles_g2(a);
+  const int t2 = p->dense_rows ? rows_update_groups(a.n) : row_tiles_g2(a);
   if ((long long)a.nb * t2 > 2LL * p->part_cap) return fail(SR_E_NOMEM, "partial buffer too small");
   float* inv = p->fscratch;  // nb floats: 1/||u_p||
   double* ysum = p->ysum;
@@ -804,8 +875,26 @@ sr_status dense_spectral(sr_plan_s* p, const float* y, const float2* v0, int ite
   DN_HIP(hipGetLastError());
   int cnt = 1;
   const float inv_mc = 1.f / (float)a.m;  // dense CN(0,1): c = 1
+  if (p->dense_rows) {  // one read of A per iteration; the norm is summed by the row kernel itself
+    RowsShape s;
+    RowsArgs r = rows_base(p, &s);
+    r.x = x0;
+    r.y = y;
+    r.ysum = ysum;
+    r.lam = lam;
+    r.inv = inv;
+    r.norm_part = p->part;
+    r.norm_ld = t2;
+    for (int it = 0; it < iters; ++it) {
+      r.norm_cnt = cnt;
+      DN_HIP(launch_rows(ROWS_SPEC, s, r, p->stream));
+      DN_HIP(launch_rows_update(ROWS_UPDATE_SPEC, s, r, x0, inv_mc, p->part, t2, a.nf, p->stream));
+      cnt = t2;
+    }
+    iters = 0;
+  }
   for (int it = 0; it < iters; ++it) {
-    hipLaunchKernelGGL(inv_norms_kernel, dim3((a.nb + 63) / 64), dim3(64), 0, p->stream, p->part, t2, cnt, a.nb, inv);
+    hipLaunchKernelGGL(inv_norms_kernel, dim3(a.nb), dim3(64), 0, p->stream, p->part, t2, cnt, inv);
     DN_HIP(hipGetLastError());
     DenseArgs g1 = a;  // r = T(y) . A (u / ||u||)
     g1.src = x0;
@@ -826,7 +915,7 @@ sr_status dense_spectral(sr_plan_s* p, const float* y, const float2* v0, int ite
     DN_HIP((gemm<2, E2_SPEC>(g2, p->dsplit, p->stream, p->dense_lib)));
     cnt = t2;
   }
-  hipLaunchKernelGGL(inv_norms_kernel, dim3((a.nb + 63) / 64), dim3(64), 0, p->stream, p->part, t2, cnt, a.nb, inv);
+  hipLaunchKernelGGL(inv_norms_kernel, dim3(a.nb), dim3(64), 0, p->stream, p->part, t2, cnt, inv);
   DN_HIP(hipGetLastError());
   const long long tot = (long long)a.n * a.nb;
   const int groups = (int)std::min<long long>((tot + 255) / 256, 2048);

@@ -94,6 +94,8 @@ struct sr_plan_s {
   const float2* dense_A = nullptr;  // caller-owned dense matrix (SR_DENSE)
   sr::DenseLib* dense_lib = nullptr;  // library GEMM state of a dense plan (null: hand-written products only)
 
+  bool dense_rows = false;  // dense products on the row kernels (few short signals; dense_rows.hip)
+
   std::map<std::pair<int, int>, float2*> tw;  // (FFT length, thread shape) -> device twiddle table
   float2* twbuf = nullptr;
 
