@@ -591,7 +591,7 @@ def autograd(torch, srpr, sr_inputs, dev):
             "torch_peak_bytes_20_steps": int(p20), "torch_peak_bytes_10_steps": int(p10),
             "torch_bytes_per_step": (p20 - p10) / (d["steps"] - d["steps"] // 2),
             "signal_bytes_per_step": 8 * n_tot, "measurement_bytes": 8 * m_tot,
-            "library_temporaries_bytes": 8 * (3 * m_tot + 2 * n_tot)}
+            "library_temporaries_bytes": 8 * L * m_tot}
 
 
 def lds_resident(torch, srpr, sr_inputs, dev, count=512, iters=300):

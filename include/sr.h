@@ -261,8 +261,10 @@ sr_status sr_adjoint_vjp(sr_plan plan, const void* r, const void* gv, void* gr_o
  * sr_intensity_vjp: y = |A x|^2 (Eq. (1)).  Given x and the cotangent gy of
  *   y, writes gx_out = d<gy, y>/dx (nullable) and ADDS d<gy, y>/dtheta into
  *   gtheta_accum.
- * Structured plans; the first call allocates 3 measurement-sized and 2
- * signal-sized complex64 temporaries for the plan's lifetime.                 */
+ * Structured plans; the first call allocates complex64 temporaries for the
+ * plan's lifetime: L grids per problem of a stack (for the largest problem
+ * otherwise) beside those of sr_forward_vjp, or, on plans with 1D problems or
+ * batched levels, 3 measurement-sized and 2 signal-sized arrays.              */
 sr_status sr_gd_step_vjp(sr_plan plan, const float* y, const void* x, const float* eta_host, const void* gx_next,
                          void* gx_out, float* gy_accum, float* gtheta_accum);
 sr_status sr_intensity_vjp(sr_plan plan, const void* x, const float* gy, void* gx_out, float* gtheta_accum);

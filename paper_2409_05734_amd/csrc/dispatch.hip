@@ -7,7 +7,7 @@ namespace sr {
 #define SR_FOR_EACH_2D_LEN(X) X(16) X(32) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(768) X(1024) X(2048)
 
 hipError_t launch_pass(int N, int kind, bool col, int B, const PassArgs& a, hipStream_t s) {
-  const bool rev = kind >= PK_MID_FWD_SAVE && kind <= PK_LAST_ADJ_GT;
+  const bool rev = reverse_kind(kind);
   // the reverse-mode passes are built for the default thread shape only, and
   // the wide shape for the column passes [F D F] and [F^H D^* F^H] only: the
   // others run the length's default tile

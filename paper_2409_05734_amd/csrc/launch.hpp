@@ -29,8 +29,18 @@ enum PassKind : int {
   PK_LAST_GD_FWD = 15,
   PK_LAST_SPEC_FWD = 16,
   PK_TURN_GD_POIS = 17,  // [F_a -> (1 - y/(|z|^2 + eps)) z -> F_a^H]  (Poisson loss)
-  PK_COUNT = 18
+  // reverse GD step and intensities (reverse-mode kernel set)
+  PK_TURN_STEP = 18,      // [F_a -> z (saved), (|z|^2 - y) z -> F_a^H]
+  PK_TURN_STEP_BAR = 19,  // [F_a -> rbar, (2|z|^2 - y) rbar + z^2 conj(rbar) -> F_a^H], y's cotangents
+  PK_TURN_INT_BAR = 20,   // [F_a -> z, 2 ybar z -> F_a^H]
+  PK_LAST_ADJ_GTV = 21,   // [F_0^H, D_1^*, gth_1 += Im(conj(step xin) v)]
+  PK_FIRST_FWD_STEP = 22, // [U, D_1, F_0] of step x
+  PK_COUNT = 23
 };
+
+inline bool reverse_kind(int kind) {
+  return (kind >= PK_MID_FWD_SAVE && kind <= PK_LAST_ADJ_GT) || (kind >= PK_TURN_STEP && kind <= PK_FIRST_FWD_STEP);
+}
 
 // Tile widths: each length is compiled for a few tile widths (transforms per
 // workgroup) and, for power-of-two lengths 64..1024, two thread shapes in

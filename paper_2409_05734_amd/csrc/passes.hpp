@@ -21,7 +21,11 @@
 
 namespace sr {
 
-enum PreOp : int { PRE_NONE = 0, PRE_PHASE = 1 };
+enum PreOp : int {
+  PRE_NONE = 0,
+  PRE_PHASE = 1,
+  PRE_PHASE_STEP = 2  // D_1 U (step x): the reverse GD step's first pass on the scaled cotangent
+};
 enum MidOp : int {
   MID_NONE = 0,
   MID_PHASE = 1,            // v <- D v
@@ -34,7 +38,11 @@ enum MidOp : int {
   MID_PHASE_CONJ_GT = 7,    // gth += Im(v conj(save)), v <- D^* v   (forward VJP)
   MID_PHASE_CONJ_SAVE = 8,  // q <- D^* v, save <- q                (adjoint recompute)
   MID_PHASE_GT = 9,         // gth += Im(conj(v) save), v <- D v     (adjoint VJP)
-  MID_GD_POIS = 10          // v <- (1 - y/(|v|^2 + eps)) v, Poisson loss partials
+  MID_GD_POIS = 10,         // v <- (1 - y/(|v|^2 + eps)) v, Poisson loss partials
+  // turnarounds of the reverse GD step and of the intensities' reverse
+  MID_STEP = 11,            // save <- z, v <- (|z|^2 - y) z
+  MID_STEP_BAR = 12,        // v <- (2|z|^2 - y) v + z^2 conj(v), gy -= Re(conj(v) z), z = save
+  MID_INT_BAR = 13          // v <- 2 y v (y: the cotangent of the intensities)
 };
 // The reverse-mode mid operations (phase diagonal with a saved intermediate).
 constexpr bool mid_rev_phase(int mid) { return mid >= MID_PHASE_SAVE && mid <= MID_PHASE_GT; }
@@ -49,7 +57,8 @@ enum PostOp : int {
   // still in registers, is padded, multiplied by D_1 and transformed along
   // axis 0 into out2 (the compact buffer the next row pass reads)
   POST_GD_FWD = 5,
-  POST_SPEC_FWD = 6
+  POST_SPEC_FWD = 6,
+  POST_GTV = 7  // gth_1 += Im(conj(step xin) D_1^* v) on the support, nothing stored
 };
 
 struct PassArgs {
@@ -112,6 +121,11 @@ struct PassArgs {
   // non-finite flag (nullable): the final update of a solve (POST_GD,
   // POST_SPEC) stores 1 here when an updated iterate entry is NaN or Inf
   unsigned* nf;
+  // reverse GD step
+  float* gy;          // MID_STEP_BAR: cotangents of y, accumulated (nullable)
+  const float2* xadd; // POST_PHASE_CONJ_GT: added to the output (nullable)
+  int s_xadd;
+  int gth_set;        // phase cotangents: write them rather than add (the first term into scratch)
 };
 
 // 1/sqrt of the sum of the previous iterate's squared-norm partials: strided
@@ -144,8 +158,10 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   using T = TileV<N, B, COL, DB, EV>;
   constexpr int E = T::E;
   constexpr bool MID_PH = (MID == MID_PHASE || MID == MID_PHASE_CONJ || mid_rev_phase(MID));
+  constexpr bool PRE_PH = (PRE != PRE_NONE);
   constexpr bool MID_SAVED = (MID == MID_PHASE_CONJ_GT || MID == MID_PHASE_GT);
-  constexpr bool MID_Y = (MID == MID_GD || MID == MID_GD_POIS || MID == MID_SPEC);
+  constexpr bool MID_Y = (MID == MID_GD || MID == MID_GD_POIS || MID == MID_SPEC || MID == MID_STEP ||
+                          MID == MID_STEP_BAR || MID == MID_INT_BAR);
   constexpr bool POST_PH = (POST != POST_STORE);
   constexpr bool POST_X = (POST == POST_GD || POST == POST_SPEC || POST == POST_GD_FWD || POST == POST_SPEC_FWD);
   constexpr bool POST_FWD = (POST == POST_GD_FWD || POST == POST_SPEC_FWD);
@@ -214,7 +230,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
     const int g = gidx(k) + o_th;  // phase index
     if constexpr (IN_WIN) v[j] = ld2(r_in, off8(m_in(k), m_idx(k) - o_win + o_in));
     else v[j] = ld2(r_in, off8(iw, in_addr(k)));
-    if constexpr (PRE == PRE_PHASE) {
+    if constexpr (PRE_PH) {
       if constexpr (TAB) dp[j] = ld2(r_pre, off8(iw, g));
       else dp[j].x = ld1(r_pre, off4(iw, g));
     }
@@ -225,7 +241,11 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
     if constexpr (MID_Y) yv[j] = ld1(r_y, off4(m_in(k), m_idx(k)));
     if constexpr (MID_SAVED) {
       sv[j] = ld2(r_save, off8(active, g - o_th + o_sv));
-      gt[j] = ld1(r_gth, off4(active, g - o_th + o_gt));
+      gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(active, g - o_th + o_gt));
+    }
+    if constexpr (MID == MID_STEP_BAR) {
+      sv[j] = ld2(r_save, off8(active, g - o_th + o_sv));
+      gt[j] = a.gy != nullptr ? ld1(rsrc(a.gy), off4(m_in(k), m_idx(k))) : 0.f;
     }
     if constexpr (MID != MID_STORE) {
       const bool ow = out_win(k);
@@ -236,7 +256,11 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
       if constexpr (POST_X) xo[j] = ld2(r_out, off8(ow, out_addr(k)));
       if constexpr (POST == POST_PHASE_CONJ_GT) {
         xo[j] = ld2(rsrc(a.xin), off8(ow, o_xin + out_rel(k)));
-        gt[j] = ld1(r_gth, off4(ow, g - o_th + o_gt));
+        gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(ow, g - o_th + o_gt));
+      }
+      if constexpr (POST == POST_GTV) {
+        xo[j] = ld2(rsrc(a.xin), off8(ow, o_xin + out_rel(k)));
+        gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(ow, g - o_th + o_gt));
       }
     }
   }
@@ -247,7 +271,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   if constexpr (!TAB) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      if constexpr (PRE == PRE_PHASE) dp[j] = phase_turns(dp[j].x);
+      if constexpr (PRE_PH) dp[j] = phase_turns(dp[j].x);
       if constexpr (MID_PH && !LATE_PH) dm[j] = phase_turns(dm[j].x);
       if constexpr (POST_PH && !LATE_PH) dq[j] = phase_turns(dq[j].x);
     }
@@ -273,10 +297,17 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
     }
   }
 
+  // the step of the lane's problem (the reverse GD step's factor -eta/m)
+  float step = a.step;
+  if constexpr (PRE == PRE_PHASE_STEP || POST == POST_GTV) {
+    if (a.step_v != nullptr && active) step = a.step_v[sp];
+  }
+  if constexpr (PRE == PRE_PHASE_STEP) s_pre *= step;
+
   // ---- pre-diagonal, first transform
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    if constexpr (PRE == PRE_PHASE) v[j] = cmul(v[j], cscale(dp[j], s_pre));
+    if constexpr (PRE_PH) v[j] = cmul(v[j], cscale(dp[j], s_pre));
     else v[j] = cscale(v[j], s_pre);
   }
   int ph = 0;
@@ -311,6 +342,30 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
         v[j] = cmul(u, Dm(j));
       }
     }
+  } else if constexpr (MID == MID_STEP) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int k = T::elem(t, j);
+      const float2 z = cscale(v[j], a.scale_mid);
+      st2(r_save, off8(active, gidx(k) + o_sv), z);
+      v[j] = cscale(z, m_in(k) ? cabs2(z) - yv[j] : 0.f);
+    }
+  } else if constexpr (MID == MID_STEP_BAR) {
+#pragma unroll
+    for (int j = 0; j < E; ++j) {
+      const int k = T::elem(t, j);
+      const bool in = m_in(k);
+      const float2 rb = cscale(v[j], a.scale_mid), z = sv[j];
+      const float w = 2.f * cabs2(z) - yv[j];
+      const float2 z2 = cmul(z, z);
+      if (a.gy != nullptr) st1(rsrc(a.gy), off4(in, m_idx(k)), gt[j] - (rb.x * z.x + rb.y * z.y));
+      v[j] = make_float2(in ? w * rb.x + z2.x * rb.x + z2.y * rb.y : 0.f,
+                         in ? w * rb.y + z2.y * rb.x - z2.x * rb.y : 0.f);
+    }
+  } else if constexpr (MID == MID_INT_BAR) {
+#pragma unroll
+    for (int j = 0; j < E; ++j)
+      v[j] = cscale(cscale(v[j], a.scale_mid), m_in(T::elem(t, j)) ? 2.f * yv[j] : 0.f);
   } else if constexpr (MID == MID_GD) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
@@ -366,7 +421,6 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   if constexpr (MID != MID_STORE) {
     constexpr bool CHECK = (POST == POST_GD || POST == POST_SPEC);  // the last update of a solve
     bool bad = false;
-    float step = a.step;
     if constexpr (POST_IS_GD) {
       if (a.step_v != nullptr && active) step = a.step_v[sp];
     }
@@ -382,6 +436,14 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
         st1(r_gth, off4(ow, gidx(k) + o_gt), gt[j] + (val.y * u1.x - val.x * u1.y));
       }
       if constexpr (POST_PH) val = cmulc(val, qj);
+      if constexpr (POST == POST_GTV) {
+        const float2 vb = cscale(xo[j], step);
+        st1(r_gth, off4(ow, gidx(k) + o_gt), gt[j] + (vb.x * val.y - vb.y * val.x));
+        continue;
+      }
+      if constexpr (POST == POST_PHASE_CONJ_GT) {
+        if (a.xadd != nullptr) val = cadd(ld2(rsrc(a.xadd), off8(ow, sp * a.s_xadd + out_rel(k))), val);
+      }
       if constexpr (POST_IS_GD) {
         val = make_float2(xo[j].x - step * val.x, xo[j].y - step * val.y);
       } else if constexpr (POST_IS_SPEC) {
@@ -419,7 +481,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
 // Whether a pass shape reads any phase diagonal.
 template <int PRE, int MID, int POST>
 constexpr bool pass_has_phase() {
-  return PRE == PRE_PHASE || MID == MID_PHASE || MID == MID_PHASE_CONJ || mid_rev_phase(MID) || POST != POST_STORE;
+  return PRE != PRE_NONE || MID == MID_PHASE || MID == MID_PHASE_CONJ || mid_rev_phase(MID) || POST != POST_STORE;
 }
 
 // pass_tile with the phase source picked at run time (the tables are set

@@ -103,6 +103,9 @@ hipError_t dispatch(int kind, const PassArgs& a, hipStream_t s) {
   if constexpr (COL) {
     if (kind == PK_LAST_ADJ_GT)
       return go<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_PHASE_CONJ_GT>(a, s);
+    if (kind == PK_LAST_ADJ_GTV) return go<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_GTV>(a, s);
+    if (kind == PK_FIRST_FWD_STEP)
+      return go<N, B, COL, PRE_PHASE_STEP, MID_NONE, false, false, false, POST_STORE>(a, s);
   }
   switch (kind) {
     case PK_MID_FWD_SAVE:
@@ -113,6 +116,12 @@ hipError_t dispatch(int kind, const PassArgs& a, hipStream_t s) {
       return go<N, B, COL, PRE_NONE, MID_PHASE_CONJ_SAVE, true, true, true, POST_STORE>(a, s);
     case PK_MID_FWD_GT:
       return go<N, B, COL, PRE_NONE, MID_PHASE_GT, true, false, false, POST_STORE>(a, s);
+    case PK_TURN_STEP:
+      return go_w<N, B, COL, PRE_NONE, MID_STEP, true, false, true, POST_STORE>(a, s);
+    case PK_TURN_STEP_BAR:
+      return go_w<N, B, COL, PRE_NONE, MID_STEP_BAR, true, false, true, POST_STORE>(a, s);
+    case PK_TURN_INT_BAR:
+      return go_w<N, B, COL, PRE_NONE, MID_INT_BAR, true, false, true, POST_STORE>(a, s);
     default:
       return hipErrorInvalidValue;
   }

@@ -214,6 +214,7 @@ sr_plan_s::~sr_plan_s() {
   if (cap_stream) (void)hipStreamDestroy(cap_stream);
   if (vjp_buf) (void)hipFree(vjp_buf);
   if (gstep_buf) (void)hipFree(gstep_buf);
+  if (step_buf) (void)hipFree(step_buf);
   if (d_off) (void)hipFree(d_off);
   if (d_scale) (void)hipFree(d_scale);
   if (stk_buf) (void)hipFree(stk_buf);

@@ -135,6 +135,8 @@ struct sr_plan_s {
   float2* gstep_buf = nullptr;
   int64_t* d_off = nullptr;  // x offsets (nprob + 1), then y offsets (nprob + 1)
   float* d_scale = nullptr;  // nprob per-problem factors
+  float2* step_buf = nullptr;  // the reverse GD step inside the passes: z and the saved q_k, grid layout
+  size_t step_elems = 0;
   std::vector<size_t> lvl_off;
   size_t vjp_elems = 0;
 

@@ -211,13 +211,14 @@ inline sr_status launch(sr_plan_s* p, const Geo& g, int k, int kind, const PassA
     a.ntr_p = a.ntr;
     a.ntr *= p->stk.P;
     a.s_th = p->stk.th_stride;
-    int sy = 0, sz = 0, syo = 0;
+    int sy = 0, sz = 0, syo = 0, sgy = 0;
     const StackState& st = p->stk;
     if (!st.stride_of(a.in, &a.s_in) || !st.stride_of(a.out, &a.s_out) || !st.stride_of(a.out2, &a.s_out2) ||
         !st.stride_of(a.save, &a.s_save) || !st.stride_of(a.gth, &a.s_gth) || !st.stride_of(a.xin, &a.s_xin) ||
-        !st.stride_of(a.y, &sy) || !st.stride_of(a.z_out, &sz) || !st.stride_of(a.y_out, &syo))
+        !st.stride_of(a.y, &sy) || !st.stride_of(a.z_out, &sz) || !st.stride_of(a.y_out, &syo) ||
+        !st.stride_of(a.gy, &sgy) || !st.stride_of(a.xadd, &a.s_xadd))
       return fail(SR_E_STATE, "stacked pass: a buffer without a per-problem stride");
-    a.s_win = std::max(sy, std::max(sz, syo));  // measurement-shaped buffers share one stride
+    a.s_win = std::max(std::max(sy, sgy), std::max(sz, syo));  // measurement-shaped buffers share one stride
     a.step_v = p->stk.steps;
     if (a.part_in != nullptr || a.part_out != nullptr) {  // per-problem partial sums: whole problems per tile
       const int bt = tile_other(p, pass_len(g, k), pass_col(k)) & (kSingleBuffer - 1);

@@ -25,25 +25,41 @@ namespace sr {
 
 namespace {
 
-// gth_1[support] += Im(conj(gv) v) for the adjoint derivative's first layer,
-// for P stacked problems (problem s: gv, v at s n, gth at s gth_stride)
+// gth_1[support] += Im(conj(gv) v) for the adjoint derivative's first layer
+// (a problem of a batched plan; elsewhere the last adjoint pass adds it)
 __global__ void gth_support_kernel(const float2* __restrict__ gv, const float2* __restrict__ v, float* gth, int N1,
-                                   int N2, int o1, int o2, long long M2, int P, long long gth_stride) {
+                                   int N2, int o1, int o2, long long M2) {
   const long long n = (long long)N1 * N2;
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n * P; e += (long long)gridDim.x * blockDim.x) {
-    const long long s = e / n, l = e - s * n;
-    const int i = (int)(l / N2), j = (int)(l % N2);
+  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < n; e += (long long)gridDim.x * blockDim.x) {
+    const int i = (int)(e / N2), j = (int)(e % N2);
     const float2 a = gv[e], b = v[e];
-    gth[s * gth_stride + (long long)(o1 + i) * M2 + (o2 + j)] += a.x * b.y - a.y * b.x;
+    gth[(long long)(o1 + i) * M2 + (o2 + j)] += a.x * b.y - a.y * b.x;
   }
 }
 
 // gth[e] += sum over the stack of part[s * len + e], added in problem order
-// (the order of a problem-by-problem loop)
-__global__ void gth_reduce_kernel(const float* __restrict__ part, float* gth, long long len, int P) {
-  for (long long e = blockIdx.x * (long long)blockDim.x + threadIdx.x; e < len; e += (long long)gridDim.x * blockDim.x) {
+// (the order of a problem-by-problem loop).  Layer 1 has terms on the signal's
+// support only (and the scratch holds nothing elsewhere), so entry q < n of
+// the work is support point q, the rest are layers 2..L in full.  Sixteen
+// loads are in flight per thread: 64 problems on 256^2 grids, L = 2 (21 MB) in
+// 6 us, 17 us with one at a time over the whole blocks.
+__global__ void __launch_bounds__(256) gth_reduce_kernel(const float* __restrict__ part, float* __restrict__ gth,
+                                                         long long len, int P, int N1, int N2, int o1, int o2, int M2,
+                                                         long long mg) {
+  const long long n = (long long)N1 * N2;
+  const long long work = n + (len - mg);
+  for (long long q = blockIdx.x * (long long)blockDim.x + threadIdx.x; q < work; q += (long long)gridDim.x * blockDim.x) {
+    const long long e = q < n ? (o1 + q / N2) * M2 + o2 + q % N2 : mg + (q - n);
     float acc = gth[e];
-    for (int s = 0; s < P; ++s) acc += part[(long long)s * len + e];
+    int s = 0;
+    for (; s + 16 <= P; s += 16) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = part[(long long)(s + u) * len + e];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) acc += v[u];
+    }
+    for (; s < P; ++s) acc += part[(long long)s * len + e];
     gth[e] = acc;
   }
 }
@@ -100,9 +116,18 @@ sr_status fused1d_vjp(sr_plan_s* p, const Geo& g, int op, Fused1DArgs a) {
     if (s_ != SR_OK) return s_; \
   } while (0)
 
-// Forward passes 1..L on x (saving u_k, k >= 2), or with phase cotangents
-// accumulated (kind_mid = PK_MID_FWD_GT).  Returns the result buffer.
-sr_status fwd_passes(sr_plan_s* p, const Geo& g, const float2* x, int kind_mid, float* gtheta, float2** cur_out) {
+// Whether the phase cotangents go to the scratch of a stack sharing its
+// phases: there each entry's first term is written, not added, so that the
+// scratch needs no clearing.
+bool gth_scratch(const sr_plan_s* p) { return p->stk.P > 1 && p->stk.th_stride == 0; }
+
+// Forward passes 1..L on x, saving u_k (k >= 2) in `save` (kind_mid =
+// PK_MID_FWD_SAVE), or accumulating the phase cotangents of layers 2..L
+// against the saved q_k (PK_MID_FWD_GT, their first term).  step: the first
+// pass works on step x (per problem on a stack; PK_FIRST_FWD_STEP).  Returns
+// the result buffer.
+sr_status fwd_passes(sr_plan_s* p, const Geo& g, const float2* x, int kind_mid, float* gtheta, float2** cur_out,
+                     float2* save, int kind_first = PK_FIRST_FWD, float step = 1.f) {
   float2* bufs[2] = {p->bufA, p->bufB};
   int which = 0;
   {
@@ -119,7 +144,8 @@ sr_status fwd_passes(sr_plan_s* p, const Geo& g, const float2* x, int kind_mid, 
     a.out_lo = 0;
     a.out_hi = g.M1;
     a.scale_out = 1.f / std::sqrt((float)g.M1);
-    VJ_CHECK(launch(p, g, 1, PK_FIRST_FWD, a));
+    a.step = step;
+    VJ_CHECK(launch(p, g, 1, kind_first, a));
   }
   for (int k = 2; k <= g.L; ++k) {
     PassArgs a = base_args(p, g, k);
@@ -129,8 +155,11 @@ sr_status fwd_passes(sr_plan_s* p, const Geo& g, const float2* x, int kind_mid, 
     const float s = 1.f / std::sqrt((float)pass_len(g, k));
     a.scale_mid = s;
     a.scale_out = s;
-    a.save = save_of(p, g, k);
-    if (kind_mid == PK_MID_FWD_GT) a.gth = gth_of(p, g, gtheta, k);
+    a.save = save + (size_t)(k - 2) * p->stk.P * g.mg;
+    if (kind_mid == PK_MID_FWD_GT) {
+      a.gth = gth_of(p, g, gtheta, k);
+      a.gth_set = gth_scratch(p);
+    }
     VJ_CHECK(launch(p, g, k, kind_mid, a));
     which ^= 1;
   }
@@ -138,21 +167,24 @@ sr_status fwd_passes(sr_plan_s* p, const Geo& g, const float2* x, int kind_mid, 
   return SR_OK;
 }
 
-// Adjoint passes from r (full grid): first [F^H], then mids of kind kind_mid
-// (save q_k or accumulate phase cotangents), then the last pass of kind
-// kind_last into x_out.
-sr_status adj_passes(sr_plan_s* p, const Geo& g, const float2* r, int kind_mid, int kind_last, float* gtheta,
-                     const float2* xin, float2* x_out) {
-  const int kt = g.L + 1;
-  float2* cur = p->bufA;
-  float2* other = p->bufB;
-  {
-    PassArgs a = base_args(p, g, kt);
-    in_full(a, g, kt, r);
-      set_out(a, g, kt, cur);
-    a.scale_out = 1.f / std::sqrt((float)pass_len(g, kt));
-    VJ_CHECK(launch(p, g, kt, PK_FIRST_ADJ, a));
-  }
+// The last adjoint pass's operands: the signal-shaped output (and, for the
+// kinds that take them, the first layer's other factor, a term to add, the
+// step, and whether the first layer's cotangents start here).
+struct LastAdj {
+  int kind;
+  float2* out = nullptr;
+  const float2* xin = nullptr;
+  const float2* xadd = nullptr;
+  float step = 1.f;
+  bool first_term = false;
+};
+
+// Adjoint passes L..2 from `cur` (the output of a turnaround or of the
+// adjoint's first pass), mids of kind kind_mid (saving q_k in `save`, or
+// accumulating phase cotangents against the saved u_k), then the last pass.
+sr_status adj_rest(sr_plan_s* p, const Geo& g, float2* cur, int kind_mid, float* gtheta, float2* save, bool first_term,
+                   const LastAdj& last) {
+  float2* other = cur == p->bufA ? p->bufB : p->bufA;
   for (int k = g.L; k >= 2; --k) {
     PassArgs a = base_args(p, g, k);
     in_full(a, g, k, cur);
@@ -161,8 +193,11 @@ sr_status adj_passes(sr_plan_s* p, const Geo& g, const float2* r, int kind_mid, 
     const float s = 1.f / std::sqrt((float)pass_len(g, k));
     a.scale_mid = s;
     a.scale_out = s;
-    a.save = save_of(p, g, k);
-    if (kind_mid == PK_MID_ADJ_GT) a.gth = gth_of(p, g, gtheta, k);
+    a.save = save + (size_t)(k - 2) * p->stk.P * g.mg;
+    if (kind_mid == PK_MID_ADJ_GT) {
+      a.gth = gth_of(p, g, gtheta, k);
+      a.gth_set = first_term && gth_scratch(p);
+    }
     VJ_CHECK(launch(p, g, k, kind_mid, a));
     std::swap(cur, other);
   }
@@ -173,17 +208,36 @@ sr_status adj_passes(sr_plan_s* p, const Geo& g, const float2* r, int kind_mid, 
   a.in_hi = g.M1;
   a.ntr = g.N2;
   a.tr_lo = g.o2;
-  a.out = x_out;
+  a.out = last.out;
   a.out_ld = g.N2;
   a.out_lo = g.o1;
   a.out_hi = g.o1 + g.N1;
   a.th_post = p->theta_l(g, 1);
   a.scale_out = 1.f / std::sqrt((float)g.M1);
-  if (kind_last == PK_LAST_ADJ_GT) {
+  a.xin = last.xin;
+  a.xadd = last.xadd;
+  a.step = last.step;
+  if (last.kind == PK_LAST_ADJ_GT || last.kind == PK_LAST_ADJ_GTV) {
     a.gth = gth_of(p, g, gtheta, 1);
-    a.xin = xin;
+    a.gth_set = last.first_term && gth_scratch(p);
   }
-  return launch(p, g, 1, kind_last, a);
+  return launch(p, g, 1, last.kind, a);
+}
+
+// Adjoint passes from r (measurements): the first, [F^H], then the rest, the
+// phase cotangents (if any) starting here.
+sr_status adj_passes(sr_plan_s* p, const Geo& g, const float2* r, int kind_mid, int kind_last, float* gtheta,
+                     const float2* xin, float2* x_out) {
+  const int kt = g.L + 1;
+  float2* cur = p->bufA;
+  PassArgs a = base_args(p, g, kt);
+  in_full(a, g, kt, r);
+  set_out(a, g, kt, cur);
+  a.scale_out = 1.f / std::sqrt((float)pass_len(g, kt));
+  VJ_CHECK(launch(p, g, kt, PK_FIRST_ADJ, a));
+  LastAdj last{kind_last, x_out, xin};
+  last.first_term = true;
+  return adj_rest(p, g, cur, kind_mid, gtheta, save_of(p, g, 2), true, last);
 }
 
 }  // namespace
@@ -192,7 +246,7 @@ namespace {
 
 // Stack set-up shared by both derivatives: buffers, the registered
 // per-problem strides of the intermediates and of the phase cotangents, and
-// the zeroed per-problem scratch when the stack shares its phases.
+// the per-problem scratch when the stack shares its phases.
 sr_status stack_vjp_setup(sr_plan_s* p, int P, float* gtheta) {
   const Geo& g = p->geo[0];
   for (int k = 2; k <= g.L; ++k) p->stk.add(save_of(p, g, k), g.mg, sizeof(float2), (int)g.mg);
@@ -212,8 +266,6 @@ sr_status stack_vjp_setup(sr_plan_s* p, int P, float* gtheta) {
         return fail(SR_E_NOMEM, "stacked derivative workspace allocation failed");
       p->stk_gth_elems = need;
     }
-    hipError_t e = hipMemsetAsync(p->stk_gth, 0, need * sizeof(float), p->stream);
-    if (e != hipSuccess) return hip_fail(e, "stacked derivative workspace clear");
     p->stk.add(p->stk_gth, block, sizeof(float), (int)block);
   } else {
     p->stk.add(gtheta + g.th_off, block, sizeof(float), p->stk.th_stride);
@@ -226,8 +278,9 @@ sr_status stack_vjp_finish(sr_plan_s* p, int P, float* gtheta) {
   if (p->stk.th_stride != 0) return SR_OK;
   const Geo& g = p->geo[0];
   const long long len = (long long)g.L * g.mg;
-  const int groups = (int)std::min<long long>((len + 255) / 256, 2048);
-  hipLaunchKernelGGL(gth_reduce_kernel, dim3(groups), dim3(256), 0, p->stream, p->stk_gth, gtheta + g.th_off, len, P);
+  const int groups = (int)std::min<long long>((len - g.mg + g.n + 255) / 256, 2048);
+  hipLaunchKernelGGL(gth_reduce_kernel, dim3(groups), dim3(256), 0, p->stream, p->stk_gth, gtheta + g.th_off, len, P,
+                     g.N1, g.N2, g.o1, g.o2, g.M2, (long long)g.mg);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SR_OK : hip_fail(e, "gth_reduce");
 }
@@ -244,7 +297,7 @@ sr_status vjp_forward_stacked(sr_plan_s* p, int P, int ths, const float2* x, con
   if (gx) p->stk.add(gx, g.n, sizeof(float2), (int)g.n);
   float2* gxi = gx ? gx : nscratch(p, g);
   float2* cur = nullptr;
-  if (g.L >= 2) VJ_CHECK(fwd_passes(p, g, x, PK_MID_FWD_SAVE, gtheta, &cur));
+  if (g.L >= 2) VJ_CHECK(fwd_passes(p, g, x, PK_MID_FWD_SAVE, gtheta, &cur, save_of(p, g, 2)));
   VJ_CHECK(adj_passes(p, g, gz, PK_MID_ADJ_GT, PK_LAST_ADJ_GT, gtheta, x, gxi));
   return stack_vjp_finish(p, P, gtheta);
 }
@@ -259,20 +312,10 @@ sr_status vjp_adjoint_stacked(sr_plan_s* p, int P, int ths, const float2* r, con
   p->stk.add(r, g.m, sizeof(float2), (int)g.m);
   p->stk.add(gv, g.n, sizeof(float2), (int)g.n);
   if (gr) p->stk.add(gr, g.m, sizeof(float2), (int)g.m);
-  float2* v = nscratch(p, g);
-  VJ_CHECK(adj_passes(p, g, r, PK_MID_ADJ_SAVE, PK_LAST_ADJ, gtheta, nullptr, v));
-  {
-    const long long n = g.n * P;
-    const int groups = (int)std::min<long long>((n + 255) / 256, 1024);
-    int sg = 0;
-    p->stk.stride_of(gth_of(p, g, gtheta, 1), &sg);
-    hipLaunchKernelGGL(gth_support_kernel, dim3(groups), dim3(256), 0, p->stream, gv, v, gth_of(p, g, gtheta, 1),
-                       g.N1, g.N2, g.o1, g.o2, (long long)g.M2, P, (long long)sg);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(e, "gth_support");
-  }
+  // q_k, and the first layer's term (v = A^H r itself is not wanted)
+  VJ_CHECK(adj_passes(p, g, r, PK_MID_ADJ_SAVE, PK_LAST_ADJ_GTV, gtheta, gv, nullptr));
   float2* cur = nullptr;
-  VJ_CHECK(fwd_passes(p, g, gv, PK_MID_FWD_GT, gtheta, &cur));
+  VJ_CHECK(fwd_passes(p, g, gv, PK_MID_FWD_GT, gtheta, &cur, save_of(p, g, 2)));
   if (gr != nullptr) {
     const int k = g.L + 1;
     PassArgs a = base_args(p, g, k);
@@ -401,7 +444,7 @@ sr_status vjp_forward_levels(sr_plan_s* p, const std::vector<int>& lvl, const fl
       float2* gxi = gx ? gx + p->xoff[i] : nscratch(p, g);
       g_recording = &recs[i];
       float2* cur = nullptr;
-      if (g.L >= 2) status = fwd_passes(p, g, xi, PK_MID_FWD_SAVE, gtheta, &cur);
+      if (g.L >= 2) status = fwd_passes(p, g, xi, PK_MID_FWD_SAVE, gtheta, &cur, save_of(p, g, 2));
       if (status == SR_OK) status = adj_passes(p, g, gz + p->yoff[i], PK_MID_ADJ_GT, PK_LAST_ADJ_GT, gtheta, xi, gxi);
       g_recording = nullptr;
       if (status != SR_OK) return status;
@@ -428,7 +471,7 @@ sr_status vjp_adjoint_levels(sr_plan_s* p, const std::vector<int>& lvl, const fl
       status = adj_passes(p, g, r + p->yoff[i], PK_MID_ADJ_SAVE, PK_LAST_ADJ, gtheta, nullptr, nscratch(p, g));
       g_recording = &rb[i];
       float2* cur = nullptr;
-      if (status == SR_OK) status = fwd_passes(p, g, gv + p->xoff[i], PK_MID_FWD_GT, gtheta, &cur);
+      if (status == SR_OK) status = fwd_passes(p, g, gv + p->xoff[i], PK_MID_FWD_GT, gtheta, &cur, save_of(p, g, 2));
       if (status == SR_OK && gr != nullptr) {
         const int k = g.L + 1;
         PassArgs a = base_args(p, g, k);
@@ -452,7 +495,7 @@ sr_status vjp_adjoint_levels(sr_plan_s* p, const std::vector<int>& lvl, const fl
     const long long n = g.n;
     const int groups = (int)std::min<long long>((n + 255) / 256, 1024);
     hipLaunchKernelGGL(gth_support_kernel, dim3(groups), dim3(256), 0, p->stream, gv + p->xoff[i], v,
-                       gtheta + g.th_off, g.N1, g.N2, g.o1, g.o2, (long long)g.M2, 1, 0LL);
+                       gtheta + g.th_off, g.N1, g.N2, g.o1, g.o2, (long long)g.M2);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "gth_support");
   }
@@ -490,7 +533,7 @@ sr_status vjp_forward(sr_plan_s* p, const float2* x, const float2* gz, float2* g
     }
     float2* gxi = gx ? gx + p->xoff[i] : nscratch(p, g);
     float2* cur = nullptr;
-    if (g.L >= 2) VJ_CHECK(fwd_passes(p, g, xi, PK_MID_FWD_SAVE, gtheta, &cur));
+    if (g.L >= 2) VJ_CHECK(fwd_passes(p, g, xi, PK_MID_FWD_SAVE, gtheta, &cur, save_of(p, g, 2)));
     VJ_CHECK(adj_passes(p, g, gzi, PK_MID_ADJ_GT, PK_LAST_ADJ_GT, gtheta, xi, gxi));
   }
   return SR_OK;
@@ -523,21 +566,11 @@ sr_status vjp_adjoint(sr_plan_s* p, const float2* r, const float2* gv, float2* g
       VJ_CHECK(fused1d_vjp(p, g, F1_ADJ_VJP, a));
       continue;
     }
-    // recompute q_k (k >= 2) and v = A^H r
-    float2* v = nscratch(p, g);
-    VJ_CHECK(adj_passes(p, g, ri, PK_MID_ADJ_SAVE, PK_LAST_ADJ, gtheta, nullptr, v));
-    // first layer: gth_1 += Im(conj(gv) v) on the support
-    {
-      const long long n = g.n;
-      const int groups = (int)std::min<long long>((n + 255) / 256, 1024);
-      hipLaunchKernelGGL(gth_support_kernel, dim3(groups), dim3(256), 0, p->stream, gvi, v, gth_of(p, g, gtheta, 1),
-                         g.N1, g.N2, g.o1, g.o2, (long long)g.M2, 1, 0LL);
-      hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return hip_fail(e, "gth_support");
-    }
+    // recompute q_k (k >= 2); the first layer's term
+    VJ_CHECK(adj_passes(p, g, ri, PK_MID_ADJ_SAVE, PK_LAST_ADJ_GTV, gtheta, gvi, nullptr));
     // forward passes on gv with the cotangents of layers 2..L, then A gv
     float2* cur = nullptr;
-    VJ_CHECK(fwd_passes(p, g, gvi, PK_MID_FWD_GT, gtheta, &cur));
+    VJ_CHECK(fwd_passes(p, g, gvi, PK_MID_FWD_GT, gtheta, &cur, save_of(p, g, 2)));
     if (gr != nullptr) {
       const int k = g.L + 1;
       PassArgs a = base_args(p, g, k);
@@ -635,12 +668,13 @@ sr_status step_bufs(sr_plan_s* p) {
     (void)hipFree(buf);
     return fail(SR_E_NOMEM, "offset table allocation failed");
   }
-  float* sc = nullptr;
-  if (hipMalloc(&sc, np * sizeof(float)) != hipSuccess) {
+  float* sc = p->d_scale;  // (the plan's from here on)
+  if (sc == nullptr && hipMalloc(&sc, np * sizeof(float)) != hipSuccess) {
     (void)hipFree(buf);
     (void)hipFree(off);
     return fail(SR_E_NOMEM, "step table allocation failed");
   }
+  p->d_scale = sc;
   // the plan's offset vectors live as long as the plan: an ordered copy
   hipError_t e = hipMemcpyAsync(off, p->xoff.data(), (np + 1) * sizeof(int64_t), hipMemcpyHostToDevice, p->stream);
   if (e == hipSuccess)
@@ -649,12 +683,113 @@ sr_status step_bufs(sr_plan_s* p) {
   if (e != hipSuccess) {
     (void)hipFree(buf);
     (void)hipFree(off);
-    (void)hipFree(sc);
     return hip_fail(e, "offset table upload");
   }
   p->gstep_buf = buf;
   p->d_off = off;
-  p->d_scale = sc;
+  return SR_OK;
+}
+
+// ---- the reverse step inside the passes
+// Where no problem of the plan runs on the batched levels or in the 1D
+// kernels, the whole reverse step is passes over the problem (or the stack):
+//   [U D_1 F_0](x), mids (u_k saved), the turnaround [F -> z (saved), r -> F^H],
+//   mids (q_k saved), the last adjoint pass (layer 1's adjoint term);
+//   [U D_1 F_0](-(eta/m) xbar+), mids (against q_k), the turnaround
+//   [F -> rbar, zbar and ybar from z -> F^H], mids (against u_k), the last
+//   adjoint pass (layer 1's forward term, plus xbar+).
+// 4 L + 2 passes.  Composed from the operator, the two derivatives and
+// elementwise kernels over whole arrays (the path of the other plans) it was
+// 6 L + 4 passes, since A x was formed twice, and five elementwise kernels of
+// 7 to 27 us: 64 problems on 256^2 grids, L = 2, 309 us a step, now 169 us (each
+// pass at 3.7 to 5.4 TB/s of what it reads and writes).
+
+bool step_in_passes(const sr_plan_s* p, bool stacked) {
+  for (const Geo& g : p->geo)
+    if (g.ndim != 2) return false;
+  return stacked || vjp_level_problems(p).empty();
+}
+
+// z and the saved q_k of the problem (of every problem of a stack), and the
+// stack's per-problem factors.
+sr_status ensure_step_buf(sr_plan_s* p, int P) {
+  size_t need = 0;
+  for (const Geo& g : p->geo) need = std::max(need, (size_t)P * (size_t)g.L * (size_t)g.mg);
+  if (need > p->step_elems) {
+    if (p->step_buf) {
+      // queued work may still use the old buffer
+      if (hipError_t w = hipStreamSynchronize(p->stream); w != hipSuccess) return hip_fail(w, "stream wait");
+      (void)hipFree(p->step_buf);
+      p->step_buf = nullptr;
+      p->step_elems = 0;
+    }
+    if (hipMalloc(&p->step_buf, need * sizeof(float2)) != hipSuccess)
+      return fail(SR_E_NOMEM, "GD-step derivative workspace allocation failed");
+    p->step_elems = need;
+  }
+  if (p->d_scale == nullptr && hipMalloc(&p->d_scale, p->geo.size() * sizeof(float)) != hipSuccess) {
+    p->d_scale = nullptr;
+    return fail(SR_E_NOMEM, "step table allocation failed");
+  }
+  return SR_OK;
+}
+
+// A turnaround of the reverse step from the forward result `cur` into the
+// other ping-pong buffer.
+sr_status step_turn(sr_plan_s* p, const Geo& g, float2* cur, int kind, const float* y, float2* z, float* gy,
+                    float2** back) {
+  const int k = g.L + 1;
+  float2* other = cur == p->bufA ? p->bufB : p->bufA;
+  PassArgs a = base_args(p, g, k);
+  set_in(a, g, k, cur);
+  set_out(a, g, k, other);
+  const float s = 1.f / std::sqrt((float)pass_len(g, k));
+  a.scale_mid = s;
+  a.scale_out = s;
+  a.y = y;
+  a.save = z;
+  a.gy = gy;
+  VJ_CHECK(launch(p, g, k, kind, a));
+  *back = other;
+  return SR_OK;
+}
+
+// One problem (or the stack): s = -eta/m (the stack reads p->stk.steps).
+sr_status step_vjp_passes(sr_plan_s* p, const Geo& g, const float* y, const float2* x, float s, const float2* gxn,
+                          float2* gx, float* gy, float* gtheta) {
+  float2* u = save_of(p, g, 2);
+  float2* z = p->step_buf;
+  float2* q = p->step_buf + (size_t)p->stk.P * g.mg;
+  float2 *cur = nullptr, *back = nullptr;
+  VJ_CHECK(fwd_passes(p, g, x, PK_MID_FWD_SAVE, gtheta, &cur, u));
+  VJ_CHECK(step_turn(p, g, cur, PK_TURN_STEP, y, z, nullptr, &back));
+  LastAdj adj{PK_LAST_ADJ_GTV, nullptr, gxn};
+  adj.step = s;
+  adj.first_term = true;
+  VJ_CHECK(adj_rest(p, g, back, PK_MID_ADJ_SAVE, gtheta, q, false, adj));
+  VJ_CHECK(fwd_passes(p, g, gxn, PK_MID_FWD_GT, gtheta, &cur, q, PK_FIRST_FWD_STEP, s));
+  VJ_CHECK(step_turn(p, g, cur, PK_TURN_STEP_BAR, y, z, gy, &back));
+  LastAdj fwd{PK_LAST_ADJ_GT, gx, x, gxn};
+  return adj_rest(p, g, back, PK_MID_ADJ_GT, gtheta, u, false, fwd);
+}
+
+// The same for the intensities: zbar = 2 ybar z between the two halves.
+sr_status intensity_vjp_passes(sr_plan_s* p, const Geo& g, const float2* x, const float* gy, float2* gx,
+                               float* gtheta) {
+  float2 *cur = nullptr, *back = nullptr;
+  VJ_CHECK(fwd_passes(p, g, x, PK_MID_FWD_SAVE, gtheta, &cur, save_of(p, g, 2)));
+  VJ_CHECK(step_turn(p, g, cur, PK_TURN_INT_BAR, gy, nullptr, nullptr, &back));
+  LastAdj last{PK_LAST_ADJ_GT, gx ? gx : nscratch(p, g), x};
+  last.first_term = true;
+  return adj_rest(p, g, back, PK_MID_ADJ_GT, gtheta, save_of(p, g, 2), true, last);
+}
+
+// Stack set-up for both: buffers and strides.
+sr_status step_stack_setup(sr_plan_s* p, int P, float* gtheta, const float2* x, float2* gx) {
+  const Geo& g = p->geo[0];
+  VJ_CHECK(stack_vjp_setup(p, P, gtheta));
+  p->stk.add(x, g.n, sizeof(float2), (int)g.n);
+  if (gx) p->stk.add(gx, g.n, sizeof(float2), (int)g.n);
   return SR_OK;
 }
 
@@ -662,6 +797,36 @@ sr_status step_bufs(sr_plan_s* p) {
 
 sr_status gd_step_vjp(sr_plan_s* p, const float* y, const float2* x, const float* eta_host, const float2* gxn,
                       float2* gx, float* gy, float* gtheta) {
+  int ths = 0;
+  const int P = stack_size(p, &ths);
+  if (step_in_passes(p, P > 1)) {
+    VJ_CHECK(ensure_vjp_buf(p, P));
+    VJ_CHECK(ensure_step_buf(p, P));
+    if (P == 1) {
+      for (size_t i = 0; i < p->geo.size(); ++i) {
+        const Geo& g = p->geo[i];
+        const int64_t xo = p->xoff[i], yo = p->yoff[i];
+        VJ_CHECK(step_vjp_passes(p, g, y + yo, x + xo, -eta_host[i] / (float)g.m, gxn + xo, gx + xo,
+                                 gy ? gy + yo : nullptr, gtheta));
+      }
+      return SR_OK;
+    }
+    const Geo& g = p->geo[0];
+    std::vector<float> s(P);
+    for (int i = 0; i < P; ++i) s[i] = -eta_host[i] / (float)p->geo[i].m;
+    VJ_CHECK(put_floats(p, p->d_scale, s.data(), P));
+    VJ_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
+    StackScope sc(p, P, ths);
+    p->stk.steps = p->d_scale;
+    VJ_CHECK(step_stack_setup(p, P, gtheta, x, gx));
+    p->stk.add(gxn, g.n, sizeof(float2), (int)g.n);
+    p->stk.add(y, g.m, sizeof(float), (int)g.m);
+    if (gy) p->stk.add(gy, g.m, sizeof(float), (int)g.m);
+    for (int k = 0; k < g.L; ++k)  // z, then q_2..q_L
+      p->stk.add(p->step_buf + (size_t)k * P * g.mg, g.mg, sizeof(float2), (int)g.mg);
+    VJ_CHECK(step_vjp_passes(p, g, y, x, 0.f, gxn, gx, gy, gtheta));
+    return stack_vjp_finish(p, P, gtheta);
+  }
   VJ_CHECK(step_bufs(p));
   const size_t m = (size_t)p->yoff.back(), n = (size_t)p->xoff.back(), np = p->geo.size();
   float2* z = p->gstep_buf;
@@ -691,6 +856,24 @@ sr_status gd_step_vjp(sr_plan_s* p, const float* y, const float2* x, const float
 }
 
 sr_status intensity_vjp(sr_plan_s* p, const float2* x, const float* gy, float2* gx, float* gtheta) {
+  int ths = 0;
+  const int P = stack_size(p, &ths);
+  if (step_in_passes(p, P > 1)) {
+    VJ_CHECK(ensure_vjp_buf(p, P));
+    if (P == 1) {
+      for (size_t i = 0; i < p->geo.size(); ++i)
+        VJ_CHECK(intensity_vjp_passes(p, p->geo[i], x + p->xoff[i], gy + p->yoff[i], gx ? gx + p->xoff[i] : nullptr,
+                                      gtheta));
+      return SR_OK;
+    }
+    const Geo& g = p->geo[0];
+    VJ_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
+    StackScope sc(p, P, ths);
+    VJ_CHECK(step_stack_setup(p, P, gtheta, x, gx));
+    p->stk.add(gy, g.m, sizeof(float), (int)g.m);
+    VJ_CHECK(intensity_vjp_passes(p, g, x, gy, gx, gtheta));
+    return stack_vjp_finish(p, P, gtheta);
+  }
   VJ_CHECK(step_bufs(p));
   const size_t m = (size_t)p->yoff.back();
   float2* z = p->gstep_buf;
