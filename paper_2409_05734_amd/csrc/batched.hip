@@ -458,17 +458,14 @@ sr_status gd_first_pass_public(sr_plan_s* p, const Geo& g, const float2* x);
 sr_status gd_steady_public(sr_plan_s* p, const Geo& g, const float* y, float2* x, float step, bool last,
                            float* loss_part = nullptr);
 
-// Loss trace: out[i * ostride] = sum of problem i's partials, in index order
-// (one thread per problem, the order of the single-problem reduction).
-__global__ void batch_loss_reduce(const float* __restrict__ parts, const int2* __restrict__ desc, int count,
-                                  float* out, int ostride) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < count) {
-    double acc = 0.0;
-    const int2 d = desc[i];
-    for (int k = 0; k < d.y; ++k) acc += (double)parts[d.x + k];
-    out[(long long)i * ostride] = (float)acc;
-  }
+// Loss trace: out[i * ostride] = sum of problem i's partials (one wave per
+// problem, the order of the single-problem reduction).
+__global__ void __launch_bounds__(64) batch_loss_reduce(const float* __restrict__ parts, const int2* __restrict__ desc,
+                                                        float* out, int ostride) {
+  const int i = blockIdx.x;
+  const int2 d = desc[i];
+  const double acc = wave_sum_of(parts + d.x, d.y);
+  if (threadIdx.x == 0) out[(long long)i * ostride] = (float)acc;
 }
 
 // Turn per-problem pass recordings into levels (level q = pass q of every
@@ -524,7 +521,7 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
 static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const float* eta, bool trace,
                                BatchState** out) {
   std::string key = std::to_string((uintptr_t)y) + ":" + std::to_string((uintptr_t)x) + (trace ? ":tr" : "") +
-                    (fused2d_enabled(false) ? ":r" : "");
+                    (fused2d_enabled(false) ? ":r" : "") + loss_key(p);
   for (size_t i = 0; i < p->geo.size(); ++i) {
     uint32_t u;
     std::memcpy(&u, &eta[i], 4);
@@ -836,8 +833,8 @@ static sr_status batched_levels_gd_trace(sr_plan_s* p, const float* y, float2* x
   const int np = (int)p->geo.size();
   for (int it = 0; it < iters; ++it) {
     if ((s = run_levels(p, it == iters - 1 ? st->last : st->steady)) != SR_OK) return s;
-    hipLaunchKernelGGL(batch_loss_reduce, dim3((np + 63) / 64), dim3(64), 0, p->stream, st->parts, st->d_pdesc, np,
-                       loss_trace + it, iters);
+    hipLaunchKernelGGL(batch_loss_reduce, dim3(np), dim3(64), 0, p->stream, st->parts, st->d_pdesc, loss_trace + it,
+                       iters);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "loss-trace reduction");
   }
@@ -984,16 +981,13 @@ __global__ void __launch_bounds__(kSpecRed) spec_setup_stage1(const SpecProb* __
   if (threadIdx.x == 0) ws[(isx ? q.wx : q.wy) + blockIdx.x] = s;
 }
 
-// one thread per problem: sum(y_i) into ysum, ||u_0||^2 as the first
-// partial set's single partial
-__global__ void spec_setup_stage2(const SpecProb* __restrict__ d, int count, const double* __restrict__ ws,
-                                  double* ysum, float* parts) {
-  const int j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= count) return;
-  const SpecProb q = d[j];
-  double a = 0.0, b = 0.0;
-  for (int k = 0; k < q.gy; ++k) a += ws[q.wy + k];
-  for (int k = 0; k < q.gx; ++k) b += ws[q.wx + k];
+// one wave per problem: sum(y_i) into ysum, ||u_0||^2 as the first partial
+// set's single partial
+__global__ void __launch_bounds__(64) spec_setup_stage2(const SpecProb* __restrict__ d, const double* __restrict__ ws,
+                                                        double* ysum, float* parts) {
+  const SpecProb q = d[blockIdx.x];
+  const double a = wave_sum_of(ws + q.wy, q.gy), b = wave_sum_of(ws + q.wx, q.gx);
+  if (threadIdx.x != 0) return;
   ysum[q.idx] = a;
   parts[q.part_off] = (float)b;
 }
@@ -1005,8 +999,7 @@ __global__ void spec_finish(const SpecProb* __restrict__ d, float2* x, const flo
   const SpecProb q = d[blockIdx.y];
   const float* P = parts + q.part_off + ((iters & 1) ? max(q.nq, 1) : 0);
   const int np = iters == 0 ? 1 : q.nq;
-  double acc = 0.0;
-  for (int i = 0; i < np; ++i) acc += (double)P[i];
+  const double acc = wave_sum_of(P, np);  // every wave the same sum
   const float sc = (float)(sqrt(ysum[q.idx] * (double)q.inv_mc) / sqrt(acc));
   bool bad = false;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < q.n; i += (long long)gridDim.x * blockDim.x) {
@@ -1233,7 +1226,7 @@ sr_status batched_spectral(sr_plan_s* p, const std::vector<int>& which, const fl
   // sum(y), u_0 = v0 and its squared norm (one partial), every problem
   hipLaunchKernelGGL(spec_setup_stage1, dim3(st->gmax, st->nprob, 2), dim3(kSpecRed), 0, p->stream, st->d_prob, y, v0,
                      x, st->ws);
-  hipLaunchKernelGGL(spec_setup_stage2, dim3((st->nprob + 63) / 64), dim3(64), 0, p->stream, st->d_prob, st->nprob,
+  hipLaunchKernelGGL(spec_setup_stage2, dim3(st->nprob), dim3(64), 0, p->stream, st->d_prob,
                      st->ws, p->ysum, st->parts);
   if (hipError_t e = hipGetLastError(); e != hipSuccess) return hip_fail(e, "power-iteration set-up");
   const bool two = st->split && st->has[0] && st->has[1];

@@ -400,25 +400,17 @@ __global__ void __launch_bounds__(NT) dense_epi2_kernel(const DenseArgs a) {
   }
 }
 
-// One wave per signal sums its cnt partials: strided per-lane sums in index
-// order, then a fixed tree.  (One thread per signal took the latency of every
-// load in turn, 15 us for 256 partials.)
-__device__ __forceinline__ double wave_row_sum(const float* __restrict__ part, int cnt) {
-  double acc = 0.0;
-  for (int t = threadIdx.x; t < cnt; t += 64) acc += (double)part[t];
-  return block_sum_t<64, double>(acc, nullptr);
-}
-
+// (one wave per signal)
 // inv[p] = 1/sqrt(sum_t part[p][t])
 __global__ void __launch_bounds__(64) inv_norms_kernel(const float* __restrict__ part, int ld, int cnt, float* inv) {
-  const double s = wave_row_sum(part + (long long)blockIdx.x * ld, cnt);
+  const double s = wave_sum_of(part + (long long)blockIdx.x * ld, cnt);
   if (threadIdx.x == 0) inv[blockIdx.x] = (float)(1.0 / sqrt(s));
 }
 
 // out[p * stride] = sum_t part[p][t]
 __global__ void __launch_bounds__(64) sum_rows_kernel(const float* __restrict__ part, int ld, int cnt, float* out,
                                                       int stride) {
-  const double s = wave_row_sum(part + (long long)blockIdx.x * ld, cnt);
+  const double s = wave_sum_of(part + (long long)blockIdx.x * ld, cnt);
   if (threadIdx.x == 0) out[(long long)blockIdx.x * stride] = (float)s;
 }
 

@@ -109,11 +109,12 @@ sr_status sr_plan_s::init(const float* theta_host) {
   size_t b_fs = align256(sizeof(float) * (8 * np + 64));
   size_t b_sync = 256;
   size_t b_red = align256(sizeof(double) * 1024);
+  size_t b_trace = kind == SR_DENSE ? 0 : align256(sizeof(float) * (size_t)sr::kTraceRows * (size_t)part_cap);
   int ngrid = (kind == SR_DENSE) ? 2 : 4;
   size_t b_dsplit = 0;
   if (kind == SR_DENSE)
     b_dsplit = align256(sizeof(float) * sr::dense_split_floats((int)geo[0].m, (int)geo[0].n, (int)np));
-  ws_bytes = b_theta + b_eph + b_tw + ngrid * b_grid + b_part + b_ysum + b_fs + b_sync + b_red + b_dsplit;
+  ws_bytes = b_theta + b_eph + b_tw + ngrid * b_grid + b_part + b_ysum + b_fs + b_sync + b_red + b_trace + b_dsplit;
   hipError_t e = hipMalloc(&ws, ws_bytes);
   if (e != hipSuccess) {
     ws = nullptr;
@@ -146,6 +147,8 @@ sr_status sr_plan_s::init(const float* theta_host) {
   c += b_sync;
   red_ws = (double*)c;
   c += b_red;
+  if (b_trace) trace_part = (float*)c;
+  c += b_trace;
   if (b_dsplit) dsplit = (float*)c;
 
   for (const auto& ta : tw_at) tw[ta.first] = twbuf + ta.second;

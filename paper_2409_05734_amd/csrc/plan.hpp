@@ -30,6 +30,10 @@ struct Geo {
   bool cropped() const { return W1 != M1 || W2 != M2; }
 };
 
+// Iterations whose loss partials a traced solve collects before summing them
+// (the iterations of one captured graph).
+constexpr int kTraceRows = 50;
+
 sr_status fail(sr_status s, const std::string& msg);
 sr_status hip_fail(hipError_t e, const char* what);
 
@@ -113,6 +117,7 @@ struct sr_plan_s {
   float* fscratch = nullptr;  // float scratch (dense solver scalars)
   float* dsplit = nullptr;    // dense plans: split-reduction partial products
   unsigned* sync = nullptr;   // [0] grid-barrier counter, [1] barrier error flag, [2] non-finite flag
+  float* trace_part = nullptr;  // loss partials of a traced solve: kTraceRows iterations' worth (structured plans)
   double* red_ws = nullptr;   // per-workgroup partials of the two-stage reductions (kRedGroups)
   float2* vjp_buf = nullptr;  // per-layer intermediates for derivatives (allocated on first use)
   sr::StackState stk;         // the stack being run (P = 1 outside stacked calls)
@@ -183,9 +188,9 @@ struct sr_plan_s {
 namespace sr {
 
 // util_kernels.hip
-// sum of n partials into *out (count > 1: that many sets of n end to end,
-// set t into out[t * ostride])
-sr_status reduce_partials(sr_plan_s* p, const float* part, int n, float* out, int count = 1, int ostride = 0);
+// loss traces: `rows` iterations' partials, each `count` problems' sets of n
+// end to end; the sum of problem t's set of row r into out[t * ostride + r]
+sr_status reduce_partials(sr_plan_s* p, const float* part, int n, float* out, int rows, int count, int ostride);
 // (count > 1: that many arrays of n elements end to end, each on its own)
 // stage-1 shape of the deterministic reductions of n elements: workgroups
 // and the contiguous chunk each one sums

@@ -325,4 +325,10 @@ inline std::string float_key(float f) {
   return std::to_string(u);
 }
 
+// the plan's loss in the key of a captured graph or a recorded schedule:
+// both hold its turnaround kernel and guard
+inline std::string loss_key(const sr_plan_s* p) {
+  return p->loss == SR_LOSS_POISSON ? ":pois" + float_key(p->loss_eps) : std::string();
+}
+
 }  // namespace sr

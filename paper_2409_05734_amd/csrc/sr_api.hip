@@ -571,6 +571,51 @@ static sr_status flush_1d(sr_plan_s* p, int op, Batch1D& items) {
   return SR_OK;
 }
 
+static bool stream_capturing(const sr_plan_s* p) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  return hipStreamIsCapturing(p->stream, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+
+// The steady iterations of a GD solve after its first pass: chunks replayed
+// from captured graphs (and the steady iterations short of a chunk as one
+// graph of their own: direct launches cost about 1.4 us more per iteration on
+// the 512^2 image), the rest launched directly.  With a trace, iteration
+// `row` of a chunk writes its loss partials to row `row` of a buffer of
+// kTraceRows rows (= the chunk), summed by one launch per chunk
+// (flush(first iteration, rows)); a traced solve under the caller's own stream
+// capture launches every pass directly.
+template <class Step, class Flush>
+static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, bool trace, Step&& step,
+                               Flush&& flush) {
+  static_assert(kTraceRows == kGraphChunk, "a chunk's iterations have a row each");
+  int it = 0;
+  auto steady = [&](int rows) {
+    return [&, rows]() -> sr_status {
+      for (int c = 0; c < rows; ++c) SR_CHECK(step(c, false));
+      return SR_OK;
+    };
+  };
+  if (graphs_enabled(p) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
+    for (; it + kGraphChunk <= iters - 1; it += kGraphChunk) {
+      SR_CHECK(launch_captured(p, key, steady(kGraphChunk)));
+      if (trace) SR_CHECK(flush(it, kGraphChunk));
+    }
+    const int rest = iters - 1 - it;
+    if (rest >= kGraphTail) {
+      SR_CHECK(launch_captured(p, key + ":" + std::to_string(rest), steady(rest)));
+      if (trace) SR_CHECK(flush(it, rest));
+      it += rest;
+    }
+  }
+  while (it < iters) {
+    const int rows = std::min(iters - it, kTraceRows);
+    for (int c = 0; c < rows; ++c) SR_CHECK(step(c, it + c == iters - 1));
+    if (trace) SR_CHECK(flush(it, rows));
+    it += rows;
+  }
+  return SR_OK;
+}
+
 // ====================================================================== ABI
 
 // ------------------------------------------------ no-allocation GD scratch
@@ -751,6 +796,7 @@ sr_status sr_plan_set_workspace(sr_plan p, void* dev_ptr, size_t bytes) {
   mv(p->fscratch);
   mv(p->sync);
   mv(p->red_ws);
+  mv(p->trace_part);
   mv(p->dsplit);
   for (auto& t : p->tw) mv(t.second);
   // recorded schedules and captured graphs hold the old addresses
@@ -932,7 +978,8 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   const Geo& g = p->geo[0];
   SR_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
   const int nparts = turn_groups(p, g);
-  if (loss_trace != nullptr) SR_CHECK(ensure_stack_parts(p, (size_t)P * nparts));
+  if (loss_trace != nullptr)
+    SR_CHECK(ensure_stack_parts(p, (size_t)P * nparts * (size_t)std::min<int>(iters, kTraceRows)));
   if (p->stk_steps_cap < P) {
     if (p->stk_steps) {
       SR_HIP(hipStreamSynchronize(p->stream));  // queued work may still read the old array
@@ -952,33 +999,15 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   p->stk.add(y, g.m, sizeof(float), (int)g.m);
   const float step = steps[0];  // (unused by the stacked update, which reads the array)
   SR_CHECK(first_pass(p, g, x, 1.f, nullptr, 0));
-  int it = 0;
-  if (loss_trace != nullptr) {
-    for (; it < iters; ++it) {
-      SR_CHECK(gd_steady(p, g, y, x, step, p->stk_part, it == iters - 1));
-      SR_CHECK(reduce_partials(p, p->stk_part, nparts, loss_trace + it, P, iters));
-    }
-    return SR_OK;
-  }
-  if (graphs_enabled(p) && iters - 1 >= kGraphChunk) {
-    const std::string key = "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
-                            ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_steps);
-    for (; it + kGraphChunk <= iters - 1; it += kGraphChunk)
-      SR_CHECK(launch_captured(p, key, [&]() -> sr_status {
-        for (int c = 0; c < kGraphChunk; ++c) SR_CHECK(gd_steady(p, g, y, x, step, nullptr, false));
-        return SR_OK;
-      }));
-    const int rest = iters - 1 - it;  // the steady iterations short of a chunk, as one graph of their own
-    if (rest >= kGraphTail) {
-      SR_CHECK(launch_captured(p, key + ":" + std::to_string(rest), [&]() -> sr_status {
-        for (int c = 0; c < rest; ++c) SR_CHECK(gd_steady(p, g, y, x, step, nullptr, false));
-        return SR_OK;
-      }));
-      it += rest;
-    }
-  }
-  for (; it < iters; ++it) SR_CHECK(gd_steady(p, g, y, x, step, nullptr, it == iters - 1));
-  return SR_OK;
+  const std::string key = "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
+                          ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_steps) +
+                          (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) + loss_key(p);
+  return gd_iterations(
+      p, key, iters, loss_trace != nullptr,
+      [&](int row, bool last) -> sr_status {
+        return gd_steady(p, g, y, x, step, loss_trace ? p->stk_part + (size_t)row * P * nparts : nullptr, last);
+      },
+      [&](int it, int rows) { return reduce_partials(p, p->stk_part, nparts, loss_trace + it, rows, P, iters); });
 }
 
 sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, const float* eta_host,
@@ -1026,29 +1055,14 @@ sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, c
     }
     const int nparts = turn_groups(p, g);
     SR_CHECK(first_pass(p, g, xi, 1.f, nullptr, 0));
-    int it = 0;
-    if (lt == nullptr && graphs_enabled(p) && iters - 1 >= kGraphChunk) {
-      const std::string key = "gd:" + std::to_string(i) + ":" + ptr_key(yi) + ":" + ptr_key(xi) + ":" + float_key(step);
-      for (; it + kGraphChunk <= iters - 1; it += kGraphChunk)
-        SR_CHECK(launch_captured(p, key, [&]() -> sr_status {
-          for (int c = 0; c < kGraphChunk; ++c) SR_CHECK(gd_steady(p, g, yi, xi, step, nullptr, false));
-          return SR_OK;
-        }));
-      // the steady iterations short of a chunk, as one graph of their own
-      // (direct launches cost about 1.4 us more per iteration here)
-      const int rest = iters - 1 - it;
-      if (rest >= kGraphTail) {
-        SR_CHECK(launch_captured(p, key + ":" + std::to_string(rest), [&]() -> sr_status {
-          for (int c = 0; c < rest; ++c) SR_CHECK(gd_steady(p, g, yi, xi, step, nullptr, false));
-          return SR_OK;
-        }));
-        it += rest;
-      }
-    }
-    for (; it < iters; ++it) {
-      SR_CHECK(gd_steady(p, g, yi, xi, step, lt ? p->part : nullptr, it == iters - 1));
-      if (lt) SR_CHECK(reduce_partials(p, p->part, nparts, lt + it));
-    }
+    const std::string key = "gd:" + std::to_string(i) + ":" + ptr_key(yi) + ":" + ptr_key(xi) + ":" +
+                            float_key(step) + (lt ? ":tr" : "") + loss_key(p);
+    SR_CHECK(gd_iterations(
+        p, key, iters, lt != nullptr,
+        [&](int row, bool last) -> sr_status {
+          return gd_steady(p, g, yi, xi, step, lt ? p->trace_part + (size_t)row * nparts : nullptr, last);
+        },
+        [&](int it, int rows) { return reduce_partials(p, p->trace_part, nparts, lt + it, rows, 1, iters); }));
   }
   return flush_1d(p, F1_GD, b1);
 }

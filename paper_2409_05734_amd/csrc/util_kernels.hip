@@ -27,25 +27,20 @@ __device__ double block_sum_d(double v, double* red) {
   return r;
 }
 
-// out = sum of part[0..n) in index order (one thread: order is fixed);
-// thread t does the t-th of `count` sets of n partials, into out[t * ostride]
+// One wave per set of n partials, set (r, t) = (blockIdx.x, blockIdx.y) the
+// (r count + t)-th: its sum into out[t * ostride + r]
 // (used for loss traces: a non-finite loss raises the plan's flag nf)
-__global__ void reduce_partials_kernel(const float* __restrict__ part, int n, float* out, int count, int ostride,
-                                       unsigned* nf) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  bool bad = false;
-  if (t < count) {
-    double acc = 0.0;
-    for (int i = 0; i < n; ++i) acc += (double)part[(long long)t * n + i];
-    out[(long long)t * ostride] = (float)acc;
-    bad = !(fabs(acc) <= 3.402823466e38);
-  }
-  flag_nonfinite(nf, bad);
+__global__ void __launch_bounds__(64) reduce_partials_kernel(const float* __restrict__ part, int n, float* out,
+                                                             int count, int ostride, unsigned* nf) {
+  const int r = blockIdx.x, t = blockIdx.y;
+  const double acc = wave_sum_of(part + ((long long)r * count + t) * n, n);
+  if (threadIdx.x == 0) out[(long long)t * ostride + r] = (float)acc;
+  flag_nonfinite(nf, !(fabs(acc) <= 3.402823466e38));
 }
 
 // Two-stage deterministic reductions: stage 1 gives workgroup g the
 // contiguous chunk [g*chunk, (g+1)*chunk) (fixed strided order + fixed tree),
-// stage 2 sums the per-workgroup partials in index order.
+// stage 2 sums the per-workgroup partials over one wave.
 constexpr int kRedGroups = 1024;
 constexpr int kRedStage1 = 256;
 
@@ -77,13 +72,13 @@ __global__ void __launch_bounds__(kRedStage1) norm2_stage1(const float2* __restr
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// stage 2: out = sum of part[0..g) in index order; as double or as float
-// (thread t: the t-th of `count` arrays, whose partials follow one another)
-__global__ void reduce_stage2(const double* __restrict__ part, int g, double* out_d, float* out_f, int count) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t < count) {
-    double acc = 0.0;
-    for (int i = 0; i < g; ++i) acc += part[(long long)t * g + i];
+// stage 2: out = sum of part[0..g), as double or as float; one wave per
+// array, array t of `count` (their partials follow one another)
+__global__ void __launch_bounds__(64) reduce_stage2(const double* __restrict__ part, int g, double* out_d,
+                                                    float* out_f) {
+  const int t = blockIdx.x;
+  const double acc = wave_sum_of(part + (long long)t * g, g);
+  if (threadIdx.x == 0) {
     if (out_d) out_d[t] = acc;
     if (out_f) out_f[t] = (float)acc;
   }
@@ -97,8 +92,7 @@ __global__ void final_scale_kernel(float2* x, long long n, const float* __restri
   x += blockIdx.y * n;
   part += blockIdx.y * npart;
   ysum += blockIdx.y;
-  double acc = 0.0;
-  for (int i = 0; i < npart; ++i) acc += (double)part[i];
+  const double acc = wave_sum_of(part, npart);  // every wave the same sum
   const float sc = (float)(sqrt(*ysum * (double)inv_mc) / sqrt(acc));
   bool bad = false;
   for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
@@ -156,9 +150,10 @@ sr_status fill_phase_table(sr_plan_s* p) {
   return e == hipSuccess ? SR_OK : hip_fail(e, "phase table");
 }
 
-sr_status reduce_partials(sr_plan_s* p, const float* part, int n, float* out, int count, int ostride) {
-  hipLaunchKernelGGL(reduce_partials_kernel, dim3((count + 63) / 64), dim3(64), 0, p->stream, part, n, out, count,
-                     ostride, p->sync + 2);
+sr_status reduce_partials(sr_plan_s* p, const float* part, int n, float* out, int rows, int count, int ostride) {
+  if (rows <= 0) return SR_OK;
+  hipLaunchKernelGGL(reduce_partials_kernel, dim3(rows, count), dim3(64), 0, p->stream, part, n, out, count, ostride,
+                     p->sync + 2);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SR_OK : hip_fail(e, "reduce_partials");
 }
@@ -175,8 +170,7 @@ sr_status sum_floats(sr_plan_s* p, const float* y, int64_t n, double* out, int c
     const int c = std::min(per, count - c0);
     hipLaunchKernelGGL(sum_floats_stage1, dim3(g, c), dim3(kRedStage1), 0, p->stream, y + (int64_t)c0 * n,
                        (long long)n, chunk, p->red_ws);
-    hipLaunchKernelGGL(reduce_stage2, dim3((c + 63) / 64), dim3(64), 0, p->stream, p->red_ws, g, out + c0,
-                       (float*)nullptr, c);
+    hipLaunchKernelGGL(reduce_stage2, dim3(c), dim3(64), 0, p->stream, p->red_ws, g, out + c0, (float*)nullptr);
   }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SR_OK : hip_fail(e, "sum_floats");
@@ -191,8 +185,7 @@ sr_status norm2_partial(sr_plan_s* p, const float2* x, int64_t n, float* out, in
     const int c = std::min(per, count - c0);
     hipLaunchKernelGGL(norm2_stage1, dim3(g, c), dim3(kRedStage1), 0, p->stream, x + (int64_t)c0 * n, (long long)n,
                        chunk, p->red_ws);
-    hipLaunchKernelGGL(reduce_stage2, dim3((c + 63) / 64), dim3(64), 0, p->stream, p->red_ws, g, (double*)nullptr,
-                       out + c0, c);
+    hipLaunchKernelGGL(reduce_stage2, dim3(c), dim3(64), 0, p->stream, p->red_ws, g, (double*)nullptr, out + c0);
   }
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? SR_OK : hip_fail(e, "norm2");
