@@ -6,9 +6,9 @@
 // lengths, layers and step size); level q of a batched iteration runs pass q
 // of every problem that has one.  A launch is a flat list of work items
 // (descriptor, tile); all tiles are 256-thread workgroups, the tile width of
-// each length chosen so that (N / E) * B = 256.  For the GD and power-
-// iteration passes, each (length, axis) runs the default thread shape (E = 8
-// or 12, radix-8 stages) or, where the length has one, the narrow shape (E =
+// each length chosen so that its transforms fill 256 threads.  For the GD and
+// power-iteration passes, each (length, axis) runs the default thread shape
+// (E = 8) or, where the length has one, the narrow shape (E =
 // 4, radix-4 stages, twice the threads per transform), as the level tuner
 // picks per plan.  Each problem owns private ping-pong buffers, so problems
 // never share scratch.
@@ -44,7 +44,7 @@ struct BatchItem {
 
 template <int N, int EV = 0>
 constexpr int batch_b() {
-  return kBatchThreads * (EV ? 4 : FftShape<N>::E) / N;
+  return kBatchThreads / TileV<N, 1, true, true, EV>::TPT;
 }
 
 template <int N, bool COL, int EV = 0>
@@ -224,33 +224,24 @@ __device__ __forceinline__ void run_kind_vjp(const PassArgs& a, int kind, int ti
   }
 }
 
-constexpr size_t kBatchLds = 2 * sizeof(float2) * kBatchThreads * 12;  // covers 2 * B * NP elements for E <= 12
-
-// Length classes of the GD level kernel.  The twelve-element lengths (96,
-// 192, 384) hold the kernel's register count up (about 200 VGPRs, with 27
-// twiddles per thread); without them it needs 124 and no spill, and its
-// tiles fit a 36 KB LDS budget, so four workgroups share a CU.  A GD solve
-// runs the problems with no twelve-element axis on that instantiation and
-// the others on one with every length, on two streams.
-enum LevelCls : int { LEN_ALL = 0, LEN_POW2 = 1, LEN_TWELVE = 2 };
-constexpr int level_groups(int cls) { return cls == LEN_POW2 ? 4 : cls == LEN_TWELVE ? 2 : 3; }
-constexpr size_t level_lds(int cls) {
-  return cls == LEN_POW2 ? 2 * sizeof(float2) * kBatchThreads * 9 : kBatchLds;  // E = 8 tiles pad 1 in 8
-}
-constexpr bool twelve_len(int N) { return N == 96 || N == 192 || N == 384; }
+// LDS of one workgroup: two buffers of 256 threads' eight elements with one pad
+// in eight (the narrow and split shapes need no more).  Every length fits 125
+// VGPRs without spilling, so four workgroups share a CU.
+constexpr size_t kBatchLds = 2 * sizeof(float2) * kBatchThreads * 9;
+constexpr int kBatchGroups = 4;  // workgroups per CU
 
 // Pass sets of the level kernel, one instantiation each (so that no set
 // carries the registers of the others).
 enum LevelSetKind : int { LS_GD = 0, LS_SPEC = 1, LS_OP = 2, LS_VJP = 3 };
 
-template <int N, int SET, int CLS>
+template <int N, int SET>
 __device__ __forceinline__ void run_len(const BatchDesc& d, int tile, float2* lds, float* red) {
-  static_assert(Tile<N, batch_b<N>(), true>::THREADS == kBatchThreads, "batched tiles are 256 threads");
-  static_assert(2 * sizeof(float2) * Tile<N, batch_b<N>(), true>::BUF <= level_lds(CLS), "batched LDS budget");
+  static_assert(TileV<N, batch_b<N>(), true>::THREADS == kBatchThreads, "batched tiles are 256 threads");
+  static_assert(2 * sizeof(float2) * TileV<N, batch_b<N>(), true>::BUF <= kBatchLds, "batched LDS budget");
   if constexpr (HasNarrow<N>::value && (SET == LS_GD || SET == LS_SPEC)) {
     using TN = TileV<N, batch_b<N, 1>(), true, true, 1>;
     static_assert(TN::THREADS == kBatchThreads, "batched narrow tiles are 256 threads");
-    static_assert(2 * sizeof(float2) * TN::BUF <= level_lds(CLS), "batched LDS budget");
+    static_assert(2 * sizeof(float2) * TN::BUF <= kBatchLds, "batched LDS budget");
     if (d.ev) {
       if constexpr (SET == LS_SPEC) {
         if (d.col) run_kind_spec<N, true, 1>(d.a, d.kind, tile, lds, red);
@@ -277,36 +268,23 @@ __device__ __forceinline__ void run_len(const BatchDesc& d, int tile, float2* ld
   }
 }
 
-// The power-of-two class compiles only those lengths; the twelve-element
-// class compiles every length, since its problems may have a power-of-two
-// length on their other axis.
-template <int N, int SET, int CLS>
-__device__ __forceinline__ void run_len_if(const BatchDesc& d, int tile, float2* lds, float* red) {
-  if constexpr (CLS != LEN_POW2 || !twelve_len(N)) run_len<N, SET, CLS>(d, tile, lds, red);
-}
-
-// All lengths: three workgroups per CU (the LDS budget's limit); the compiler
-// fits the kernel in 168 VGPRs (a small spill on the twelve-element lengths)
-// instead of 197, which held it to two (71 -> 62.5 ms on 256 uneven
-// problems).  The power-of-two class: four workgroups per CU, 124 VGPRs, no
-// spill; the twelve-element class: two, no spill.
-template <int SET, int CLS>
-__global__ void __launch_bounds__(kBatchThreads, level_groups(CLS))
+template <int SET>
+__global__ void __launch_bounds__(kBatchThreads, kBatchGroups)
     batched_level_kernel(const BatchItem* __restrict__ items, const BatchDesc* __restrict__ descs) {
   extern __shared__ float2 lds[];
   __shared__ float red[kBatchThreads];
   const BatchItem it = items[xcd_tile(blockIdx.x, gridDim.x)];
   const BatchDesc& d = descs[it.desc];
   switch (d.N) {
-    case 16: run_len_if<16, SET, CLS>(d, it.tile, lds, red); break;
-    case 32: run_len_if<32, SET, CLS>(d, it.tile, lds, red); break;
-    case 64: run_len_if<64, SET, CLS>(d, it.tile, lds, red); break;
-    case 96: run_len_if<96, SET, CLS>(d, it.tile, lds, red); break;
-    case 128: run_len_if<128, SET, CLS>(d, it.tile, lds, red); break;
-    case 192: run_len_if<192, SET, CLS>(d, it.tile, lds, red); break;
-    case 256: run_len_if<256, SET, CLS>(d, it.tile, lds, red); break;
-    case 384: run_len_if<384, SET, CLS>(d, it.tile, lds, red); break;
-    case 512: run_len_if<512, SET, CLS>(d, it.tile, lds, red); break;
+    case 16: run_len<16, SET>(d, it.tile, lds, red); break;
+    case 32: run_len<32, SET>(d, it.tile, lds, red); break;
+    case 64: run_len<64, SET>(d, it.tile, lds, red); break;
+    case 96: run_len<96, SET>(d, it.tile, lds, red); break;
+    case 128: run_len<128, SET>(d, it.tile, lds, red); break;
+    case 192: run_len<192, SET>(d, it.tile, lds, red); break;
+    case 256: run_len<256, SET>(d, it.tile, lds, red); break;
+    case 384: run_len<384, SET>(d, it.tile, lds, red); break;
+    case 512: run_len<512, SET>(d, it.tile, lds, red); break;
     default: break;
   }
 }
@@ -347,38 +325,20 @@ hipError_t launch_level_set0(dim3 grid, hipStream_t s, const void* items, const 
 hipError_t launch_level_set1(dim3 grid, hipStream_t s, const void* items, const void* descs);
 hipError_t launch_level_set2(dim3 grid, hipStream_t s, const void* items, const void* descs);
 hipError_t launch_level_set3(dim3 grid, hipStream_t s, const void* items, const void* descs);
-// the GD and spectral sets by length class (SR_LEVEL_SET = 0 / 1 built with
-// SR_LEVEL_CLS = 1 / 2): launch_level_s<set>_c<class>
-hipError_t launch_level_s0_c1(dim3 grid, hipStream_t s, const void* items, const void* descs);
-hipError_t launch_level_s0_c2(dim3 grid, hipStream_t s, const void* items, const void* descs);
-hipError_t launch_level_s1_c1(dim3 grid, hipStream_t s, const void* items, const void* descs);
-hipError_t launch_level_s1_c2(dim3 grid, hipStream_t s, const void* items, const void* descs);
-
 #if defined(SR_LEVEL_SET)
-#if !defined(SR_LEVEL_CLS) || SR_LEVEL_CLS == 0
 #define SR_LAUNCHER_NAME(k) launch_level_set##k
 #define SR_LAUNCHER(k) SR_LAUNCHER_NAME(k)
 hipError_t SR_LAUNCHER(SR_LEVEL_SET)(dim3 grid, hipStream_t s, const void* items, const void* descs) {
-  hipLaunchKernelGGL((batched_level_kernel<SR_LEVEL_SET, LEN_ALL>), grid, dim3(kBatchThreads), level_lds(LEN_ALL), s,
+  hipLaunchKernelGGL((batched_level_kernel<SR_LEVEL_SET>), grid, dim3(kBatchThreads), kBatchLds, s,
                      (const BatchItem*)items, (const BatchDesc*)descs);
   return hipGetLastError();
 }
-#else
-#define SR_CLS_LAUNCHER_NAME(k, c) launch_level_s##k##_c##c
-#define SR_CLS_LAUNCHER(k, c) SR_CLS_LAUNCHER_NAME(k, c)
-hipError_t SR_CLS_LAUNCHER(SR_LEVEL_SET, SR_LEVEL_CLS)(dim3 grid, hipStream_t s, const void* items, const void* descs) {
-  hipLaunchKernelGGL((batched_level_kernel<SR_LEVEL_SET, SR_LEVEL_CLS>), grid, dim3(kBatchThreads),
-                     level_lds(SR_LEVEL_CLS), s, (const BatchItem*)items, (const BatchDesc*)descs);
-  return hipGetLastError();
-}
-#endif
 }  // namespace sr
 #else
 
 // Level lists of one recorded pass sequence (device descriptors and items).
 struct LevelSet {
   int set = LS_GD;  // pass set (which instantiation of the level kernel)
-  int cls = LEN_ALL;  // length class (GD set only)
   BatchDesc* d_descs = nullptr;
   BatchItem* d_items = nullptr;
   std::vector<int> level_off, level_cnt;  // item ranges per level
@@ -395,9 +355,7 @@ struct LevelSet {
 struct BatchState {
   std::string key;
   LevelSet first, steady, last;  // every problem (loss traces)
-  // without a trace: the same per length class of the problem (0: both
-  // axes a power of two, 1: an axis of twelve-element length), each on its
-  // own instantiation and stream
+  // without a trace: the same per group of problems, each on its own stream
   LevelSet cfirst[2], csteady[2], clast[2];
   bool has[2] = {false, false};
   bool split = false;
@@ -477,11 +435,34 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
   std::vector<BatchItem> items;
   ls.level_off.assign(max_levels, 0);
   ls.level_cnt.assign(max_levels, 0);
+  // a problem with fewer passes than the deepest starts at the level that
+  // leaves the levels' loads most even (with every problem starting at level 0
+  // the last levels hold a third of the first ones' work; 256 problems of one
+  // to three layers: 10.4 -> 9.9 ms)
+  std::vector<size_t> shift(recs.size(), 0);
+  std::vector<int64_t> load(max_levels, 0);
+  std::vector<std::pair<int64_t, size_t>> order;
+  for (size_t i = 0; i < recs.size(); ++i)
+    if (!recs[i].empty()) order.push_back({-(int64_t)recs[i].size() * ((int64_t)1 << 40) - p->geo[i].mg, i});
+  std::sort(order.begin(), order.end());
+  for (const auto& o : order) {
+    const size_t i = o.second, n = recs[i].size();
+    int64_t best = -1;
+    for (size_t s0 = 0; s0 + n <= max_levels; ++s0) {
+      int64_t top = 0;
+      for (size_t q = s0; q < s0 + n; ++q) top = std::max(top, load[q]);
+      if (best < 0 || top < best) {
+        best = top;
+        shift[i] = s0;
+      }
+    }
+    for (size_t q = shift[i]; q < shift[i] + n; ++q) load[q] += p->geo[i].mg;
+  }
   for (size_t q = 0; q < max_levels; ++q) {
     ls.level_off[q] = (int)items.size();
     for (size_t i = 0; i < recs.size(); ++i) {
-      if (q >= recs[i].size()) continue;
-      const PassRecord& r = recs[i][q];
+      if (q < shift[i] || q - shift[i] >= recs[i].size()) continue;
+      const PassRecord& r = recs[i][q - shift[i]];
       const Geo& g = p->geo[i];
       BatchDesc d;
       std::memset(&d, 0, sizeof(d));
@@ -514,6 +495,36 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
   if (e == hipSuccess) e = hipStreamSynchronize(p->stream);  // the host vectors go out of scope
   if (e != hipSuccess) return hip_fail(e, "batched descriptor upload");
   return SR_OK;
+}
+
+// Two groups of a plan's level problems, balanced by grid points times passes
+// (largest first, each to the lighter group).  The groups are independent, so
+// each runs on its own stream and one's launch boundaries and last workgroups
+// are covered by the other: 20 power and 40 GD iterations of 256 problems take
+// 9.9 ms in two groups and 10.4 ms in one, of 128 problems 5.0 and 6.0 ms.
+// Plans of fewer points keep one group: 64 problems (2.3 M points) gain 5 %
+// while calls are queued and lose 10 % from an idle GPU.  Returns 0 / 1 per
+// problem of the plan.  SR_BATCH_STREAMS=1: one group.
+constexpr int64_t kGroupPoints = 4000000;
+static std::vector<int> level_groups(const sr_plan_s* p, const std::vector<int>& which) {
+  std::vector<int> grp(p->geo.size(), 0);
+  const char* ns = std::getenv("SR_BATCH_STREAMS");
+  if (ns != nullptr && std::atoi(ns) == 1) return grp;
+  int64_t points = 0;
+  std::vector<std::pair<int64_t, int>> order;
+  for (int i : which) {
+    points += p->geo[i].mg;
+    order.push_back({-p->geo[i].mg * p->geo[i].L, i});
+  }
+  if (which.size() < 2 || points < kGroupPoints) return grp;
+  std::sort(order.begin(), order.end());
+  int64_t load[2] = {0, 0};
+  for (const auto& o : order) {
+    const int c = load[1] < load[0] ? 1 : 0;
+    grp[o.second] = c;
+    load[c] -= o.first;
+  }
+  return grp;
 }
 
 // Build (or reuse) the level sets for GD on (y, x, eta), with or without the
@@ -603,6 +614,10 @@ static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const fl
   st->split = !trace && !batched_any_resident(p);  // (the aux stream serves the LDS-resident solver otherwise)
   if (st->split) {
     std::vector<std::vector<PassRecord>> cf[2], cs[2], cl[2];
+    std::vector<int> which;
+    for (size_t i = 0; i < np; ++i)
+      if (!rec_first[i].empty()) which.push_back((int)i);
+    const std::vector<int> grp = level_groups(p, which);
     for (int c = 0; c < 2; ++c) {
       cf[c].assign(np, {});
       cs[c].assign(np, {});
@@ -611,8 +626,7 @@ static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const fl
     }
     for (size_t i = 0; i < np; ++i) {
       if (rec_first[i].empty()) continue;
-      const Geo& g = p->geo[i];
-      const int c = (twelve_len(g.M1) || twelve_len(g.M2)) ? 1 : 0;
+      const int c = grp[i];
       cf[c][i] = std::move(rec_first[i]);
       cs[c][i] = std::move(rec_steady[i]);
       cl[c][i] = std::move(rec_last[i]);
@@ -620,8 +634,6 @@ static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const fl
     }
     for (int c = 0; c < 2; ++c) {
       if (!st->has[c]) continue;
-      const int cls = c == 0 ? LEN_POW2 : LEN_TWELVE;
-      st->cfirst[c].cls = st->csteady[c].cls = st->clast[c].cls = cls;
       if ((status = build_levels(p, cf[c], st->cfirst[c])) != SR_OK) return status;
       if ((status = build_levels(p, cs[c], st->csteady[c])) != SR_OK) return status;
       if ((status = build_levels(p, cl[c], st->clast[c])) != SR_OK) return status;
@@ -642,11 +654,7 @@ static sr_status run_levels(sr_plan_s* p, const LevelSet& ls) {
     const dim3 grid(ls.level_cnt[q]);
     const BatchItem* items = ls.d_items + ls.level_off[q];
     hipError_t e;
-    if (ls.set == LS_GD && ls.cls == LEN_POW2) e = launch_level_s0_c1(grid, p->stream, items, ls.d_descs);
-    else if (ls.set == LS_GD && ls.cls == LEN_TWELVE) e = launch_level_s0_c2(grid, p->stream, items, ls.d_descs);
-    else if (ls.set == LS_SPEC && ls.cls == LEN_POW2) e = launch_level_s1_c1(grid, p->stream, items, ls.d_descs);
-    else if (ls.set == LS_SPEC && ls.cls == LEN_TWELVE) e = launch_level_s1_c2(grid, p->stream, items, ls.d_descs);
-    else if (ls.set == LS_SPEC) e = launch_level_set1(grid, p->stream, items, ls.d_descs);
+    if (ls.set == LS_SPEC) e = launch_level_set1(grid, p->stream, items, ls.d_descs);
     else if (ls.set == LS_OP) e = launch_level_set2(grid, p->stream, items, ls.d_descs);
     else if (ls.set == LS_VJP) e = launch_level_set3(grid, p->stream, items, ls.d_descs);
     else e = launch_level_set0(grid, p->stream, items, ls.d_descs);
@@ -799,11 +807,7 @@ static sr_status batched_levels_gd(sr_plan_s* p, const float* y, float2* x, int 
   sr_status s = batch_prepare(p, y, x, eta, false, &st);
   if (s != SR_OK) return s;
   if (!st->split) return levels_gd_run(p, st->first, st->steady, st->last, iters, "batch:" + st->key);
-  // the two length classes are independent problems: the twelve-element one
-  // on the auxiliary stream beside the other (SR_BATCH_STREAMS=1: both on
-  // the plan's stream, one after the other)
-  const char* ns = std::getenv("SR_BATCH_STREAMS");
-  const bool two = st->has[0] && st->has[1] && (ns == nullptr || std::atoi(ns) != 1);
+  const bool two = st->has[0] && st->has[1];  // the second group on the auxiliary stream
   if (two && (s = aux_fork(p)) != SR_OK) return s;
   for (int c = 0; c < 2 && s == SR_OK; ++c) {
     if (!st->has[c]) continue;
@@ -1021,8 +1025,7 @@ struct SpecBatchState {
   std::vector<size_t> part_off;
   std::vector<int> nq;                 // partials per set (tiles of the last pass)
   // the level sets: of every problem in cls[0] (split == false), or per
-  // length class of the problem (0: both axes a power of two, 1: an axis
-  // of twelve-element length), each on its own instantiation and stream
+  // group of problems, each on its own stream
   SpecSets cls[2];
   bool has[2] = {false, false};
   bool split = false;
@@ -1158,28 +1161,25 @@ static sr_status spec_prepare(sr_plan_s* p, const std::vector<int>& which, const
     if (e == hipSuccess) e = hipStreamSynchronize(p->stream);  // dp goes out of scope
     if (e != hipSuccess) return hip_fail(e, "batched power-iteration descriptors");
   }
-  // level sets, per length class where the auxiliary stream is free (the
+  // level sets, per group where the auxiliary stream is free (the
   // LDS-resident problems' solves use it otherwise)
   std::vector<std::vector<PassRecord>>* recsets[7] = {&r_first, &r_it0, &r_it0l, &r_odd, &r_oddl, &r_even, &r_evenl};
   st->split = !batched_any_resident(p);
   st->has[0] = st->has[1] = false;
+  const std::vector<int> grp = st->split ? level_groups(p, which) : std::vector<int>(np, 0);
   for (int c = 0; c < 2; ++c) {
     std::vector<std::vector<PassRecord>> part[7];
     for (int k = 0; k < 7; ++k) part[k].assign(np, {});
     for (int i : which) {
-      const Geo& g = p->geo[i];
-      const int ci = st->split && (twelve_len(g.M1) || twelve_len(g.M2)) ? 1 : 0;
-      if (ci != c) continue;
+      if (grp[i] != c) continue;
       for (int k = 0; k < 7; ++k) part[k][i] = (*recsets[k])[i];
       st->has[c] = true;
     }
     if (!st->has[c]) continue;
     SpecSets& S = st->cls[c];
     LevelSet* sets[7] = {&S.first, &S.it0, &S.it0_last, &S.odd, &S.odd_last, &S.even, &S.even_last};
-    const int cls = !st->split ? LEN_ALL : c == 0 ? LEN_POW2 : LEN_TWELVE;
     for (int k = 0; k < 7; ++k) {
       sets[k]->set = LS_SPEC;
-      sets[k]->cls = cls;
       if ((status = build_levels(p, part[k], *sets[k])) != SR_OK) return status;
     }
   }

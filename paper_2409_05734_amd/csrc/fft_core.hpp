@@ -2,9 +2,10 @@
 // register/LDS Stockham transform over a tile of B independent length-N
 // transforms.
 //
-// Layout contract ("canonical" register layout): the TPT = N/E threads of one
-// transform each hold E elements; thread t holds elements k = t + j*TPT,
-// j = 0..E-1.  Both the input and the output of `Tile::fft` use this layout,
+// Layout contract ("canonical" register layout): the ACT = N/E active threads
+// of one transform each hold E elements; thread t holds elements k = t + j*ACT,
+// j = 0..E-1.  (A transform is allocated TPT threads; TPT = ACT except for the
+// split shapes of the lengths with a factor of three.)  Both the input and the output of `Tile::fft` use this layout,
 // so that pointwise work between two transforms (phase diagonals, epilogues)
 // happens in registers, and global loads/stores along a contiguous axis are
 // coalesced.
@@ -259,6 +260,53 @@ struct Dft<16, INV> {
   }
 };
 
+// 6 = 2 x 3 with coprime factors, so no twiddles between them: index
+// n = 3 n1 + 2 n2 (mod 6) in, k = 3 k1 + 4 k2 (mod 6) out (the Chinese
+// remainder map); three 2-point DFTs over n1, two 3-point DFTs over n2.
+template <bool INV>
+struct Dft<6, INV> {
+  __device__ __forceinline__ static void run(float2* u) {
+    float2 a[3][2];
+#pragma unroll
+    for (int n2 = 0; n2 < 3; ++n2) {
+      const float2 x = u[(2 * n2) % 6], y = u[(3 + 2 * n2) % 6];
+      a[n2][0] = cadd(x, y);
+      a[n2][1] = csub(x, y);
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 2; ++k1) {
+      float2 t[3] = {a[0][k1], a[1][k1], a[2][k1]};
+      Dft<3, INV>::run(t);
+#pragma unroll
+      for (int k2 = 0; k2 < 3; ++k2) u[(3 * k1 + 4 * k2) % 6] = t[k2];
+    }
+  }
+};
+
+// 12 = 3 x 4 with coprime factors, so no twiddles between them: index
+// n = 4 n1 + 3 n2 (mod 12) in, k = 4 k1 + 9 k2 (mod 12) out (the Chinese
+// remainder map); four 3-point DFTs over n1, three 4-point DFTs over n2.
+template <bool INV>
+struct Dft<12, INV> {
+  __device__ __forceinline__ static void run(float2* u) {
+    float2 a[4][3];
+#pragma unroll
+    for (int n2 = 0; n2 < 4; ++n2) {
+      float2 t[3] = {u[(3 * n2) % 12], u[(4 + 3 * n2) % 12], u[(8 + 3 * n2) % 12]};
+      Dft<3, INV>::run(t);
+#pragma unroll
+      for (int k1 = 0; k1 < 3; ++k1) a[n2][k1] = t[k1];
+    }
+#pragma unroll
+    for (int k1 = 0; k1 < 3; ++k1) {
+      float2 t[4] = {a[0][k1], a[1][k1], a[2][k1], a[3][k1]};
+      Dft<4, INV>::run(t);
+#pragma unroll
+      for (int k2 = 0; k2 < 4; ++k2) u[(4 * k1 + 9 * k2) % 12] = t[k2];
+    }
+  }
+};
+
 // ------------------------------------------------------------- radix lists
 template <int... Rs>
 struct RadixList {
@@ -290,10 +338,10 @@ template <> struct FftShape<2048> { static constexpr int E = 8;  using R = Radix
 template <> struct FftShape<4096> { static constexpr int E = 8;  using R = RadixList<8, 8, 8, 8>; };
 template <> struct FftShape<24>   { static constexpr int E = 12; using R = RadixList<3, 4, 2>; };
 template <> struct FftShape<48>   { static constexpr int E = 12; using R = RadixList<3, 4, 4>; };
-template <> struct FftShape<96>   { static constexpr int E = 12; using R = RadixList<3, 4, 4, 2>; };
-template <> struct FftShape<192>  { static constexpr int E = 12; using R = RadixList<3, 4, 4, 4>; };
-template <> struct FftShape<384>  { static constexpr int E = 12; using R = RadixList<3, 4, 4, 4, 2>; };
-template <> struct FftShape<768>  { static constexpr int E = 12; using R = RadixList<3, 4, 4, 4, 4>; };
+template <> struct FftShape<96>   { static constexpr int E = 12; using R = RadixList<12, 4, 2>; };
+template <> struct FftShape<192>  { static constexpr int E = 12; using R = RadixList<12, 4, 4>; };
+template <> struct FftShape<384>  { static constexpr int E = 12; using R = RadixList<12, 4, 4, 2>; };
+template <> struct FftShape<768>  { static constexpr int E = 12; using R = RadixList<12, 4, 4, 4>; };
 
 // Narrow variant of the power-of-two lengths: four elements per thread
 // (radix-4 stages, one radix-2 stage for odd powers), i.e. twice the threads
@@ -307,6 +355,22 @@ template <> struct FftNarrow<128>  { using R = RadixList<4, 4, 4, 2>; };
 template <> struct FftNarrow<256>  { using R = RadixList<4, 4, 4, 4>; };
 template <> struct FftNarrow<512>  { using R = RadixList<4, 4, 4, 4, 2>; };
 template <> struct FftNarrow<1024> { using R = RadixList<4, 4, 4, 4, 4>; };
+// Split shapes of the lengths with a factor of three: N/8 threads hold eight
+// elements each for the loads, the stores and the first and last stages, and
+// the stage between them, whose radix takes the factor of three, spreads its
+// butterflies over the power of two of threads (T) that the transform is
+// allocated.  Three stages, and as few registers as the powers of two: twelve
+// elements per thread throughout take four or five stages, half the threads
+// and up to 36 twiddles each, and a length of 384 or 768 then has as few
+// waves and as long a chain a wave as a power of two twice as long (768 x 384
+// grid, [F D F] row pass: 8.3 us in radices 3, 4, 4, 4, 2 with twelve
+// elements, 4.6 us this way).
+template <int N> struct FftSplit { static constexpr bool value = false; };
+template <> struct FftSplit<96>  { static constexpr bool value = true; static constexpr int T = 16;  using R = RadixList<8, 3, 4>; };
+template <> struct FftSplit<192> { static constexpr bool value = true; static constexpr int T = 32;  using R = RadixList<8, 3, 8>; };
+template <> struct FftSplit<384> { static constexpr bool value = true; static constexpr int T = 64;  using R = RadixList<8, 6, 8>; };
+template <> struct FftSplit<768> { static constexpr bool value = true; static constexpr int T = 128; using R = RadixList<8, 12, 8>; };
+
 // Wide thread shape: sixteen elements per thread with radix-16 stages, for
 // column tiles of eight 2048-point transforms in 1024 threads.
 template <int N> struct FftWide;
@@ -327,16 +391,23 @@ template <> struct HasNarrow<1024> { static constexpr bool value = true; };
 // lane = b*TPT + t with LDS layout [b][k + pad].  DB: ping-pong LDS buffers
 // (one barrier per stage) or a single buffer (half the LDS, two barriers per
 // stage) -- the single buffer lets two large column tiles share a CU.
-template <int N, int B, bool COL, bool DB = true, int E_ = FftShape<N>::E, class RL = typename FftShape<N>::R>
+template <int N, int B, bool COL, bool DB = true, int E_ = FftShape<N>::E, class RL = typename FftShape<N>::R,
+          int T_ = N / E_>
 struct Tile {
   static constexpr int E = E_;
-  static constexpr int TPT = N / E;
+  static constexpr int TPT = T_;     // threads allocated to one transform
+  static constexpr int ACT = N / E;  // threads that hold elements of it
   static constexpr int THREADS = TPT * B;
   // One pad slot every R0 elements for radix-8- or radix-4-first lengths:
   // the stage-0 scatter (stride R0) would otherwise put lanes on one LDS
-  // bank pair.
-  static constexpr int PADSHIFT =
-      RL::values[0] == 16 ? 4 : RL::values[0] == 8 ? 3 : (RL::values[0] == 4 && E_ == 4) ? 2 : 0;
+  // bank pair.  Radix-12-first lengths take one every 32, which spreads both
+  // that scatter and the later stages' reads (768 points as rows: 208 LDS
+  // cycles a wave for all exchanges by bank count, 248 without pads, 264 and
+  // 288 with one every 4 or 8).
+  static constexpr int PADSHIFT = RL::values[0] == 16   ? 4
+                                  : RL::values[0] == 12 ? 5
+                                  : RL::values[0] == 8  ? 3
+                                  : (RL::values[0] == 4 && E_ == 4) ? 2 : 0;
   static constexpr int NP = PADSHIFT ? N + (N >> PADSHIFT) : N;  // padded transform length
   static constexpr int LD = NP;               // row-mode LDS stride
   static constexpr int BUF = B * NP;          // complex elements per LDS buffer
@@ -348,14 +419,26 @@ struct Tile {
   __device__ __forceinline__ static int lidx(int b, int k) { return COL ? (padk(k) * B + b) : (b * LD + padk(k)); }
   __device__ __forceinline__ static int thread_t() { return COL ? (int)(threadIdx.x / B) : (int)(threadIdx.x % TPT); }
   __device__ __forceinline__ static int thread_b() { return COL ? (int)(threadIdx.x % B) : (int)(threadIdx.x / TPT); }
-  __device__ __forceinline__ static int elem(int t, int j) { return t + j * TPT; }
+  __device__ __forceinline__ static int elem(int t, int j) { return t + j * ACT; }
+  // Whether thread t holds elements (the callers give the others zeros and
+  // drop their results).
+  __device__ __forceinline__ static bool holds(int t) { return ACT == TPT || t < ACT; }
+
+  // Stage S: butterflies per thread, and the threads that have them.  The
+  // first and last stages work on the canonical layout, the others on what
+  // the exchanges through LDS hand them.
+  static constexpr bool canonical(int S) { return S == 0 || S + 1 == RL::count; }
+  static constexpr int stage_q(int S) {
+    return canonical(S) ? E / RL::values[S] : (N / RL::values[S] + TPT - 1) / TPT;
+  }
+  static constexpr int stage_act(int S) { return N / RL::values[S] / stage_q(S); }
 
   // Twiddle factors this thread needs, preloaded into registers once
   // (stages >= 1; stage 0 has span 1 and no twiddles).  Forward and inverse
   // transforms of the same length share them (the inverse conjugates).
   static constexpr int tw_offset(int S) {
     int c = 0;
-    for (int s = 1; s < S && s < RL::count; ++s) c += (E / RL::values[s]) * (RL::values[s] - 1);
+    for (int s = 1; s < S && s < RL::count; ++s) c += stage_q(s) * (RL::values[s] - 1);
     return c;
   }
   static constexpr int NTW = tw_offset(RL::count) > 0 ? tw_offset(RL::count) : 1;
@@ -377,6 +460,12 @@ struct Tile {
 #pragma unroll
       for (int i = 0; i < NTW; ++i) w[i] = tw[i * TPT + t];
     }
+  }
+
+  // This thread's twiddle slot i.
+  __device__ __forceinline__ static float2 twiddle(const Twiddles& w, int i) {
+    if constexpr (LAZY_TW) return w.p[i * TPT];
+    else return w[i];
   }
 
   // Host: calls f(slot, t, e) for every twiddle slot of every thread, where
@@ -404,11 +493,12 @@ struct Tile {
     if constexpr (S < RL::count) {
       constexpr int R = RL::values[S];
       constexpr int P = RL::span(S);
-      constexpr int Q = E / R;
+      constexpr int Q = stage_q(S);
+      constexpr int A = stage_act(S);
       constexpr int STRIDE = N / (P * R);
-      for (int t = 0; t < TPT; ++t)
+      for (int t = 0; t < A; ++t)
         for (int q = 0; q < Q; ++q) {
-          const int k = (t + q * TPT) % P;
+          const int k = (t + q * A) % P;
           for (int r = 1; r < R; ++r) f(tw_offset(S) + q * (R - 1) + (r - 1), t, r * k * STRIDE);
         }
       twiddle_stage<S + 1>(f);
@@ -435,32 +525,49 @@ struct Tile {
     if constexpr (S < RL::count) {
       constexpr int R = RL::values[S];
       constexpr int P = RL::span(S);
-      constexpr int Q = E / R;  // butterflies per thread in this stage
-      static_assert(E % R == 0, "radix must divide elements per thread");
+      constexpr int Q = stage_q(S);    // butterflies per thread in this stage
+      constexpr int A = stage_act(S);  // threads that have them
+      constexpr bool LAST = S + 1 == RL::count;
+      static_assert(N % (R * Q) == 0 && A <= TPT, "a stage's butterflies divide evenly over its threads");
+      static_assert(!canonical(S) || (E % R == 0 && A == ACT), "the outer stages keep the canonical layout");
+      const bool mine = A == TPT || t < A;
       // this stage's twiddles (from registers, or loaded from the table now,
       // in flight across the exchange below)
       constexpr int NS = S > 0 ? Q * (R - 1) : 1;
       float2 ws[NS];
       if constexpr (S > 0) {
 #pragma unroll
-        for (int i = 0; i < NS; ++i) {
-          if constexpr (LAZY_TW) ws[i] = w.p[(tw_offset(S) + i) * TPT];
-          else ws[i] = w[tw_offset(S) + i];
-        }
+        for (int i = 0; i < NS; ++i) ws[i] = twiddle(w, tw_offset(S) + i);
       }
+      // butterfly q's input r sits at i + r N/R, i = t + q A (for the outer
+      // stages that is canonical element q + r Q)
+      float2 x[Q * R];
       if constexpr (S > 0) {
-        // inputs of this stage: canonical positions in the buffer written last
         xsync();
-        float2* src = DB ? lds + (phase ^ 1) * BUF : lds;
+        const float2* src = DB ? lds + (phase ^ 1) * BUF : lds;
+        if (mine) {
 #pragma unroll
-        for (int j = 0; j < E; ++j) v[j] = src[lidx(b, elem(t, j))];
+          for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int r = 0; r < R; ++r) x[q + r * Q] = src[lidx(b, t + q * A + r * (N / R))];
+        } else {
+#pragma unroll
+          for (int j = 0; j < Q * R; ++j) x[j] = make_float2(0.f, 0.f);
+        }
+      } else {
+#pragma unroll
+        for (int j = 0; j < E; ++j) x[j] = v[j];
       }
+      // single buffer: every thread must be done reading it (this stage's
+      // loads, or an earlier transform's) before anyone overwrites it
+      if constexpr (!DB && !LAST) xsync();
+      float2* dst = DB ? lds + phase * BUF : lds;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         float2 u[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) u[r] = v[q + r * Q];
-        const int i = t + q * TPT;
+        for (int r = 0; r < R; ++r) u[r] = x[q + r * Q];
+        const int i = t + q * A;
         const int k = i % P;
         if constexpr (S > 0) {
 #pragma unroll
@@ -470,32 +577,36 @@ struct Tile {
           }
         }
         Dft<R, INV>::run(u);
-        if constexpr (S + 1 < RL::count) {
-          if constexpr (!DB) {
-            // single buffer: every thread must be done reading it (this stage's
-            // loads, or an earlier transform's) before anyone overwrites it
-            if (q == 0) xsync();
-          }
-          float2* dst = DB ? lds + phase * BUF : lds;
-          const int base = (i / P) * P * R + k;
+        if constexpr (!LAST) {
+          if (mine) {
+            const int base = (i / P) * P * R + k;
 #pragma unroll
-          for (int r = 0; r < R; ++r) dst[lidx(b, base + r * P)] = u[r];
+            for (int r = 0; r < R; ++r) dst[lidx(b, base + r * P)] = u[r];
+          }
         } else {
 #pragma unroll
           for (int r = 0; r < R; ++r) v[q + r * Q] = u[r];
         }
       }
-      if constexpr (S + 1 < RL::count) phase ^= 1;
+      if constexpr (!LAST) phase ^= 1;
       stage<INV, S + 1>(v, lds, phase, w, t, b);
     }
   }
 };
 
-// Tile of shape variant EV: 0 = the length's default shape, 1 = narrow,
-// 2 = wide.
+// Tile of shape variant EV: 0 = the length's default shape (the split shape
+// where the length has one), 1 = narrow, 2 = wide.
+template <int N, int B, bool COL, bool DB, bool SPLIT>
+struct TileDefault {
+  using type = Tile<N, B, COL, DB>;
+};
+template <int N, int B, bool COL, bool DB>
+struct TileDefault<N, B, COL, DB, true> {
+  using type = Tile<N, B, COL, DB, 8, typename FftSplit<N>::R, FftSplit<N>::T>;
+};
 template <int N, int B, bool COL, bool DB, int EV>
 struct TileSel {
-  using type = Tile<N, B, COL, DB>;
+  using type = typename TileDefault<N, B, COL, DB, FftSplit<N>::value>::type;
 };
 template <int N, int B, bool COL, bool DB>
 struct TileSel<N, B, COL, DB, 1> {

@@ -47,7 +47,12 @@ struct Fused1DArgs {
 // (The host passes the matching twiddle table: the narrow one where the
 // length has it.)
 template <int N>
-using F1Tile = TileV<N, 1, false, true, HasNarrow<N>::value ? 1 : 0>;
+struct F1Full {
+  using type = Tile<N, 1, false>;
+};
+template <int N>
+using F1Tile =
+    typename std::conditional<HasNarrow<N>::value, TileSel<N, 1, false, true, 1>, F1Full<N>>::type::type;
 
 template <int N, int OP>
 __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {

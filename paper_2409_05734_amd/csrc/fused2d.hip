@@ -91,7 +91,7 @@ __device__ __forceinline__ void f2_stage(float2 (&v)[F2T<N>::E], const typename 
       if constexpr (S > 0) {
 #pragma unroll
         for (int r = 1; r < R; ++r) {
-          const float2 tf = w[T::tw_offset(S) + q * (R - 1) + (r - 1)];
+          const float2 tf = T::twiddle(w, T::tw_offset(S) + q * (R - 1) + (r - 1));
           u[r] = INV ? cmulc(u[r], tf) : cmul(u[r], tf);
         }
       }
@@ -470,8 +470,8 @@ static F2Desc f2_desc(const sr_plan_s* p, size_t i, int op, const float* y, floa
   d.eph = p->use_table ? p->eph + g.th_off : nullptr;
   d.y = y + p->yoff[i];
   d.x = x + p->xoff[i];
-  d.tw0 = p->twiddles(g.M1, 0);
-  d.tw1 = p->twiddles(g.M2, 0);
+  d.tw0 = p->twiddles_resident(g.M1);
+  d.tw1 = p->twiddles_resident(g.M2);
   d.inv_m = 1.f / (float)g.m;  // (not cropped: m is the grid size)
   d.iters = iters;
   d.op = op;

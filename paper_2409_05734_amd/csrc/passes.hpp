@@ -170,7 +170,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   int t = T::thread_t();
   const int bl = T::thread_b();
   const int tb = tile * B + bl;  // transform index (over every problem of a stack)
-  const bool active = tb < a.ntr;
+  const bool active = tb < a.ntr && T::holds(t);
   int b = tb, sp = 0;            // this lane's transform within its problem, and the problem
   if (a.stack > 1) {
     sp = tb / a.ntr_p;

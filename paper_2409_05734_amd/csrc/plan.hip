@@ -17,9 +17,8 @@ size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
 // Thread-order twiddle table of one tile shape (see Tile::load_twiddles):
 // slot i of thread t at i * TPT + t, exp(-2 pi i e/N) evaluated in float64
 // and rounded once.
-template <int N, int EV>
+template <class T, int N>
 void fill_twiddles(std::vector<float2>& out) {
-  using T = sr::TileV<N, 1, false, true, EV>;
   out.assign((size_t)T::NTW * T::TPT, make_float2(1.f, 0.f));
   T::for_each_twiddle([&](int slot, int t, int e) {
     const double ang = -2.0 * M_PI * (double)e / (double)N;
@@ -30,18 +29,24 @@ void fill_twiddles(std::vector<float2>& out) {
 template <int N>
 bool twiddles_for(int shape, std::vector<float2>& out) {
   if (shape == 0) {
-    fill_twiddles<N, 0>(out);
+    fill_twiddles<sr::TileV<N, 1, false, true, 0>, N>(out);
     return true;
   }
   if constexpr (sr::HasNarrow<N>::value) {
     if (shape == 1) {
-      fill_twiddles<N, 1>(out);
+      fill_twiddles<sr::TileV<N, 1, false, true, 1>, N>(out);
       return true;
     }
   }
   if constexpr (sr::HasWide<N>::value) {
     if (shape == 2) {
-      fill_twiddles<N, 2>(out);
+      fill_twiddles<sr::TileV<N, 1, false, true, 2>, N>(out);
+      return true;
+    }
+  }
+  if constexpr (sr::FftSplit<N>::value) {
+    if (shape == 3) {
+      fill_twiddles<sr::Tile<N, 1, false>, N>(out);
       return true;
     }
   }
@@ -87,7 +92,7 @@ sr_status sr_plan_s::init(const float* theta_host) {
   std::vector<float2> host_tw;
   std::vector<std::pair<std::pair<int, int>, size_t>> tw_at;  // ((length, shape), offset)
   for (int N : lens)
-    for (int shape = 0; shape < 3; ++shape) {
+    for (int shape = 0; shape < 4; ++shape) {
       std::vector<float2> t;
       if (!thread_twiddles(N, shape, t)) continue;
       tw_at.push_back({{N, shape}, host_tw.size()});
