@@ -139,12 +139,20 @@ __device__ __forceinline__ float inv_norm_from_partials(const float* part, int n
   return (float)(1.0 / sqrt(block_sum_t<NTHREADS, double>(acc, redd)));
 }
 
+// A phase diagonal's entry evaluated on the fly: polynomials or the hardware
+// sine and cosine.
+template <bool POLY>
+__device__ __forceinline__ float2 phase_of(float theta) {
+  if constexpr (POLY) return phase_poly(theta);
+  else return phase_turns(theta);
+}
+
 // One tile (B transforms) of a fused pass.  `lds` holds 2*B*N complex
 // elements, `red` one float per thread.  part_in/npart/part_out override the
 // partial-sum pointers of `a` (persistent kernels alternate them per
 // iteration); partial sums are written at index `tile`.  TAB selects the
-// phase source: exp(i theta) tables (ep_*) or the phases themselves (th_*,
-// evaluated with sincos).
+// phase source: exp(i theta) tables (ep_*) or the phases themselves (th_*),
+// evaluated with the hardware's sine and cosine or (POLY) with polynomials.
 //
 // Every global load the tile needs (input, phases, measurements, twiddles,
 // the previous iterate) is issued up front, so a pass costs one memory
@@ -152,7 +160,7 @@ __device__ __forceinline__ float inv_norm_from_partials(const float* part, int n
 // stores go through buffer resources: lanes outside a window (the zero-padded
 // rows/columns, transforms past ntr) read zeros and drop their writes.
 template <int N, int B, bool COL, int PRE, int MID, bool FFT2, bool INV1, bool INV2, int POST, bool DB = true,
-          int EV = 0, bool TAB = false, bool WIN = false>
+          int EV = 0, bool TAB = false, bool WIN = false, bool POLY = false>
 __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* lds, float* red, const float* part_in,
                                           int npart, float* part_out) {
   using T = TileV<N, B, COL, DB, EV>;
@@ -271,17 +279,17 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   if constexpr (!TAB) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      if constexpr (PRE_PH) dp[j] = phase_turns(dp[j].x);
-      if constexpr (MID_PH && !LATE_PH) dm[j] = phase_turns(dm[j].x);
-      if constexpr (POST_PH && !LATE_PH) dq[j] = phase_turns(dq[j].x);
+      if constexpr (PRE_PH) dp[j] = phase_of<POLY>(dp[j].x);
+      if constexpr (MID_PH && !LATE_PH) dm[j] = phase_of<POLY>(dm[j].x);
+      if constexpr (POST_PH && !LATE_PH) dq[j] = phase_of<POLY>(dq[j].x);
     }
   }
   auto Dm = [&](int j) -> float2 {
-    if constexpr (LATE_PH) return phase_turns(dm[j].x);
+    if constexpr (LATE_PH) return phase_of<POLY>(dm[j].x);
     else return dm[j];
   };
   auto Dq = [&](int j) -> float2 {
-    if constexpr (LATE_PH) return phase_turns(dq[j].x);
+    if constexpr (LATE_PH) return phase_of<POLY>(dq[j].x);
     else return dq[j];
   };
 

@@ -106,14 +106,14 @@ static sr_status forward_rest(sr_plan_s* p, const Geo& g, float2** cur_out) {
   int which = 0;
   for (int k = 2; k <= g.L; ++k) {
     PassArgs a = base_args(p, g, k);
-    set_in(a, g, k, bufs[which]);
-    out_full(a, g, k, bufs[which ^ 1]);
+    if (k == 2) which ^= 1;  // compact in, full out; the later ones work in place
+    set_in(a, g, k, bufs[k == 2 ? which ^ 1 : which]);
+    out_full(a, g, k, bufs[which]);
     a.th_mid = p->theta_l(g, k);
     const float s = 1.f / std::sqrt((float)pass_len(g, k));
     a.scale_mid = s;
     a.scale_out = s;
     SR_CHECK(launch(p, g, k, PK_MID_FWD, a));
-    which ^= 1;
   }
   *cur_out = bufs[which];
   return SR_OK;
@@ -132,17 +132,17 @@ static sr_status forward_body(sr_plan_s* p, const Geo& g, const float2* x, float
 static sr_status adjoint_body(sr_plan_s* p, const Geo& g, float2* cur, int last_kind, float2* x, float step,
                               float two_lam, const float* part_in, int npart, float* part_out,
                               float2* out2 = nullptr) {
-  float2* other = (cur == p->bufA) ? p->bufB : p->bufA;
   for (int k = g.L; k >= 2; --k) {
     PassArgs a = base_args(p, g, k);
     in_full(a, g, k, cur);
+    float2* other = k == 2 ? (cur == p->bufA ? p->bufB : p->bufA) : cur;  // full in, compact out; else in place
     set_out(a, g, k, other);
     a.th_mid = p->theta_l(g, k);
     const float s = 1.f / std::sqrt((float)pass_len(g, k));
     a.scale_mid = s;
     a.scale_out = s;
     SR_CHECK(launch(p, g, k, PK_MID_ADJ, a));
-    std::swap(cur, other);
+    cur = other;
   }
   PassArgs a = base_args(p, g, 1);
   a.in = cur;
@@ -172,7 +172,7 @@ static sr_status adjoint_body(sr_plan_s* p, const Geo& g, float2* cur, int last_
 static sr_status turnaround(sr_plan_s* p, const Geo& g, float2* cur, int kind, const float* y, float lam,
                             const double* ysum, float* part_out, float2** out) {
   const int k = g.L + 1;
-  float2* other = (cur == p->bufA) ? p->bufB : p->bufA;
+  float2* other = cur;  // in place: input and output have one layout (compact for k = 2, else full)
   PassArgs a = base_args(p, g, k);
   set_in(a, g, k, cur);
   set_out(a, g, k, other);
