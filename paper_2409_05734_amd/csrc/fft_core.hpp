@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <type_traits>
+#include <utility>
 #include <stdint.h>
 
 namespace sr {
@@ -148,24 +149,25 @@ constexpr unsigned kOob = 0x80000000u;  // byte offset past every resource
 __device__ __forceinline__ Rsrc rsrc(const void* p) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), (short)0, 0x7fffffff, 0x00020000);
 }
-__device__ __forceinline__ unsigned off8(bool ok, int e) { return ok ? (unsigned)e * 8u : kOob; }
-__device__ __forceinline__ unsigned off4(bool ok, int e) { return ok ? (unsigned)e * 4u : kOob; }
-__device__ __forceinline__ float2 ld2(Rsrc r, unsigned off) {
-  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+// Each access takes a lane offset and a scalar offset (added by the memory
+// pipeline, outside the range check), so that a thread's elements at a fixed
+// stride share one lane offset and cost no address arithmetic apiece.
+__device__ __forceinline__ float2 ld2(Rsrc r, unsigned off, unsigned soff) {
+  const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, off, soff, 0);
   return make_float2(__builtin_bit_cast(float, (unsigned)v[0]), __builtin_bit_cast(float, (unsigned)v[1]));
 }
-__device__ __forceinline__ float ld1(Rsrc r, unsigned off) {
-  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0));
+__device__ __forceinline__ float ld1(Rsrc r, unsigned off, unsigned soff) {
+  return __builtin_bit_cast(float, (unsigned)__builtin_amdgcn_raw_buffer_load_b32(r, off, soff, 0));
 }
-__device__ __forceinline__ void st2(Rsrc r, unsigned off, float2 x) {
+__device__ __forceinline__ void st2(Rsrc r, unsigned off, unsigned soff, float2 x) {
   typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
   u32x2 v;
   v[0] = __builtin_bit_cast(unsigned, x.x);
   v[1] = __builtin_bit_cast(unsigned, x.y);
-  __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
+  __builtin_amdgcn_raw_buffer_store_b64(v, r, off, soff, 0);
 }
-__device__ __forceinline__ void st1(Rsrc r, unsigned off, float x) {
-  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off, 0, 0);
+__device__ __forceinline__ void st1(Rsrc r, unsigned off, unsigned soff, float x) {
+  __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, x), r, off, soff, 0);
 }
 
 // ------------------------------------------------------- non-finite values
@@ -443,6 +445,17 @@ struct Tile {
 
   __device__ __forceinline__ static int padk(int k) { return PADSHIFT ? k + (k >> PADSHIFT) : k; }
   __device__ __forceinline__ static int lidx(int b, int k) { return COL ? (padk(k) * B + b) : (b * LD + padk(k)); }
+  // lidx(b, k + C) from at = lidx(b, k), for a constant C.  Where C is a whole
+  // number of pad periods the sum is a constant too, which goes into the LDS
+  // instruction.
+  template <int C>
+  static constexpr bool shifts_whole() {
+    return PADSHIFT == 0 || C % (1 << PADSHIFT) == 0;
+  }
+  template <int C>
+  static constexpr int shift_of() {
+    return (PADSHIFT ? C + (C >> PADSHIFT) : C) * (COL ? B : 1);
+  }
   __device__ __forceinline__ static int thread_t() { return COL ? (int)(threadIdx.x / B) : (int)(threadIdx.x % TPT); }
   __device__ __forceinline__ static int thread_b() { return COL ? (int)(threadIdx.x % B) : (int)(threadIdx.x / TPT); }
   __device__ __forceinline__ static int elem(int t, int j) { return t + j * ACT; }
@@ -472,7 +485,8 @@ struct Tile {
   // that stage instead (its 29 would not fit in registers beside the data).
   static constexpr bool LAZY_TW = E_ >= 16;
   struct TableTw {
-    const float2* p;  // the table, offset to this thread
+    Rsrc r;  // the table
+    int t;   // this thread
   };
   using Twiddles = typename std::conditional<LAZY_TW, TableTw, float2[NTW]>::type;
 
@@ -480,17 +494,19 @@ struct Tile {
   // slot i of thread t (so each load instruction reads consecutive entries),
   // values exp(-2 pi i e/N) rounded from float64 (see for_each_twiddle).
   __device__ __forceinline__ static void load_twiddles(Twiddles& w, const float2* __restrict__ tw, int t) {
+    const Rsrc r = rsrc(tw);
     if constexpr (LAZY_TW) {
-      w.p = tw + t;
+      w.r = r;
+      w.t = t;
     } else {
 #pragma unroll
-      for (int i = 0; i < NTW; ++i) w[i] = tw[i * TPT + t];
+      for (int i = 0; i < NTW; ++i) w[i] = ld2(r, (unsigned)t * 8u, (unsigned)(i * TPT * 8));
     }
   }
 
   // This thread's twiddle slot i.
   __device__ __forceinline__ static float2 twiddle(const Twiddles& w, int i) {
-    if constexpr (LAZY_TW) return w.p[i * TPT];
+    if constexpr (LAZY_TW) return ld2(w.r, (unsigned)w.t * 8u, (unsigned)(i * TPT * 8));
     else return w[i];
   }
 
@@ -545,6 +561,31 @@ struct Tile {
     }
   }
 
+  // x[j] = element t + q A + r N/R, j = q + r Q; `at` points to element t
+  template <int R, int Q, int A, int... J>
+  __device__ __forceinline__ static void read_stage(float2* x, const float2* at, const float2* src, int t, int b,
+                                                    std::integer_sequence<int, J...>) {
+    ((x[J] = read_one<(J % Q) * A + (J / Q) * (N / R)>(at, src, t, b)), ...);
+  }
+  template <int C>
+  __device__ __forceinline__ static float2 read_one(const float2* at, const float2* src, int t, int b) {
+    if constexpr (shifts_whole<C>()) return at[shift_of<C>()];
+    else return src[lidx(b, t + C)];
+  }
+  // element base + r P <- u[r]; `at` points to element base (a multiple of R
+  // where P = 1, so that a pad period of R holds all R outputs)
+  template <int R, int P, int... J>
+  __device__ __forceinline__ static void write_stage(const float2* u, float2* at, float2* dst, int base, int b,
+                                                     std::integer_sequence<int, J...>) {
+    (write_one<R, P, J>(u[J], at, dst, base, b), ...);
+  }
+  template <int R, int P, int J>
+  __device__ __forceinline__ static void write_one(float2 u, float2* at, float2* dst, int base, int b) {
+    if constexpr (P == 1 && PADSHIFT && R == (1 << PADSHIFT)) at[J * (COL ? B : 1)] = u;
+    else if constexpr (shifts_whole<J * P>()) at[shift_of<J * P>()] = u;
+    else dst[lidx(b, base + J * P)] = u;
+  }
+
   template <bool INV, int S>
   __device__ __forceinline__ static void stage(float2 (&v)[E], float2* lds, int& phase, const Twiddles& w, int t,
                                                int b) {
@@ -572,10 +613,7 @@ struct Tile {
         xsync();
         const float2* src = DB ? lds + (phase ^ 1) * BUF : lds;
         if (mine) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q)
-#pragma unroll
-            for (int r = 0; r < R; ++r) x[q + r * Q] = src[lidx(b, t + q * A + r * (N / R))];
+          read_stage<R, Q, A>(x, src + lidx(b, t), src, t, b, std::make_integer_sequence<int, Q * R>{});
         } else {
 #pragma unroll
           for (int j = 0; j < Q * R; ++j) x[j] = make_float2(0.f, 0.f);
@@ -588,13 +626,12 @@ struct Tile {
       // loads, or an earlier transform's) before anyone overwrites it
       if constexpr (!DB && !LAST) xsync();
       float2* dst = DB ? lds + phase * BUF : lds;
+      const int base0 = (t / P) * P * R + t % P;
 #pragma unroll
       for (int q = 0; q < Q; ++q) {
         float2 u[R];
 #pragma unroll
         for (int r = 0; r < R; ++r) u[r] = x[q + r * Q];
-        const int i = t + q * A;
-        const int k = i % P;
         if constexpr (S > 0) {
 #pragma unroll
           for (int r = 1; r < R; ++r) {
@@ -605,9 +642,11 @@ struct Tile {
         Dft<R, INV>::run(u);
         if constexpr (!LAST) {
           if (mine) {
-            const int base = (i / P) * P * R + k;
-#pragma unroll
-            for (int r = 0; r < R; ++r) dst[lidx(b, base + r * P)] = u[r];
+            // butterfly q's outputs sit at base + r P; q A further butterflies
+            // move the base by q A R where A is a multiple of P
+            const int i = t + q * A;
+            const int base = A % P == 0 ? base0 + q * A * R : (i / P) * P * R + i % P;
+            write_stage<R, P>(u, dst + lidx(b, base), dst, base, b, std::make_integer_sequence<int, R>{});
           }
         } else {
 #pragma unroll

@@ -175,7 +175,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   constexpr bool POST_FWD = (POST == POST_GD_FWD || POST == POST_SPEC_FWD);
   constexpr bool POST_IS_GD = (POST == POST_GD || POST == POST_GD_FWD);
   constexpr bool POST_IS_SPEC = (POST == POST_SPEC || POST == POST_SPEC_FWD);
-  int t = T::thread_t();
+  const int t = T::thread_t();
   const int bl = T::thread_b();
   const int tb = tile * B + bl;  // transform index (over every problem of a stack)
   const bool active = tb < a.ntr && T::holds(t);
@@ -184,31 +184,45 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
     sp = tb / a.ntr_p;
     b = tb - sp * a.ntr_p;
   }
-  int gb = a.tr_lo + b;  // grid coordinate of this transform
+  const int gb = a.tr_lo + b;  // grid coordinate of this transform
   const int gld = (int)a.grid_ld, ild = (int)a.in_ld, old = (int)a.out_ld;
   // the lane's problem's offset in each buffer (zero without a stack)
   const int o_in = sp * a.s_in, o_out = sp * a.s_out, o_out2 = sp * a.s_out2, o_win = sp * a.s_win;
   const int o_th = sp * a.s_th, o_sv = sp * a.s_save, o_gt = sp * a.s_gth, o_xin = sp * a.s_xin;
 
-  // element offsets: grid position, input and output buffer positions
-  auto gidx = [&](int k) -> int { return COL ? k * gld + gb : gb * gld + k; };
-  auto in_addr = [&](int k) -> int { return o_in + (COL ? (k - a.in_lo) * ild + b : b * ild + (k - a.in_lo)); };
-  auto out_rel = [&](int k) -> int { return COL ? (k - a.out_lo) * old + b : b * old + (k - a.out_lo); };
-  auto out_addr = [&](int k) -> int { return o_out + out_rel(k); };
-  auto in_win = [&](int k) { return active && k >= a.in_lo && k < a.in_hi; };
-  auto out_win = [&](int k) { return active && k >= a.out_lo && k < a.out_hi; };
-  // measurement window: membership and index of grid element k of this
-  // transform (the transform's own coordinate is tested once; the index is
-  // affine in k).  Kernels built without WIN take the window to be the whole
-  // grid (no trimming), where membership is `active` and the index is gidx.
+  // ---- addressing.  Element j of this lane sits j steps after element 0 in
+  // every buffer (ACT rows or columns each), so an access takes the lane's
+  // offset of element 0 and the scalar offset of j steps.  What does not vary
+  // over the lanes (a window's start) goes into the buffer's base, which keeps
+  // lane offsets non-negative.  A window that covers the whole transform (all
+  // but the passes next to the support, and trimmed measurements) needs no
+  // test per element: the lane is in or out.
+  // (2048 x 2048 grid, 1024 x 1024 signal: vector instructions a thread of the
+  // two column passes 858 -> 700 and 811 -> 646, their longest shape 126 -> 97
+  // registers; a GD iteration, L = 2, 154 -> 146 us.)
+  constexpr int ACT = T::ACT;
+  const int g_lane = COL ? t * gld + gb : gb * gld + t, g_step = COL ? ACT * gld : ACT;      // grid
+  const int i_lane = COL ? t * ild + b : b * ild + t, i_step = COL ? ACT * ild : ACT;        // input buffer
+  const int u_lane = COL ? t * old + b : b * old + t, u_step = COL ? ACT * old : ACT;        // output buffer
+  const int i_cut = COL ? a.in_lo * ild : a.in_lo, u_cut = COL ? a.out_lo * old : a.out_lo;  // their windows' starts
+  const bool in_full = a.in_lo <= 0 && a.in_hi >= N, out_full = a.out_lo <= 0 && a.out_hi >= N;
+  const int in_len = active ? a.in_hi - a.in_lo : 0, out_len = active ? a.out_hi - a.out_lo : 0;
+  auto in_win = [&](int j) { return (unsigned)(t - a.in_lo + j * ACT) < (unsigned)in_len; };
+  auto out_win = [&](int j) { return (unsigned)(t - a.out_lo + j * ACT) < (unsigned)out_len; };
+  // lane offset of an element of B bytes, past the range where !ok
+  auto off = [](bool ok, int lane, unsigned bytes) -> unsigned { return ok ? (unsigned)lane * bytes : kOob; };
+  // measurement window: membership and index of element j of this transform
+  // (the transform's own coordinate is tested once).  Kernels built without
+  // WIN take the window to be the whole grid (no trimming).
   const int wld = (int)a.win_ld;
   const bool m_lane =
       WIN ? active && (COL ? (gb >= a.win_lo1 && gb < a.win_hi1) : (gb >= a.win_lo0 && gb < a.win_hi0)) : active;
   const int m_klo = COL ? a.win_lo0 : a.win_lo1;
-  const int m_khi = COL ? a.win_hi0 : a.win_hi1;
-  const int m_base = COL ? (gb - a.win_lo1) - a.win_lo0 * wld : (gb - a.win_lo0) * wld - a.win_lo1;
-  auto m_in = [&](int k) { return WIN ? m_lane && k >= m_klo && k < m_khi : active; };
-  auto m_idx = [&](int k) -> int { return o_win + (WIN ? (COL ? m_base + k * wld : m_base + k) : gidx(k)); };
+  const int m_len = m_lane ? (COL ? a.win_hi0 : a.win_hi1) - m_klo : 0;
+  const int m_off = o_win + (WIN ? (COL ? t * wld + gb : gb * wld + t) : g_lane);
+  const int m_step = WIN ? (COL ? ACT * wld : ACT) : g_step;
+  const int m_cut = WIN ? a.win_lo0 * wld + a.win_lo1 : 0;
+  auto m_in = [&](int j) { return WIN ? (unsigned)(t - m_klo + j * ACT) < (unsigned)m_len : active; };
   // the adjoint's first pass ([F_a^H] alone) reads its input on the window
   constexpr bool IN_WIN = WIN && (PRE == PRE_NONE && MID == MID_NONE && !FFT2 && INV1 && POST == POST_STORE);
 
@@ -223,52 +237,51 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   float gt[E];    // phase-cotangent accumulator
   typename T::Twiddles w;
   T::load_twiddles(w, EV ? a.tw_n : a.tw, t);
-  const Rsrc r_in = rsrc(a.in);
-  const Rsrc r_out = rsrc(a.out);
+  const Rsrc r_in = rsrc(a.in - (IN_WIN ? m_cut : i_cut));
+  const Rsrc r_out = rsrc(a.out - u_cut);
   const Rsrc r_pre = TAB ? rsrc(a.ep_pre) : rsrc(a.th_pre);
   const Rsrc r_mid = TAB ? rsrc(a.ep_mid) : rsrc(a.th_mid);
   const Rsrc r_post = TAB ? rsrc(a.ep_post) : rsrc(a.th_post);
-  const Rsrc r_y = rsrc(a.y);
+  const Rsrc r_y = rsrc(a.y - m_cut);
   const Rsrc r_save = rsrc(a.save);
   const Rsrc r_gth = rsrc(a.gth);
+  const Rsrc r_xin = rsrc(a.xin - u_cut);
+  constexpr unsigned PB = TAB ? 8 : 4;  // bytes of a phase entry
+  const unsigned p_all = off(active, g_lane + o_th, PB);
+  auto ld_phase = [&](Rsrc r, unsigned o, int j) -> float2 {
+    if constexpr (TAB) return ld2(r, o, (unsigned)(j * g_step) * 8u);
+    else return make_float2(ld1(r, o, (unsigned)(j * g_step) * 4u), 0.f);
+  };
+  if constexpr (IN_WIN) {
+    const int lane = m_off - o_win + o_in;
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = ld2(r_in, off(m_in(j), lane, 8), (unsigned)(j * m_step) * 8u);
+  } else if (in_full) {
+    const unsigned o = off(active, i_lane + o_in, 8);
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = ld2(r_in, o, (unsigned)(j * i_step) * 8u);
+  } else {
+#pragma unroll
+    for (int j = 0; j < E; ++j) v[j] = ld2(r_in, off(in_win(j), i_lane + o_in, 8), (unsigned)(j * i_step) * 8u);
+  }
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    const int k = T::elem(t, j);
-    const bool iw = in_win(k);
-    const int g = gidx(k) + o_th;  // phase index
-    if constexpr (IN_WIN) v[j] = ld2(r_in, off8(m_in(k), m_idx(k) - o_win + o_in));
-    else v[j] = ld2(r_in, off8(iw, in_addr(k)));
-    if constexpr (PRE_PH) {
-      if constexpr (TAB) dp[j] = ld2(r_pre, off8(iw, g));
-      else dp[j].x = ld1(r_pre, off4(iw, g));
-    }
-    if constexpr (MID_PH) {
-      if constexpr (TAB) dm[j] = ld2(r_mid, off8(active, g));
-      else dm[j].x = ld1(r_mid, off4(active, g));
-    }
-    if constexpr (MID_Y) yv[j] = ld1(r_y, off4(m_in(k), m_idx(k)));
-    if constexpr (MID_SAVED) {
-      sv[j] = ld2(r_save, off8(active, g - o_th + o_sv));
-      gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(active, g - o_th + o_gt));
-    }
-    if constexpr (MID == MID_STEP_BAR) {
-      sv[j] = ld2(r_save, off8(active, g - o_th + o_sv));
-      gt[j] = a.gy != nullptr ? ld1(rsrc(a.gy), off4(m_in(k), m_idx(k))) : 0.f;
-    }
-    if constexpr (MID != MID_STORE) {
-      const bool ow = out_win(k);
-      if constexpr (POST_PH) {
-        if constexpr (TAB) dq[j] = ld2(r_post, off8(ow, g));
-        else dq[j].x = ld1(r_post, off4(ow, g));
-      }
-      if constexpr (POST_X) xo[j] = ld2(r_out, off8(ow, out_addr(k)));
-      if constexpr (POST == POST_PHASE_CONJ_GT) {
-        xo[j] = ld2(rsrc(a.xin), off8(ow, o_xin + out_rel(k)));
-        gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(ow, g - o_th + o_gt));
-      }
-      if constexpr (POST == POST_GTV) {
-        xo[j] = ld2(rsrc(a.xin), off8(ow, o_xin + out_rel(k)));
-        gt[j] = a.gth_set ? 0.f : ld1(r_gth, off4(ow, g - o_th + o_gt));
+    if constexpr (PRE_PH) dp[j] = ld_phase(r_pre, in_win(j) ? p_all : kOob, j);
+    if constexpr (MID_PH) dm[j] = ld_phase(r_mid, p_all, j);
+    if constexpr (MID_Y) yv[j] = ld1(r_y, off(m_in(j), m_off, 4), (unsigned)(j * m_step) * 4u);
+    if constexpr (MID_SAVED || MID == MID_STEP_BAR)
+      sv[j] = ld2(r_save, off(active, g_lane + o_sv, 8), (unsigned)(j * g_step) * 8u);
+    if constexpr (MID_SAVED)
+      gt[j] = a.gth_set ? 0.f : ld1(r_gth, off(active, g_lane + o_gt, 4), (unsigned)(j * g_step) * 4u);
+    if constexpr (MID == MID_STEP_BAR)
+      gt[j] = a.gy != nullptr ? ld1(rsrc(a.gy - m_cut), off(m_in(j), m_off, 4), (unsigned)(j * m_step) * 4u) : 0.f;
+    if constexpr (MID != MID_STORE && POST_PH) {
+      const bool ow = out_win(j);
+      dq[j] = ld_phase(r_post, ow ? p_all : kOob, j);
+      if constexpr (POST_X) xo[j] = ld2(r_out, off(ow, u_lane + o_out, 8), (unsigned)(j * u_step) * 8u);
+      if constexpr (POST == POST_PHASE_CONJ_GT || POST == POST_GTV) {
+        xo[j] = ld2(r_xin, off(ow, u_lane + o_xin, 8), (unsigned)(j * u_step) * 8u);
+        gt[j] = a.gth_set ? 0.f : ld1(r_gth, off(ow, g_lane + o_gt, 4), (unsigned)(j * g_step) * 4u);
       }
     }
   }
@@ -284,6 +297,9 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
       if constexpr (POST_PH && !LATE_PH) dq[j] = phase_of<POLY>(dq[j].x);
     }
   }
+  // a weight of measurement j, zero outside the window (without WIN the lanes
+  // outside hold zeros anyway: their loads returned none)
+  auto in_weight = [&](int j, float wgt) -> float { return !WIN || m_in(j) ? wgt : 0.f; };
   auto Dm = [&](int j) -> float2 {
     if constexpr (LATE_PH) return phase_of<POLY>(dm[j].x);
     else return dm[j];
@@ -315,118 +331,119 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   // ---- pre-diagonal, first transform
 #pragma unroll
   for (int j = 0; j < E; ++j) {
-    if constexpr (PRE_PH) v[j] = cmul(v[j], cscale(dp[j], s_pre));
-    else v[j] = cscale(v[j], s_pre);
+    if constexpr (PRE_PH) v[j] = cmul(v[j], cscale(dp[j], s_pre));  // (only these passes have a scale_pre)
   }
   int ph = 0;
   T::template fft<INV1>(v, lds, ph, w, t, bl);
 
-  // ---- mid operation
+  // ---- mid operation.  A pass of two transforms along one axis scales by
+  // 1/sqrt(N) twice; where a factor is applied between them, both go into it as
+  // 1/N (FOLD), which the powers of two hold exactly: two multiplications an
+  // element less, and none of the bias that the rounded 1/sqrt(N) leaves.
+  constexpr bool FOLD = FFT2 && !mid_rev_phase(MID);
+  static_assert(!FOLD || POST == POST_STORE, "a folded scale has no post operation to precede");
+  constexpr float kInvN = 1.f / (float)N;
+  const float s_mid = a.scale_mid, s_out = a.scale_out;
   float acc = 0.f;
   if constexpr (MID == MID_PHASE || MID == MID_PHASE_CONJ) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const float2 d = cscale(Dm(j), a.scale_mid);
+      const float2 d = cscale(Dm(j), kInvN);
       v[j] = (MID == MID_PHASE_CONJ) ? cmulc(v[j], d) : cmul(v[j], d);
     }
   } else if constexpr (mid_rev_phase(MID)) {
+    const unsigned o8 = off(active, g_lane + o_sv, 8), o4 = off(active, g_lane + o_gt, 4);
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      const unsigned go8 = off8(active, gidx(k) + o_sv), go4 = off4(active, gidx(k) + o_gt);
-      const float2 u = cscale(v[j], a.scale_mid);
+      const unsigned j8 = (unsigned)(j * g_step) * 8u, j4 = (unsigned)(j * g_step) * 4u;
+      const float2 u = cscale(v[j], s_mid);
       if constexpr (MID == MID_PHASE_SAVE) {
         v[j] = cmul(u, Dm(j));
-        st2(r_save, go8, v[j]);
+        st2(r_save, o8, j8, v[j]);
       } else if constexpr (MID == MID_PHASE_CONJ_SAVE) {
         v[j] = cmulc(u, Dm(j));
-        st2(r_save, go8, v[j]);
+        st2(r_save, o8, j8, v[j]);
       } else if constexpr (MID == MID_PHASE_CONJ_GT) {
         // Im(u conj(s)) = u.y s.x - u.x s.y
-        st1(r_gth, go4, gt[j] + (u.y * sv[j].x - u.x * sv[j].y));
+        st1(r_gth, o4, j4, gt[j] + (u.y * sv[j].x - u.x * sv[j].y));
         v[j] = cmulc(u, Dm(j));
       } else {  // MID_PHASE_GT: Im(conj(u) s) = u.x s.y - u.y s.x
-        st1(r_gth, go4, gt[j] + (u.x * sv[j].y - u.y * sv[j].x));
+        st1(r_gth, o4, j4, gt[j] + (u.x * sv[j].y - u.y * sv[j].x));
         v[j] = cmul(u, Dm(j));
       }
     }
   } else if constexpr (MID == MID_STEP) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      const float2 z = cscale(v[j], a.scale_mid);
-      st2(r_save, off8(active, gidx(k) + o_sv), z);
-      v[j] = cscale(z, m_in(k) ? cabs2(z) - yv[j] : 0.f);
+      const float2 z = cscale(v[j], s_mid);
+      st2(r_save, off(active, g_lane + o_sv, 8), (unsigned)(j * g_step) * 8u, z);
+      v[j] = cscale(v[j], in_weight(j, cabs2(z) - yv[j]) * kInvN);
     }
   } else if constexpr (MID == MID_STEP_BAR) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      const bool in = m_in(k);
-      const float2 rb = cscale(v[j], a.scale_mid), z = sv[j];
+      const bool in = m_in(j);
+      const float2 rb = cscale(v[j], s_mid), z = sv[j];
       const float w = 2.f * cabs2(z) - yv[j];
       const float2 z2 = cmul(z, z);
-      if (a.gy != nullptr) st1(rsrc(a.gy), off4(in, m_idx(k)), gt[j] - (rb.x * z.x + rb.y * z.y));
-      v[j] = make_float2(in ? w * rb.x + z2.x * rb.x + z2.y * rb.y : 0.f,
-                         in ? w * rb.y + z2.y * rb.x - z2.x * rb.y : 0.f);
+      if (a.gy != nullptr)
+        st1(rsrc(a.gy - m_cut), off(in, m_off, 4), (unsigned)(j * m_step) * 4u, gt[j] - (rb.x * z.x + rb.y * z.y));
+      v[j] = make_float2(in ? (w * rb.x + z2.x * rb.x + z2.y * rb.y) * s_out : 0.f,
+                         in ? (w * rb.y + z2.y * rb.x - z2.x * rb.y) * s_out : 0.f);
     }
   } else if constexpr (MID == MID_INT_BAR) {
 #pragma unroll
-    for (int j = 0; j < E; ++j)
-      v[j] = cscale(cscale(v[j], a.scale_mid), m_in(T::elem(t, j)) ? 2.f * yv[j] : 0.f);
+    for (int j = 0; j < E; ++j) v[j] = cscale(v[j], in_weight(j, 2.f * yv[j]) * kInvN);
   } else if constexpr (MID == MID_GD) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const bool in = m_in(T::elem(t, j));
-      float2 z = cscale(v[j], a.scale_mid);
-      float d = in ? cabs2(z) - yv[j] : 0.f;  // zero residual outside the measurement window
+      const float d = in_weight(j, cabs2(cscale(v[j], s_mid)) - yv[j]);  // zero residual outside the measurement window
       acc += d * d;
-      v[j] = cscale(z, d);
+      v[j] = cscale(v[j], d * kInvN);
     }
   } else if constexpr (MID == MID_GD_POIS) {
     float z2[E];
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const bool in = m_in(T::elem(t, j));
-      float2 z = cscale(v[j], a.scale_mid);
-      z2[j] = cabs2(z);
-      v[j] = cscale(z, in ? poisson_weight(z2[j], yv[j], a.loss_eps) : 0.f);
+      z2[j] = cabs2(cscale(v[j], s_mid));
+      v[j] = cscale(v[j], in_weight(j, poisson_weight(z2[j], yv[j], a.loss_eps)) * kInvN);
     }
     if (part_out != nullptr) {  // the logarithms only for a loss trace
 #pragma unroll
-      for (int j = 0; j < E; ++j)
-        acc += m_in(T::elem(t, j)) ? poisson_term(z2[j], yv[j], a.loss_eps) : 0.f;
+      for (int j = 0; j < E; ++j) acc += m_in(j) ? poisson_term(z2[j], yv[j], a.loss_eps) : 0.f;
     }
   } else if constexpr (MID == MID_SPEC) {
     const float ybar = (float)(a.ysum[active ? sp : 0] * (double)a.inv_m);  // the problem's sum(y) (a stack: one each)
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      float2 z = cscale(v[j], a.scale_mid);
       float wgt = a.lam;
       if (yv[j] > 0.f) wgt = fmaxf(1.f - ybar / yv[j], a.lam);
-      v[j] = cscale(z, m_in(T::elem(t, j)) ? wgt : 0.f);
+      v[j] = cscale(v[j], in_weight(j, wgt) * kInvN);
     }
   } else if constexpr (MID == MID_STORE) {
-    const Rsrc r_z = rsrc(a.z_out), r_yo = rsrc(a.y_out);
+    const Rsrc r_z = rsrc(a.z_out - m_cut), r_yo = rsrc(a.y_out - m_cut);
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      float2 z = cscale(v[j], a.scale_mid);
-      if (a.z_out) st2(r_z, off8(m_in(k), m_idx(k)), z);
-      if (a.y_out) st1(r_yo, off4(m_in(k), m_idx(k)), cabs2(z));
+      float2 z = cscale(v[j], s_mid);
+      const bool in = m_in(j);
+      if (a.z_out) st2(r_z, off(in, m_off, 8), (unsigned)(j * m_step) * 8u, z);
+      if (a.y_out) st1(r_yo, off(in, m_off, 4), (unsigned)(j * m_step) * 4u, cabs2(z));
     }
   }
 
   // ---- second transform, post-diagonal, update, store
   if constexpr (FFT2) T::template fft<INV2>(v, lds, ph, w, t, bl);
-  if constexpr (E >= 16) {
-    // the sixteen-element shape recomputes its store addresses here rather
-    // than keeping the load phase's ones live (in scratch) across the
-    // transforms: the lane coordinates are marked as changed (no code)
-    asm volatile("" : "+v"(t), "+v"(b), "+v"(gb));
-  }
-
-  if constexpr (MID != MID_STORE) {
+  if constexpr (MID != MID_STORE && POST == POST_STORE) {
+    auto val = [&](int j) { return FOLD ? v[j] : cscale(v[j], s_out); };
+    if (out_full) {
+      const unsigned o = off(active, u_lane + o_out, 8);
+#pragma unroll
+      for (int j = 0; j < E; ++j) st2(r_out, o, (unsigned)(j * u_step) * 8u, val(j));
+    } else {
+#pragma unroll
+      for (int j = 0; j < E; ++j) st2(r_out, off(out_win(j), u_lane + o_out, 8), (unsigned)(j * u_step) * 8u, val(j));
+    }
+  } else if constexpr (MID != MID_STORE) {
     constexpr bool CHECK = (POST == POST_GD || POST == POST_SPEC);  // the last update of a solve
     bool bad = false;
     if constexpr (POST_IS_GD) {
@@ -434,23 +451,23 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
     }
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      const bool ow = out_win(k);
-      float2 val = cscale(v[j], a.scale_out);
-      float2 qj = make_float2(1.f, 0.f);
-      if constexpr (POST_PH) qj = Dq(j);
+      const bool ow = out_win(j);
+      const unsigned ju = (unsigned)(j * u_step) * 8u, j4 = (unsigned)(j * g_step) * 4u;
+      float2 val = cscale(v[j], s_out);
+      const float2 qj = Dq(j);
       if constexpr (POST == POST_PHASE_CONJ_GT) {
         const float2 u1 = cmul(xo[j], qj);  // u_1 = D_1 U x at this position
-        st1(r_gth, off4(ow, gidx(k) + o_gt), gt[j] + (val.y * u1.x - val.x * u1.y));
+        st1(r_gth, off(ow, g_lane + o_gt, 4), j4, gt[j] + (val.y * u1.x - val.x * u1.y));
       }
-      if constexpr (POST_PH) val = cmulc(val, qj);
+      val = cmulc(val, qj);
       if constexpr (POST == POST_GTV) {
         const float2 vb = cscale(xo[j], step);
-        st1(r_gth, off4(ow, gidx(k) + o_gt), gt[j] + (vb.x * val.y - vb.y * val.x));
+        st1(r_gth, off(ow, g_lane + o_gt, 4), j4, gt[j] + (vb.x * val.y - vb.y * val.x));
         continue;
       }
       if constexpr (POST == POST_PHASE_CONJ_GT) {
-        if (a.xadd != nullptr) val = cadd(ld2(rsrc(a.xadd), off8(ow, sp * a.s_xadd + out_rel(k))), val);
+        if (a.xadd != nullptr)
+          val = cadd(ld2(rsrc(a.xadd - u_cut), off(ow, sp * a.s_xadd + u_lane, 8), ju), val);
       }
       if constexpr (POST_IS_GD) {
         val = make_float2(xo[j].x - step * val.x, xo[j].y - step * val.y);
@@ -459,7 +476,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
                           s_prev * (a.step * val.y - a.two_lam * xo[j].y));
         acc += ow ? cabs2(val) : 0.f;
       }
-      st2(r_out, off8(ow, out_addr(k)), val);
+      st2(r_out, off(ow, u_lane + o_out, 8), ju, val);
       if constexpr (CHECK) bad |= ow && !finite2(val);
       if constexpr (POST_FWD) v[j] = ow ? cmul(val, qj) : make_float2(0.f, 0.f);  // zero outside the support
     }
@@ -467,15 +484,13 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   }
 
   if constexpr (POST_FWD) {
+    // the next iteration's [U, D_1, F_0] into the compact buffer (full columns)
     T::template fft<false>(v, lds, ph, w, t, bl);
-    const float s1 = a.scale_out;  // 1/sqrt(M1) for both transforms of this column pass
     const Rsrc r_o2 = rsrc(a.out2);
     const int o2ld = (int)a.out2_ld;
+    const unsigned o = off(active, o_out2 + t * o2ld + b, 8);
 #pragma unroll
-    for (int j = 0; j < E; ++j) {
-      const int k = T::elem(t, j);
-      st2(r_o2, off8(active, o_out2 + k * o2ld + b), cscale(v[j], s1));
-    }
+    for (int j = 0; j < E; ++j) st2(r_o2, o, (unsigned)(j * ACT * o2ld) * 8u, cscale(v[j], s_out));
   }
 
   if constexpr (MID == MID_GD || MID == MID_GD_POIS || POST_IS_SPEC) {
