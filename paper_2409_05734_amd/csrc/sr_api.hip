@@ -19,6 +19,7 @@
 #include "../../include/sr.h"
 #include "fused1d.hpp"
 #include "launch.hpp"
+#include "op_small.hpp"
 #include "persist.hpp"
 #include "plan.hpp"
 #include "schedule.hpp"
@@ -868,10 +869,39 @@ sr_status sr_plan_destroy(sr_plan p) {
   return SR_OK;
 }
 
+// A (A^H) of P problems of one geometry, their phases ths elements apart, in
+// one launch, for the grids op_small.hip takes.
+static sr_status operator_small(sr_plan_s* p, const Geo& g, int P, int ths, bool adjoint, const float2* in,
+                                float2* out, float* y) {
+  OpSmallArgs a{};
+  a.in = in;
+  a.z = out;
+  a.y = y;
+  a.eph = p->eph + g.th_off;
+  a.tw0 = p->twiddles(g.M1);
+  a.tw1 = p->twiddles(g.M2);
+  a.L = g.L;
+  a.N1 = g.N1;
+  a.N2 = g.N2;
+  a.o1 = g.o1;
+  a.o2 = g.o2;
+  a.W1 = g.W1;
+  a.W2 = g.W2;
+  a.c1 = g.c1;
+  a.c2 = g.c2;
+  a.s_one = (float)(1.0 / std::sqrt((double)g.mg));
+  a.s_x = (int)g.n;
+  a.s_m = (int)g.m;
+  a.s_th = ths;
+  hipError_t e = launch_op_small(g.M1, g.M2, adjoint, a, P, p->stream);
+  return e == hipSuccess ? SR_OK : hip_fail(e, "small operator");
+}
+
 // A x for a stack of problems (stack_size > 1): problem 0's schedule, each
 // pass launched once for all of them.
 static sr_status forward_stacked(sr_plan_s* p, int P, int ths, const float2* x, float2* z, float* y) {
   const Geo& g = p->geo[0];
+  if (op_small_supported(g)) return operator_small(p, g, P, ths, false, x, z, y);
   SR_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
   StackScope sc(p, P, ths);
   p->stk.add(x, g.n, sizeof(float2), (int)g.n);
@@ -882,6 +912,7 @@ static sr_status forward_stacked(sr_plan_s* p, int P, int ths, const float2* x, 
 
 static sr_status adjoint_stacked(sr_plan_s* p, int P, int ths, const float2* r, float2* x) {
   const Geo& g = p->geo[0];
+  if (op_small_supported(g)) return operator_small(p, g, P, ths, true, r, x, nullptr);
   SR_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
   StackScope sc(p, P, ths);
   p->stk.add(r, g.m, sizeof(float2), (int)g.m);
@@ -928,6 +959,8 @@ sr_status sr_forward(sr_plan p, const void* x, void* z, float* y) {
       a.z_out = zi;
       a.y_out = yi;
       b1.push_back({g.M1, args_1d(p, g, a)});
+    } else if (op_small_supported(g)) {
+      SR_CHECK(operator_small(p, g, 1, 0, false, xi, zi, yi));
     } else {
       SR_CHECK(forward_2d(p, g, xi, zi, yi));
     }
@@ -954,6 +987,8 @@ sr_status sr_adjoint(sr_plan p, const void* r, void* x_out) {
       a.r_in = rs + p->yoff[i];
       a.x_out = xs + p->xoff[i];
       b1.push_back({g.M1, args_1d(p, g, a)});
+    } else if (op_small_supported(g)) {
+      SR_CHECK(operator_small(p, g, 1, 0, true, rs + p->yoff[i], xs + p->xoff[i], nullptr));
     } else {
       SR_CHECK(adjoint_2d(p, g, rs + p->yoff[i], xs + p->xoff[i]));
     }
