@@ -14,6 +14,8 @@
 //                Br[i][2p] = Re r_pi, Br[i][2p+1] = Im r_pi,
 //                g_pk = (P[2k][2p] + P[2k+1][2p+1]) + i (P[2k][2p+1] - P[2k+1][2p]).
 //
+// Large products run in bf16 parts instead (dense_bf16.hip).
+//
 // The epilogues fuse the solver arithmetic: |z|^2, the GD residual
 // (|z|^2 - y) z with loss partials, the spectral weight T(y) z, and the GD or
 // spectral update of the iterate with norm partials.
@@ -26,6 +28,7 @@
 #include <cstring>
 #include <new>
 
+#include "dense_bf16.hpp"
 #include "dense_rows.hpp"
 #include "fft_core.hpp"
 #include "loss.hpp"
@@ -50,7 +53,12 @@ constexpr int BK = 64;    // reduction chunk
 constexpr int PADK = BK + 4;
 constexpr int NT = 256;   // 4 waves, 2 x 2 wave tiles of 32 x 32
 constexpr int kTargetGroups = 1024;
-constexpr int kMaxSplit = 8;  // the epilogue sums at most this many partial tiles
+constexpr int kMaxSplit = 16;    // the epilogues sum at most this many partial tiles
+constexpr int kMaxOwnSplit = 8;  // ... dense_mm_kernel leaves at most this many
+// Threads of an epilogue's workgroup: one load a split and thread, all in
+// flight (16384 rows, 32 signals, 8 splits: 25 us with 256 threads of eight
+// rows each, 8 us; the other product's 10 -> 5.6 us).
+constexpr int NTE = 1024;
 
 enum Epi : int {
   E1_STORE = 0,  // after A X: z and/or |z|^2
@@ -83,6 +91,8 @@ struct DenseArgs {
   int q_ld;                // 2 * (signals rounded up to 32): row length of the partials of A X
   int loss;                // E1_GD: LOSS_L2 or LOSS_POISSON
   float loss_eps;          // E1_GD: Poisson guard
+  bool bf16[2];            // the product runs on the bf16 matrix cores (dense_bf16.hip) ...
+  void* bf16_pack;         // ... with its small operand packed here
   unsigned* nf;            // E2_GD / E2_SPEC: set to 1 when an updated entry is NaN or Inf
 };
 
@@ -255,52 +265,79 @@ __global__ void __launch_bounds__(NT) dense_mm_kernel(const DenseArgs a) {
       }
 }
 
+// Sum over the half wave that this thread is in.
+__device__ __forceinline__ float half_wave_sum(float v) {
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o);
+  return v;
+}
+
+constexpr float kUnscale = 1.f / (kBf16Scale * kBf16Scale);
+
+// One entry of a product (G 1: (A x_p)_at, G 2: (A^H r_p)_at) in FP32, where
+// the bf16 products, which take both operands times kBf16Scale, gave no finite
+// one: an infinite operand, or a result above 2^96.
+__device__ __forceinline__ float2 product_entry(const DenseArgs& a, int G, int at, int p) {
+  const float sc = a.src_scale != nullptr ? a.src_scale[p] : 1.f;
+  const int len = G == 1 ? a.n : a.m;
+  const float2* A = reinterpret_cast<const float2*>(a.A);
+  double re = 0.0, im = 0.0;
+#pragma unroll 1
+  for (int k = 0; k < len; ++k) {
+    const float2 w = G == 1 ? A[(long long)at * a.n + k] : A[(long long)k * a.n + at];
+    const float2 v = cscale(a.src[(long long)p * len + k], sc);
+    const float2 t = G == 1 ? cmul(v, w) : cmulc(v, w);
+    re += (double)t.x;
+    im += (double)t.y;
+    if (re != re && im != im) break;  // (a diverged solve has nothing but NaNs)
+  }
+  return make_float2((float)re, (float)im);
+}
+
 // Epilogue after A X: z_pi = sum_s C_s[i][2p] + i C_s[i][2p+1] for 64 rows and
 // 32 signals, then the E1 arithmetic.  grid (row tiles, signal tiles).
 template <int EPI>
-__global__ void __launch_bounds__(NT) dense_epi1_kernel(const DenseArgs a) {
+__global__ void __launch_bounds__(NTE) dense_epi1_kernel(const DenseArgs a) {
   __shared__ float2 zs[BT][33];
-  __shared__ float red[NT];
   const int tid = threadIdx.x;
   const int i0 = blockIdx.x * BT;
   const int p0 = blockIdx.y * 32;
   {
-    // gather: thread (row il = tid/32 + 8u, signal pl = tid%32): coalesced over signals
-    const int pl = tid & 31;
+    // gather: thread (row il = tid/16, signals 2 (tid%16) + 0, 1): coalesced over signals
+    const int il = tid >> 4, pl = 2 * (tid & 15), gi = i0 + il;
+    float4 z = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (gi < a.m && p0 + pl < a.nb) {
 #pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int il = (tid >> 5) + 8 * u;
-      const int gi = i0 + il;
-      float2 z = make_float2(0.f, 0.f);
-      if (gi < a.m) {
-#pragma unroll
-        for (int s = 0; s < kMaxSplit; ++s) {
-          if (s < a.S) {
-            const float2 c =
-                *reinterpret_cast<const float2*>(&a.split[((long long)s * a.m + gi) * a.q_ld + 2 * (p0 + pl)]);
-            z.x += c.x;
-            z.y += c.y;
-          }
+      for (int s = 0; s < kMaxSplit; ++s) {
+        if (s < a.S) {
+          const float4 c =
+              *reinterpret_cast<const float4*>(&a.split[((long long)s * a.m + gi) * a.q_ld + 2 * (p0 + pl)]);
+          z.x += c.x;
+          z.y += c.y;
+          z.z += c.z;
+          z.w += c.w;
         }
       }
-      zs[il][pl] = z;
     }
+    zs[il][pl] = make_float2(z.x, z.y);
+    zs[il][pl + 1] = make_float2(z.z, z.w);
   }
   __syncthreads();
-  // apply: thread (signal pl = tid/8, rows 8*(tid&7) .. +8): coalesced over rows
-  const int pl = tid >> 3;
+  // apply: thread (signal pl = tid/32, rows 2*(tid&31) + 0, 1): coalesced over rows
+  const int pl = tid >> 5;
   const int p = p0 + pl;
-  const int ib = (tid & 7) * 8;
+  const int ib = (tid & 31) * 2;
   float part = 0.f;
   float ybar = 0.f;
   if constexpr (EPI == E1_SPEC) ybar = p < a.nb ? (float)(a.ysum[p] / (double)a.m) : 0.f;
   if (p < a.nb) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
+    for (int q = 0; q < 2; ++q) {
       const int il = ib + q;
       const int gi = i0 + il;
       if (gi >= a.m) break;
-      const float2 z = zs[il][pl];
+      float2 z = zs[il][pl];
+      if (a.bf16[0]) z = finite2(z) ? cscale(z, kUnscale) : product_entry(a, 1, gi, p);
       const long long o = (long long)p * a.m + gi;
       if constexpr (EPI == E1_STORE) {
         if (a.z_out) a.z_out[o] = z;
@@ -324,15 +361,9 @@ __global__ void __launch_bounds__(NT) dense_epi1_kernel(const DenseArgs a) {
     }
   }
   if constexpr (EPI == E1_GD) {
-    // per-signal partials: the 8 threads of signal pl are consecutive
-    red[tid] = part;
-    __syncthreads();
-    if ((tid & 7) == 0 && p < a.nb) {
-      float t = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) t += red[tid + q];
-      a.part[(long long)p * a.part_ld + blockIdx.x] = t;
-    }
+    // per-signal partials: half a wave has signal pl
+    const float t = half_wave_sum(part);
+    if ((tid & 31) == 0 && p < a.nb) a.part[(long long)p * a.part_ld + blockIdx.x] = t;
   }
 }
 
@@ -340,63 +371,50 @@ __global__ void __launch_bounds__(NT) dense_epi1_kernel(const DenseArgs a) {
 // P[2k+1][2p]), P = sum_s P_s, for 32 entries k and 32 signals, then the E2
 // arithmetic.  grid (k tiles of 32, signal tiles).
 template <int EPI>
-__global__ void __launch_bounds__(NT) dense_epi2_kernel(const DenseArgs a) {
-  __shared__ float red[NT];
+__global__ void __launch_bounds__(NTE) dense_epi2_kernel(const DenseArgs a) {
   const int tid = threadIdx.x;
-  const int pl = tid >> 3;
-  const int p = blockIdx.y * 32 + pl;
-  const int kb = blockIdx.x * 32 + (tid & 7) * 4;
+  const int p = blockIdx.y * 32 + (tid >> 5);
+  const int gk = blockIdx.x * 32 + (tid & 31);
   const int J = 2 * a.n;
   float part = 0.f;
   bool bad = false;
-  if (p < a.nb) {
+  if (p < a.nb && gk < a.n) {
+    float2 re = make_float2(0.f, 0.f), im = make_float2(0.f, 0.f);  // (P[2k][2p], P[2k+1][2p]), (.., 2p+1)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int gk = kb + q;
-      if (gk >= a.n) break;
-      float2 re = make_float2(0.f, 0.f), im = make_float2(0.f, 0.f);  // (P[2k][2p], P[2k+1][2p]), (.., 2p+1)
-#pragma unroll
-      for (int s = 0; s < kMaxSplit; ++s) {
-        if (s < a.S) {
-          const float2 u = *reinterpret_cast<const float2*>(&a.split[((long long)s * a.q_ld + 2 * p) * J + 2 * gk]);
-          const float2 v =
-              *reinterpret_cast<const float2*>(&a.split[((long long)s * a.q_ld + 2 * p + 1) * J + 2 * gk]);
-          re.x += u.x;
-          re.y += u.y;
-          im.x += v.x;
-          im.y += v.y;
-        }
+    for (int s = 0; s < kMaxSplit; ++s) {
+      if (s < a.S) {
+        const float2 u = *reinterpret_cast<const float2*>(&a.split[((long long)s * a.q_ld + 2 * p) * J + 2 * gk]);
+        const float2 v = *reinterpret_cast<const float2*>(&a.split[((long long)s * a.q_ld + 2 * p + 1) * J + 2 * gk]);
+        re.x += u.x;
+        re.y += u.y;
+        im.x += v.x;
+        im.y += v.y;
       }
-      const float2 gv = make_float2(re.x + im.y, im.x - re.y);
-      const long long o = (long long)p * a.n + gk;
-      if constexpr (EPI == E2_STORE) {
-        a.x[o] = cscale(gv, a.step);
-      } else if constexpr (EPI == E2_GD) {
-        const float2 xo = a.x[o];
-        const float2 nx = make_float2(xo.x - a.step * gv.x, xo.y - a.step * gv.y);
-        a.x[o] = nx;
-        bad |= !finite2(nx);
-      } else {
-        // u_new = step * M v - 2 lambda v, v = u / ||u|| (the 1/||u|| was applied to R's source in A X)
-        const float2 uo = a.x[o];
-        const float c = 2.f * a.lam * a.prev_scale[p];
-        const float2 nu = make_float2(a.step * gv.x - c * uo.x, a.step * gv.y - c * uo.y);
-        a.x[o] = nu;
-        part += cabs2(nu);
-        bad |= !finite2(nu);
-      }
+    }
+    float2 gv = make_float2(re.x + im.y, im.x - re.y);
+    if (a.bf16[1]) gv = finite2(gv) ? cscale(gv, kUnscale) : product_entry(a, 2, gk, p);
+    const long long o = (long long)p * a.n + gk;
+    if constexpr (EPI == E2_STORE) {
+      a.x[o] = cscale(gv, a.step);
+    } else if constexpr (EPI == E2_GD) {
+      const float2 xo = a.x[o];
+      const float2 nx = make_float2(xo.x - a.step * gv.x, xo.y - a.step * gv.y);
+      a.x[o] = nx;
+      bad |= !finite2(nx);
+    } else {
+      // u_new = step * M v - 2 lambda v, v = u / ||u|| (the 1/||u|| was applied to R's source in A X)
+      const float2 uo = a.x[o];
+      const float c = 2.f * a.lam * a.prev_scale[p];
+      const float2 nu = make_float2(a.step * gv.x - c * uo.x, a.step * gv.y - c * uo.y);
+      a.x[o] = nu;
+      part += cabs2(nu);
+      bad |= !finite2(nu);
     }
   }
   if constexpr (EPI == E2_GD || EPI == E2_SPEC) flag_nonfinite(a.nf, bad);
   if constexpr (EPI == E2_SPEC) {
-    red[tid] = part;
-    __syncthreads();
-    if ((tid & 7) == 0 && p < a.nb) {
-      float t = 0.f;
-#pragma unroll
-      for (int q = 0; q < 8; ++q) t += red[tid + q];
-      a.part[(long long)p * a.part_ld + blockIdx.x] = t;
-    }
+    const float t = half_wave_sum(part);
+    if ((tid & 31) == 0 && p < a.nb) a.part[(long long)p * a.part_ld + blockIdx.x] = t;
   }
 }
 
@@ -540,7 +558,7 @@ constexpr size_t kLibWorkspace = size_t(64) << 20;
 // split a whole number of BK chunks.
 void plan_split(int tiles, int K, int* S, int* kchunk) {
   const int chunks = (K + BK - 1) / BK;
-  int want = std::max(1, std::min(std::min(chunks, kMaxSplit), (kTargetGroups + tiles - 1) / tiles));
+  int want = std::max(1, std::min(std::min(chunks, kMaxOwnSplit), (kTargetGroups + tiles - 1) / tiles));
   const int per = (chunks + want - 1) / want;
   *kchunk = per * BK;
   *S = (chunks + per - 1) / per;
@@ -548,8 +566,8 @@ void plan_split(int tiles, int K, int* S, int* kchunk) {
 
 int signal_tiles(const DenseArgs& a) { return (a.nb + 31) / 32; }
 
-// The product of kind G: on the library (lib != nullptr and chosen for G)
-// or on dense_mm_kernel; then the epilogue EPI.
+// The product of kind G: in bf16 parts or on the library where the plan chose
+// them for G, else on dense_mm_kernel; then the epilogue EPI.
 template <int G, int EPI>
 hipError_t gemm(DenseArgs a, float* split, hipStream_t st, const DenseLib* lib = nullptr) {
   const int M = G == 1 ? a.m : 2 * a.n;
@@ -558,7 +576,12 @@ hipError_t gemm(DenseArgs a, float* split, hipStream_t st, const DenseLib* lib =
   a.split = split;
   a.q_ld = 64 * signal_tiles(a);
   hipError_t e = hipSuccess;
-  if (lib != nullptr && lib->use[G - 1]) {
+  if (a.bf16[G - 1]) {
+    int steps;
+    a.S = bf16_splits(G, a.m, a.n, a.nb, &steps);
+    const Bf16Gemm b{a.A, a.m, a.n, a.nb, a.src, a.src_scale, a.bf16_pack, split, a.q_ld};
+    if ((e = launch_bf16_gemm(G, b, st)) != hipSuccess) return e;
+  } else if (lib != nullptr && lib->use[G - 1]) {
     a.S = 1;
     const long long pairs = G == 1 ? (long long)a.n * a.q_ld / 2 : (long long)a.m * (a.q_ld / 2);
     const int groups = (int)std::min<long long>((pairs + 255) / 256, 8192);
@@ -582,9 +605,9 @@ hipError_t gemm(DenseArgs a, float* split, hipStream_t st, const DenseLib* lib =
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if constexpr (G == 1) {
-    hipLaunchKernelGGL((dense_epi1_kernel<EPI>), dim3(tiles, signal_tiles(a)), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((dense_epi1_kernel<EPI>), dim3(tiles, signal_tiles(a)), dim3(NTE), 0, st, a);
   } else {
-    hipLaunchKernelGGL((dense_epi2_kernel<EPI>), dim3((a.n + 31) / 32, signal_tiles(a)), dim3(NT), 0, st, a);
+    hipLaunchKernelGGL((dense_epi2_kernel<EPI>), dim3((a.n + 31) / 32, signal_tiles(a)), dim3(NTE), 0, st, a);
   }
   return hipGetLastError();
 }
@@ -596,6 +619,8 @@ DenseArgs base(const sr_plan_s* p) {
   a.n = (int)p->geo[0].n;
   a.nb = (int)p->geo.size();
   a.nf = p->sync + 2;
+  a.bf16_pack = p->dpack;
+  for (int g = 0; g < 2; ++g) a.bf16[g] = (p->dense_bf16 >> g) & 1;
   return a;
 }
 
@@ -625,7 +650,10 @@ size_t dense_split_floats(int m, int n, int nb) {
   const size_t f2 = (size_t)S2 * 2 * n * 64 * st;
   RowsShape rs;
   const size_t f3 = rows_shape(m, n, nb, &rs) ? 2 * (size_t)rs.G * nb * n : 0;  // the row kernels' partials of A^H r
-  return std::max(std::max(f1, f2), f3);
+  int steps;
+  const size_t f4 = (size_t)bf16_splits(1, m, n, nb, &steps) * m * 64 * st;
+  const size_t f5 = (size_t)bf16_splits(2, m, n, nb, &steps) * 2 * n * 64 * st;
+  return std::max({f1, f2, f3, f4, f5});
 }
 
 // Whether a plan's products run on the row kernels: their shape, with room
@@ -648,6 +676,12 @@ sr_status dense_lib_setup(sr_plan_s* p) {
   }
   if (force != nullptr && std::strcmp(force, "own") == 0) return SR_OK;
   DenseArgs a = base(p);
+  // the bf16 products load A sixteen bytes at a time
+  const bool bf16_ok = (uintptr_t)a.A % 16 == 0;  // (n is even)
+  if (force != nullptr && std::strcmp(force, "bf16") == 0) {
+    p->dense_bf16 = bf16_ok ? 3 : 0;
+    return SR_OK;
+  }
   const uint64_t q = 64 * (uint64_t)signal_tiles(a), m = (uint64_t)a.m, n2 = 2 * (uint64_t)a.n;
   DenseLib* d = new (std::nothrow) DenseLib();
   if (d == nullptr) return SR_OK;
@@ -695,10 +729,14 @@ sr_status dense_lib_setup(sr_plan_s* p) {
   if (need > 0 && hipMalloc(&d->ws, need) != hipSuccess) return give_up();
   d->ws_bytes = need;
   if (hipMalloc(&d->pack, sizeof(float) * std::max(q * n2, m * q)) != hipSuccess) return give_up();
-  // per product: the fastest of dense_mm_kernel and the library's candidates
-  // (best of three applications each after a warm-up, on the plan's own
+  // per product: the fastest of dense_mm_kernel, the bf16 products and the
+  // library's candidates (bf16 for the large ones, where A's stream bounds it:
+  // A X and A^H R of 16384 x 4096 on 32 signals 212 and 230 us in
+  // dense_mm_kernel, 158 and 171 us on the library, 141 and 127 us in bf16
+  // parts; dense_mm_kernel for the small ones, which are launches and
+  // latency: 1000 x 258 on 32 signals 12, 20 and 16 us; best of three applications each after a warm-up, on the plan's own
   // matrix; the source is scratch of the right size, the epilogue writes
-  // nothing but scratch); SR_DENSE_GEMM=lib leaves dense_mm_kernel out
+  // nothing but scratch); SR_DENSE_GEMM=lib leaves the hand-written ones out
   const bool all_lib = force != nullptr && std::strcmp(force, "lib") == 0;
   const bool can_time = (size_t)a.n <= (size_t)a.m;  // bufB (m x nb) holds the A^H R output
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -708,6 +746,9 @@ sr_status dense_lib_setup(sr_plan_s* p) {
     for (int g = 0; g < 2; ++g) d->use[g] = d->ok[g];  // the heuristic's first choice, untimed
     e0 = e1 = nullptr;
   } else {
+    // (any finite source)
+    if (hipMemsetD32Async((hipDeviceptr_t)p->bufA, 0x3f800000, 2 * (size_t)a.m * a.nb, p->stream) != hipSuccess)
+      return give_up();
     for (int g = 0; g < 2; ++g) {
       if (!d->ok[g]) continue;
       auto time_it = [&]() -> float {
@@ -729,11 +770,19 @@ sr_status dense_lib_setup(sr_plan_s* p) {
         return best;
       };
       float best = 1e30f;
-      int pick = -1;  // -1: dense_mm_kernel
+      int pick = -1;  // -1: dense_mm_kernel, or the bf16 products
       if (!all_lib) {
         d->use[g] = false;
         best = time_it();
+        if (bf16_ok) {
+          a.bf16[g] = true;
+          const float t = time_it();
+          a.bf16[g] = t < best;
+          best = std::min(best, t);
+        }
       }
+      const bool bf16 = a.bf16[g];
+      a.bf16[g] = false;
       d->use[g] = true;
       for (int c = 0; c < ncand[g]; ++c) {
         d->algo[g] = cand[g][c];
@@ -745,6 +794,7 @@ sr_status dense_lib_setup(sr_plan_s* p) {
       }
       if (all_lib && pick < 0) pick = 0;
       d->use[g] = pick >= 0;
+      if (pick < 0 && bf16) p->dense_bf16 |= 1u << g;
       if (pick >= 0) d->algo[g] = cand[g][pick];
     }
   }

@@ -119,7 +119,9 @@ sr_status sr_plan_s::init(const float* theta_host) {
   size_t b_dsplit = 0;
   if (kind == SR_DENSE)
     b_dsplit = align256(sizeof(float) * sr::dense_split_floats((int)geo[0].m, (int)geo[0].n, (int)np));
-  ws_bytes = b_theta + b_eph + b_tw + ngrid * b_grid + b_part + b_ysum + b_fs + b_sync + b_red + b_trace + b_dsplit;
+  const size_t b_dpack =
+      kind == SR_DENSE ? align256(sr::bf16_pack_bytes((int)geo[0].m, (int)geo[0].n, (int)np)) : 0;
+  ws_bytes = b_theta + b_eph + b_tw + ngrid * b_grid + b_part + b_ysum + b_fs + b_sync + b_red + b_trace + b_dsplit + b_dpack;
   hipError_t e = hipMalloc(&ws, ws_bytes);
   if (e != hipSuccess) {
     ws = nullptr;
@@ -155,6 +157,8 @@ sr_status sr_plan_s::init(const float* theta_host) {
   if (b_trace) trace_part = (float*)c;
   c += b_trace;
   if (b_dsplit) dsplit = (float*)c;
+  c += b_dsplit;
+  if (b_dpack) dpack = c;
 
   for (const auto& ta : tw_at) tw[ta.first] = twbuf + ta.second;
   if (tw_elems) {

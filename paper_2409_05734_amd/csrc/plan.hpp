@@ -98,6 +98,8 @@ struct sr_plan_s {
   const float2* dense_A = nullptr;  // caller-owned dense matrix (SR_DENSE)
   sr::DenseLib* dense_lib = nullptr;  // library GEMM state of a dense plan (null: hand-written products only)
 
+  unsigned dense_bf16 = 0;  // dense products on the bf16 matrix cores (dense_bf16.hip): bit 0 A X, bit 1 A^H R
+  void* dpack = nullptr;    // ... and their packed small operand
   bool dense_rows = false;  // dense products on the row kernels (few short signals; dense_rows.hip)
 
   std::map<std::pair<int, int>, float2*> tw;  // (FFT length, thread shape) -> device twiddle table
@@ -199,12 +201,13 @@ sr_status put_floats(sr_plan_s* p, float* dst, const float* host, int count);
 
 // dense.hip (i.i.d. complex Gaussian baseline)
 size_t dense_split_floats(int m, int n, int nb);
+size_t bf16_pack_bytes(int m, int n, int nb);
 sr_status dense_forward(sr_plan_s* p, const float2* x, float2* z, float* y);
 sr_status dense_adjoint(sr_plan_s* p, const float2* r, float2* x);
 sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const float* eta, float* loss_trace);
 sr_status dense_spectral(sr_plan_s* p, const float* y, const float2* v0, int iters, float lam, float2* x0);
-// hipBLASLt for the dense products where it is faster (timed per product at
-// plan creation; SR_DENSE_GEMM=own / lib pins the choice)
+// bf16 parts or hipBLASLt for the dense products where they are faster (timed
+// per product at plan creation; SR_DENSE_GEMM=own / bf16 / lib pins the choice)
 sr_status dense_lib_setup(sr_plan_s* p);
 
 // fused2d.hip (LDS-resident solves of small 2D problems, one workgroup each)

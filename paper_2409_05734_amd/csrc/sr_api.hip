@@ -799,6 +799,7 @@ sr_status sr_plan_set_workspace(sr_plan p, void* dev_ptr, size_t bytes) {
   mv(p->red_ws);
   mv(p->trace_part);
   mv(p->dsplit);
+  mv(p->dpack);
   for (auto& t : p->tw) mv(t.second);
   // recorded schedules and captured graphs hold the old addresses
   for (auto& g : p->graphs) (void)hipGraphExecDestroy(g.second);
