@@ -7,7 +7,7 @@
 // unitary DFT on a grid of max(n, m) points, U the centred zero padding
 // (m > n) and S the centred trimming to the m measurements (m < n).
 #pragma once
-#include "fft_core.hpp"
+#include "lane_fft.hpp"
 #include "loss.hpp"
 
 namespace sr {
@@ -21,7 +21,7 @@ struct Fused1DArgs {
   int n, m, L, off;          // signal length, grid length, layers, pad offset
   int mw, moff;              // measurement window [moff, moff + mw) of the grid
   const float* theta;        // L*m phases
-  const float2* tw;          // exp(-2 pi i e/m), e = 0..m-1
+  const float2* tw;          // twiddles of F1Tile<m>
   const float2* x_in;        // forward: x; spectral: v0
   float2* x_out;             // adjoint / spectral: output; GD: iterate (in place)
   const float2* r_in;        // adjoint input
@@ -38,21 +38,26 @@ struct Fused1DArgs {
   unsigned* nf;              // GD / spectral: set to 1 when the result holds NaN or Inf (nullable)
 };
 
-// The transform shape of the 1D kernels: the narrow shape (four elements per
-// thread, twice the threads) where the length has one.  A single 1D problem
-// is one workgroup whose whole solve is a chain of dependent transforms, so
-// its time is the chain's latency: halving each lane's arithmetic shortens
-// it more than the extra exchange stage lengthens it (the default shape of
-// the shorter lengths does not even fill one wave).
-// (The host passes the matching twiddle table: the narrow one where the
-// length has it.)
+// The transform shape of the 1D kernels.  A single 1D problem is one workgroup
+// whose whole solve is a chain of dependent transforms, so its time is the
+// chain's latency: an element a lane where the length has that shape
+// (lane_fft.hpp; the 60 GD and 20 power iterations, L = 2, of one problem took
+// 132, 178, 168 and 259 us at 64, 128, 256 and 512 points with four elements a
+// lane, 445, 502 and 465 us at 192, 384 and 768 with twelve, and take 70, 92,
+// 114, 163, 102, 138 and 204 us; 2048 problems of 256 points 511 -> 385 us), else
+// the narrow shape (four elements) where it has one, else the default.
+template <int N> struct F1Full { using type = Tile<N, 1, false>; };
+template <int N> struct F1Lane { using type = LaneTile<N>; };
 template <int N>
-struct F1Full {
-  using type = Tile<N, 1, false>;
-};
-template <int N>
-using F1Tile =
-    typename std::conditional<HasNarrow<N>::value, TileSel<N, 1, false, true, 1>, F1Full<N>>::type::type;
+using F1Tile = typename std::conditional<
+    HasLane<N>::value, F1Lane<N>,
+    typename std::conditional<HasNarrow<N>::value, TileSel<N, 1, false, true, 1>, F1Full<N>>::type>::type::type;
+// its table (sr_plan_s::twiddles)
+template <class P>
+inline const float2* twiddles_1d(const P* p, int N) {
+  if (const float2* lane = p->twiddles(N, 4)) return lane;
+  return p->twiddles(N, 1) ? p->twiddles(N, 1) : p->twiddles_resident(N);
+}
 
 template <int N, int OP>
 __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {
@@ -63,7 +68,7 @@ __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {
   __shared__ float2 dl[kFused1DPhaseSlots];  // e^{i theta_l}, L*m <= slots
   __shared__ float red[NT];
   const int t = threadIdx.x;
-  const float s = rsqrtf((float)N);
+  const float s = HasLane<N>::value ? 1.f : rsqrtf((float)N);  // (the lane transforms are scaled)
   const int L = a.L;
 
   for (int e = t; e < L * N; e += NT) {
@@ -82,9 +87,16 @@ __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {
 
   // forward layers from v = U x (already in registers); leaves z = A x in v
   auto forward_layers = [&]() {
+    float2 d[E];
+#pragma unroll
+    for (int j = 0; j < E; ++j) d[j] = dl[T::elem(t, j)];
     for (int l = 0; l < L; ++l) {
 #pragma unroll
-      for (int j = 0; j < E; ++j) v[j] = cmul(v[j], dl[l * N + T::elem(t, j)]);
+      for (int j = 0; j < E; ++j) v[j] = cmul(v[j], d[j]);
+      if (l + 1 < L) {
+#pragma unroll
+        for (int j = 0; j < E; ++j) d[j] = dl[(l + 1) * N + T::elem(t, j)];
+      }
       T::template fft<false>(v, lds, ph, w, t, 0);
 #pragma unroll
       for (int j = 0; j < E; ++j) v[j] = cscale(v[j], s);
@@ -93,9 +105,12 @@ __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {
   // adjoint layers from v = r; leaves D_1^* F^H ... in v (crop left to caller)
   auto adjoint_layers = [&]() {
     for (int l = L - 1; l >= 0; --l) {
+      float2 d[E];
+#pragma unroll
+      for (int j = 0; j < E; ++j) d[j] = dl[l * N + T::elem(t, j)];
       T::template fft<true>(v, lds, ph, w, t, 0);
 #pragma unroll
-      for (int j = 0; j < E; ++j) v[j] = cscale(cmulc(v[j], dl[l * N + T::elem(t, j)]), s);
+      for (int j = 0; j < E; ++j) v[j] = cscale(cmulc(v[j], d[j]), s);
     }
   };
 

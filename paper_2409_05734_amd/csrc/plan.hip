@@ -6,6 +6,7 @@
 #include <set>
 #include <vector>
 
+#include "lane_fft.hpp"
 #include "launch.hpp"
 #include "plan.hpp"
 
@@ -50,6 +51,12 @@ bool twiddles_for(int shape, std::vector<float2>& out) {
       return true;
     }
   }
+  if constexpr (sr::HasLane<N>::value) {
+    if (shape == 4) {
+      fill_twiddles<sr::LaneTile<N>, N>(out);
+      return true;
+    }
+  }
   return false;
 }
 
@@ -78,7 +85,7 @@ sr_status sr_plan_s::init(const float* theta_host) {
   }
 
   // twiddle tables of every FFT length (and thread shape) the plan uses
-  std::set<int> lens;
+  std::set<int> lens, lens_1d;
   int64_t max_m = 0;
   int cap = 1;
   int64_t max_grid = 0;
@@ -88,11 +95,13 @@ sr_status sr_plan_s::init(const float* theta_host) {
     if (kind != SR_STRUCTURED) continue;
     lens.insert(g.M1);
     if (g.ndim == 2) lens.insert(g.M2);
+    else lens_1d.insert(g.M1);
   }
   std::vector<float2> host_tw;
   std::vector<std::pair<std::pair<int, int>, size_t>> tw_at;  // ((length, shape), offset)
   for (int N : lens)
-    for (int shape = 0; shape < 4; ++shape) {
+    for (int shape = 0; shape < 5; ++shape) {
+      if (shape == 4 && !lens_1d.count(N)) continue;
       std::vector<float2> t;
       if (!thread_twiddles(N, shape, t)) continue;
       tw_at.push_back({{N, shape}, host_tw.size()});

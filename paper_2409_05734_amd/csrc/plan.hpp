@@ -173,7 +173,8 @@ struct sr_plan_s {
 
   sr_status init(const float* theta_host);
   // table of the passes' thread shape (0 default, 1 narrow, 2 wide), or of the
-  // LDS-resident kernels' (which have no split shapes; 3 where that differs)
+  // LDS-resident kernels' (which have no split shapes; 3 where that differs), or
+  // an element a lane (4; lengths of 1D problems)
   const float2* twiddles(int N, int shape = 0) const;
   const float2* twiddles_resident(int N) const { return twiddles(N, 3) ? twiddles(N, 3) : twiddles(N, 0); }
   const float* theta_l(const sr::Geo& g, int l) const;

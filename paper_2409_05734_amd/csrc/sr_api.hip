@@ -523,7 +523,7 @@ static Fused1DArgs args_1d(const sr_plan_s* p, const Geo& g, Fused1DArgs a) {
   a.mw = g.W1;
   a.moff = g.c1;
   a.theta = p->theta_l(g, 1);
-  a.tw = p->twiddles(g.M1, 1) ? p->twiddles(g.M1, 1) : p->twiddles_resident(g.M1);  // the 1D kernels' shape
+  a.tw = twiddles_1d(p, g.M1);
   a.loss = p->loss;
   a.loss_eps = p->loss_eps;
   a.nf = p->sync + 2;
