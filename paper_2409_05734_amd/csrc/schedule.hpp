@@ -168,13 +168,15 @@ inline sr_status ensure_stack_parts(sr_plan_s* p, size_t elems) {
 struct StackScope {
   sr_plan_s* p;
   float2 *a0, *b0;
-  StackScope(sr_plan_s* pl, int P, int th_stride) : p(pl), a0(pl->bufA), b0(pl->bufB) {
+  // (P problems from number `first` of the `all` that the buffers hold)
+  StackScope(sr_plan_s* pl, int P, int th_stride, int first = 0, int all = 0) : p(pl), a0(pl->bufA), b0(pl->bufB) {
     const Geo& g = p->geo[0];
+    if (all == 0) all = P;
     p->stk.P = P;
     p->stk.th_stride = th_stride;
     p->stk.regions.clear();
-    p->bufA = p->stk_buf;
-    p->bufB = p->stk_buf + (size_t)P * g.mg;
+    p->bufA = p->stk_buf + (size_t)first * g.mg;
+    p->bufB = p->bufA + (size_t)all * g.mg;
     p->stk.add(p->bufA, g.mg, sizeof(float2), (int)g.mg);
     p->stk.add(p->bufB, g.mg, sizeof(float2), (int)g.mg);
   }

@@ -584,19 +584,15 @@ static bool stream_capturing(const sr_plan_s* p) {
 // `row` of a chunk writes its loss partials to row `row` of a buffer of
 // kTraceRows rows (= the chunk), summed by one launch per chunk
 // (flush(first iteration, rows)); a traced solve under the caller's own stream
-// capture launches every pass directly.
-template <class Step, class Flush>
-static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, bool trace, Step&& step,
-                               Flush&& flush) {
+// capture launches every pass directly.  chunk(rows, last) runs that many
+// iterations, the last of them the solve's last if `last`; `direct` leaves the graphs out.
+template <class Chunk, class Flush>
+static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, bool trace, Chunk&& chunk,
+                               Flush&& flush, bool direct = false) {
   static_assert(kTraceRows == kGraphChunk, "a chunk's iterations have a row each");
   int it = 0;
-  auto steady = [&](int rows) {
-    return [&, rows]() -> sr_status {
-      for (int c = 0; c < rows; ++c) SR_CHECK(step(c, false));
-      return SR_OK;
-    };
-  };
-  if (graphs_enabled(p) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
+  auto steady = [&](int rows) { return [&, rows]() -> sr_status { return chunk(rows, false); }; };
+  if (!direct && graphs_enabled(p) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
     for (; it + kGraphChunk <= iters - 1; it += kGraphChunk) {
       SR_CHECK(launch_captured(p, key, steady(kGraphChunk)));
       if (trace) SR_CHECK(flush(it, kGraphChunk));
@@ -610,7 +606,7 @@ static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, 
   }
   while (it < iters) {
     const int rows = std::min(iters - it, kTraceRows);
-    for (int c = 0; c < rows; ++c) SR_CHECK(step(c, it + c == iters - 1));
+    SR_CHECK(chunk(rows, it + rows == iters));
     if (trace) SR_CHECK(flush(it, rows));
     it += rows;
   }
@@ -1006,6 +1002,26 @@ static bool stack_trace_ok(const sr_plan_s* p, const Geo& g) {
   return ntr % bt == 0;
 }
 
+// Parts of a stack whose GD iterations run beside each other, on streams of
+// their own.  A pass of a large stack spends its first and last microseconds
+// with the memory system idle, and its workgroups load and transform in step;
+// two halves fill each other's gaps.  60 iterations, one part -> two: 16 of 512
+// x 512, L = 2 (4.2M points) 3678 -> 3230 us, 64 (16.8M) 15050 -> 14160; 4.2M
+// points of 256 x 256 3550 -> 3140, of 1024 x 1024 4600 -> 4070, of 384 x 384
+// 3980 -> 3230, of 2048 x 512 6970 -> 6920, of 768 x 512 (3.9M) 4140 -> 3980;
+// below, halves are too short: 8 of 512 x 512 (2.1M) 2337 -> 2370, 16 of 256 x
+// 256 (1.0M) 1332 -> 1830.  Short solves (one iteration a call in unrolled
+// training) lose to the fork and the join: 64 of 256 x 256, 10 steps and their
+// reverse 5039 -> 5981 us.  SR_STACK_PARTS=1 / 2 sets it.
+constexpr int64_t kPartPoints = 3900000;
+constexpr int kPartIters = 16;
+static int stack_parts(const Geo& g, int P, int iters) {
+  if (P < 4) return 1;  // a part is a stack (reads its steps from the array): two problems at least
+  const char* env = std::getenv("SR_STACK_PARTS");
+  if (env != nullptr) return std::atoi(env) == 2 ? 2 : 1;
+  return iters >= kPartIters && (int64_t)P * g.mg >= kPartPoints ? 2 : 1;
+}
+
 // GD on a stack: problem 0's schedule, each pass launched once for all
 // problems, each with its own step; with a loss trace, each problem's loss
 // partials (whole problems per turnaround tile) reduced in one launch.
@@ -1029,21 +1045,51 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   std::vector<float> steps(P);
   for (int i = 0; i < P; ++i) steps[i] = eta_host[i] / (float)p->geo[i].m;
   SR_CHECK(put_floats(p, p->stk_steps, steps.data(), P));
-  StackScope sc(p, P, ths);
-  p->stk.steps = p->stk_steps;
-  p->stk.add(x, g.n, sizeof(float2), (int)g.n);
-  p->stk.add(y, g.m, sizeof(float), (int)g.m);
+  const int parts = stack_parts(g, P, iters);
+  // f(geometry, signals, measurements, number of the first problem) on part h
+  auto on_part = [&](int h, auto&& f) -> sr_status {
+    const int lo = (int)((int64_t)P * h / parts), cnt = (int)((int64_t)P * (h + 1) / parts) - lo;
+    StackScope sc(p, cnt, ths, lo, P);
+    Geo q = g;
+    q.th_off += (int64_t)lo * ths;
+    float2* xp = x + (int64_t)lo * g.n;
+    const float* yp = y + (int64_t)lo * g.m;
+    p->stk.steps = p->stk_steps + lo;
+    p->stk.add(xp, g.n, sizeof(float2), (int)g.n);
+    p->stk.add(yp, g.m, sizeof(float), (int)g.m);
+    return f(q, xp, yp, lo);
+  };
+  for (int h = 0; h < parts; ++h)
+    SR_CHECK(on_part(h, [&](const Geo& q, float2* xp, const float*, int) {
+      return first_pass(p, q, xp, 1.f, nullptr, 0);
+    }));
   const float step = steps[0];  // (unused by the stacked update, which reads the array)
-  SR_CHECK(first_pass(p, g, x, 1.f, nullptr, 0));
   const std::string key = "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
                           ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_steps) +
                           (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) + loss_key(p);
   return gd_iterations(
       p, key, iters, loss_trace != nullptr,
-      [&](int row, bool last) -> sr_status {
-        return gd_steady(p, g, y, x, step, loss_trace ? p->stk_part + (size_t)row * P * nparts : nullptr, last);
+      [&](int rows, bool last) -> sr_status {
+        const hipStream_t main = p->stream;
+        if (parts > 1) SR_CHECK(aux_fork(p));
+        sr_status st = SR_OK;
+        for (int c = 0; c < rows && st == SR_OK; ++c)
+          for (int h = 0; h < parts && st == SR_OK; ++h) {
+            if (h == 1) p->stream = p->aux_stream;
+            st = on_part(h, [&](const Geo& q, float2* xp, const float* yp, int lo) {
+              float* part = loss_trace ? p->stk_part + ((size_t)c * P + lo) * nparts : nullptr;
+              return gd_steady(p, q, yp, xp, step, part, last && c == rows - 1);
+            });
+            p->stream = main;
+          }
+        if (parts > 1) {
+          const sr_status joined = aux_join(p);
+          if (st == SR_OK) st = joined;
+        }
+        return st;
       },
-      [&](int it, int rows) { return reduce_partials(p, p->stk_part, nparts, loss_trace + it, rows, P, iters); });
+      [&](int it, int rows) { return reduce_partials(p, p->stk_part, nparts, loss_trace + it, rows, P, iters); },
+      parts > 1);
 }
 
 sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, const float* eta_host,
@@ -1095,8 +1141,11 @@ sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, c
                             float_key(step) + (lt ? ":tr" : "") + loss_key(p);
     SR_CHECK(gd_iterations(
         p, key, iters, lt != nullptr,
-        [&](int row, bool last) -> sr_status {
-          return gd_steady(p, g, yi, xi, step, lt ? p->trace_part + (size_t)row * nparts : nullptr, last);
+        [&](int rows, bool last) -> sr_status {
+          for (int c = 0; c < rows; ++c)
+            SR_CHECK(gd_steady(p, g, yi, xi, step, lt ? p->trace_part + (size_t)c * nparts : nullptr,
+                               last && c == rows - 1));
+          return SR_OK;
         },
         [&](int it, int rows) { return reduce_partials(p, p->trace_part, nparts, lt + it, rows, 1, iters); }));
   }
