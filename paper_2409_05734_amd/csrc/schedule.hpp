@@ -250,8 +250,16 @@ constexpr int kGraphChunk = 50;  // iterations per captured graph (even)
 constexpr int kGraphTail = 8;    // a remainder of at least this many steady iterations gets a graph too
 constexpr size_t kGraphCacheSize = 8;
 
-inline bool graphs_enabled(const sr_plan_s* p) {
-  if (p->schedule == SR_SCHED_LOOP) return false;
+// From this many grid points on a pass outlasts its launch: the iterations run
+// as fast launched directly (60 GD iterations, graph -> direct: 2048 x 1024
+// 3373 -> 3370 us, 8 of 512 x 512 2345 -> 2325, 2048 x 2048 7485 -> 7480; at
+// half the points 4 of 512 x 512 1710 -> 1793), and the first call on new
+// buffers is spared the capture (3810 -> 3415, 2725 -> 2364, 8140 -> 7495 us).
+constexpr int64_t kDirectPoints = 2000000;
+
+// points: grid points a pass works on.
+inline bool graphs_enabled(const sr_plan_s* p, int64_t points = 0) {
+  if (p->schedule == SR_SCHED_LOOP || points >= kDirectPoints) return false;
   const char* e = std::getenv("SR_GRAPH");
   return e == nullptr || std::atoi(e) != 0;
 }

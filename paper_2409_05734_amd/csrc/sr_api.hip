@@ -585,14 +585,14 @@ static bool stream_capturing(const sr_plan_s* p) {
 // kTraceRows rows (= the chunk), summed by one launch per chunk
 // (flush(first iteration, rows)); a traced solve under the caller's own stream
 // capture launches every pass directly.  chunk(rows, last) runs that many
-// iterations, the last of them the solve's last if `last`; `direct` leaves the graphs out.
+// iterations, the last of them the solve's last if `last`, on `points` grid points a pass.
 template <class Chunk, class Flush>
 static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, bool trace, Chunk&& chunk,
-                               Flush&& flush, bool direct = false) {
+                               Flush&& flush, int64_t points) {
   static_assert(kTraceRows == kGraphChunk, "a chunk's iterations have a row each");
   int it = 0;
   auto steady = [&](int rows) { return [&, rows]() -> sr_status { return chunk(rows, false); }; };
-  if (!direct && graphs_enabled(p) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
+  if (graphs_enabled(p, points) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
     for (; it + kGraphChunk <= iters - 1; it += kGraphChunk) {
       SR_CHECK(launch_captured(p, key, steady(kGraphChunk)));
       if (trace) SR_CHECK(flush(it, kGraphChunk));
@@ -1066,7 +1066,8 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   const float step = steps[0];  // (unused by the stacked update, which reads the array)
   const std::string key = "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
                           ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_steps) +
-                          (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) + loss_key(p);
+                          (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) +
+                          (parts > 1 ? ":parts" : "") + loss_key(p);
   return gd_iterations(
       p, key, iters, loss_trace != nullptr,
       [&](int rows, bool last) -> sr_status {
@@ -1089,7 +1090,7 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
         return st;
       },
       [&](int it, int rows) { return reduce_partials(p, p->stk_part, nparts, loss_trace + it, rows, P, iters); },
-      parts > 1);
+      P * g.mg);
 }
 
 sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, const float* eta_host,
@@ -1147,7 +1148,7 @@ sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, c
                                last && c == rows - 1));
           return SR_OK;
         },
-        [&](int it, int rows) { return reduce_partials(p, p->trace_part, nparts, lt + it, rows, 1, iters); }));
+        [&](int it, int rows) { return reduce_partials(p, p->trace_part, nparts, lt + it, rows, 1, iters); }, g.mg));
   }
   return flush_1d(p, F1_GD, b1);
 }
@@ -1230,7 +1231,7 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
       npart = nq;
       it = 1;
     }
-    if (graphs_enabled(p) && iters - 1 - it >= kGraphChunk) {
+    if (graphs_enabled(p, P * g.mg) && iters - 1 - it >= kGraphChunk) {
       const std::string key = "specstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
                               ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_part) + ":" + float_key(lambda);
       for (; it + kGraphChunk <= iters - 1; it += kGraphChunk)
@@ -1338,7 +1339,7 @@ sr_status sr_spectral_init(sr_plan p, const float* y, const void* v0, int32_t it
         npart = nq;
         it = 1;
       }
-      if (graphs_enabled(p) && iters - 1 - it >= kGraphChunk) {
+      if (graphs_enabled(p, g.mg) && iters - 1 - it >= kGraphChunk) {
         // chunks start at odd iterations, so every chunk has the same partial-buffer parity
         const std::string key = "spec:" + std::to_string(i) + ":" + ptr_key(yi) + ":" + ptr_key(xi) + ":" +
                                 float_key(lambda);
