@@ -199,7 +199,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   // test per element: the lane is in or out.
   // (2048 x 2048 grid, 1024 x 1024 signal: vector instructions a thread of the
   // two column passes 858 -> 700 and 811 -> 646, their longest shape 126 -> 97
-  // registers; a GD iteration, L = 2, 154 -> 146 us.)
+  // registers; a GD iteration, L = 3, 129 -> 122 us.)
   constexpr int ACT = T::ACT;
   const int g_lane = COL ? t * gld + gb : gb * gld + t, g_step = COL ? ACT * gld : ACT;      // grid
   const int i_lane = COL ? t * ild + b : b * ild + t, i_step = COL ? ACT * ild : ACT;        // input buffer

@@ -580,7 +580,8 @@ static bool stream_capturing(const sr_plan_s* p) {
 // The steady iterations of a GD solve after its first pass: chunks replayed
 // from captured graphs (and the steady iterations short of a chunk as one
 // graph of their own: direct launches cost about 1.4 us more per iteration on
-// the 512^2 image), the rest launched directly.  With a trace, iteration
+// the 512^2 image), the rest launched directly, and all of them on large
+// grids (kDirectPoints).  With a trace, iteration
 // `row` of a chunk writes its loss partials to row `row` of a buffer of
 // kTraceRows rows (= the chunk), summed by one launch per chunk
 // (flush(first iteration, rows)); a traced solve under the caller's own stream
@@ -611,6 +612,65 @@ static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, 
     it += rows;
   }
   return SR_OK;
+}
+
+// Parts of a stack whose iterations run beside each other, on streams of their
+// own.  A pass of a large stack spends its first and last microseconds
+// with the memory system idle, and its workgroups load and transform in step;
+// two halves fill each other's gaps.  60 iterations, one part -> two: 16 of 512
+// x 512, L = 2 (4.2M points) 3678 -> 3230 us, 64 (16.8M) 15050 -> 14160; 4.2M
+// points of 256 x 256 3550 -> 3140, of 1024 x 1024 4600 -> 4070, of 384 x 384
+// 3980 -> 3230, of 2048 x 512 6970 -> 6920, of 768 x 512 (3.9M) 4140 -> 3980;
+// below, halves are too short: 8 of 512 x 512 (2.1M) 2337 -> 2370, 16 of 256 x
+// 256 (1.0M) 1332 -> 1830.  Short solves (one iteration a call in unrolled
+// training) lose to the fork and the join: 64 of 256 x 256, 10 steps and their
+// reverse 5039 -> 5981 us.  SR_STACK_PARTS=1 / 2 sets it.
+constexpr int64_t kPartPoints = 3900000;
+constexpr int kPartIters = 16;
+static int stack_parts(const Geo& g, int P, int iters) {
+  if (P < 4) return 1;  // a part is a stack (reads its steps from the array): two problems at least
+  const char* env = std::getenv("SR_STACK_PARTS");
+  if (env != nullptr) return std::atoi(env) == 2 ? 2 : 1;
+  return iters >= kPartIters && (int64_t)P * g.mg >= kPartPoints ? 2 : 1;
+}
+
+static int stack_parts(const sr_plan_s* p, const Geo& g, int P, int iters) {
+  if (p->aux_stream == nullptr && stream_capturing(p)) return 1;  // (no stream is made inside a capture)
+  return stack_parts(g, P, iters);
+}
+
+// f(geometry, signals, measurements, number of its first problem) on part h of
+// a stack.
+template <class F>
+static sr_status on_stack_part(sr_plan_s* p, int P, int ths, int parts, int h, float2* x, const float* y, F&& f) {
+  const int lo = (int)((int64_t)P * h / parts), cnt = (int)((int64_t)P * (h + 1) / parts) - lo;
+  StackScope sc(p, cnt, ths, lo, P);
+  Geo q = p->geo[0];
+  q.th_off += (int64_t)lo * ths;
+  float2* xp = x + (int64_t)lo * q.n;
+  const float* yp = y + (int64_t)lo * q.m;
+  p->stk.add(xp, q.n, sizeof(float2), (int)q.n);
+  p->stk.add(yp, q.m, sizeof(float), (int)q.m);
+  return f(q, xp, yp, lo);
+}
+
+// step(c, h), c < rows, on the parts h beside each other.
+template <class Step>
+static sr_status beside(sr_plan_s* p, int parts, int rows, Step&& step) {
+  const hipStream_t main = p->stream;
+  if (parts > 1) SR_CHECK(aux_fork(p));
+  sr_status st = SR_OK;
+  for (int c = 0; c < rows && st == SR_OK; ++c)
+    for (int h = 0; h < parts && st == SR_OK; ++h) {
+      if (h == 1) p->stream = p->aux_stream;
+      st = step(c, h);
+      p->stream = main;
+    }
+  if (parts > 1) {
+    const sr_status joined = aux_join(p);
+    if (st == SR_OK) st = joined;
+  }
+  return st;
 }
 
 // ====================================================================== ABI
@@ -1002,26 +1062,6 @@ static bool stack_trace_ok(const sr_plan_s* p, const Geo& g) {
   return ntr % bt == 0;
 }
 
-// Parts of a stack whose GD iterations run beside each other, on streams of
-// their own.  A pass of a large stack spends its first and last microseconds
-// with the memory system idle, and its workgroups load and transform in step;
-// two halves fill each other's gaps.  60 iterations, one part -> two: 16 of 512
-// x 512, L = 2 (4.2M points) 3678 -> 3230 us, 64 (16.8M) 15050 -> 14160; 4.2M
-// points of 256 x 256 3550 -> 3140, of 1024 x 1024 4600 -> 4070, of 384 x 384
-// 3980 -> 3230, of 2048 x 512 6970 -> 6920, of 768 x 512 (3.9M) 4140 -> 3980;
-// below, halves are too short: 8 of 512 x 512 (2.1M) 2337 -> 2370, 16 of 256 x
-// 256 (1.0M) 1332 -> 1830.  Short solves (one iteration a call in unrolled
-// training) lose to the fork and the join: 64 of 256 x 256, 10 steps and their
-// reverse 5039 -> 5981 us.  SR_STACK_PARTS=1 / 2 sets it.
-constexpr int64_t kPartPoints = 3900000;
-constexpr int kPartIters = 16;
-static int stack_parts(const Geo& g, int P, int iters) {
-  if (P < 4) return 1;  // a part is a stack (reads its steps from the array): two problems at least
-  const char* env = std::getenv("SR_STACK_PARTS");
-  if (env != nullptr) return std::atoi(env) == 2 ? 2 : 1;
-  return iters >= kPartIters && (int64_t)P * g.mg >= kPartPoints ? 2 : 1;
-}
-
 // GD on a stack: problem 0's schedule, each pass launched once for all
 // problems, each with its own step; with a loss trace, each problem's loss
 // partials (whole problems per turnaround tile) reduced in one launch.
@@ -1045,19 +1085,12 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   std::vector<float> steps(P);
   for (int i = 0; i < P; ++i) steps[i] = eta_host[i] / (float)p->geo[i].m;
   SR_CHECK(put_floats(p, p->stk_steps, steps.data(), P));
-  const int parts = stack_parts(g, P, iters);
-  // f(geometry, signals, measurements, number of the first problem) on part h
+  const int parts = stack_parts(p, g, P, iters);
   auto on_part = [&](int h, auto&& f) -> sr_status {
-    const int lo = (int)((int64_t)P * h / parts), cnt = (int)((int64_t)P * (h + 1) / parts) - lo;
-    StackScope sc(p, cnt, ths, lo, P);
-    Geo q = g;
-    q.th_off += (int64_t)lo * ths;
-    float2* xp = x + (int64_t)lo * g.n;
-    const float* yp = y + (int64_t)lo * g.m;
-    p->stk.steps = p->stk_steps + lo;
-    p->stk.add(xp, g.n, sizeof(float2), (int)g.n);
-    p->stk.add(yp, g.m, sizeof(float), (int)g.m);
-    return f(q, xp, yp, lo);
+    return on_stack_part(p, P, ths, parts, h, x, y, [&](const Geo& q, float2* xp, const float* yp, int lo) {
+      p->stk.steps = p->stk_steps + lo;
+      return f(q, xp, yp, lo);
+    });
   };
   for (int h = 0; h < parts; ++h)
     SR_CHECK(on_part(h, [&](const Geo& q, float2* xp, const float*, int) {
@@ -1071,23 +1104,12 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
   return gd_iterations(
       p, key, iters, loss_trace != nullptr,
       [&](int rows, bool last) -> sr_status {
-        const hipStream_t main = p->stream;
-        if (parts > 1) SR_CHECK(aux_fork(p));
-        sr_status st = SR_OK;
-        for (int c = 0; c < rows && st == SR_OK; ++c)
-          for (int h = 0; h < parts && st == SR_OK; ++h) {
-            if (h == 1) p->stream = p->aux_stream;
-            st = on_part(h, [&](const Geo& q, float2* xp, const float* yp, int lo) {
-              float* part = loss_trace ? p->stk_part + ((size_t)c * P + lo) * nparts : nullptr;
-              return gd_steady(p, q, yp, xp, step, part, last && c == rows - 1);
-            });
-            p->stream = main;
-          }
-        if (parts > 1) {
-          const sr_status joined = aux_join(p);
-          if (st == SR_OK) st = joined;
-        }
-        return st;
+        return beside(p, parts, rows, [&](int c, int h) {
+          return on_part(h, [&](const Geo& q, float2* xp, const float* yp, int lo) {
+            float* part = loss_trace ? p->stk_part + ((size_t)c * P + lo) * nparts : nullptr;
+            return gd_steady(p, q, yp, xp, step, part, last && c == rows - 1);
+          });
+        });
       },
       [&](int it, int rows) { return reduce_partials(p, p->stk_part, nparts, loss_trace + it, rows, P, iters); },
       P * g.mg);
@@ -1220,7 +1242,20 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
   SR_CHECK(sum_floats(p, y, g.m, p->ysum, P));
   SR_CHECK(norm2_partial(p, x, g.n, parts[0], P));
   int npart = 1;
-  {
+  if (const int halves = stack_parts(p, g, P, iters); halves > 1 && iters > 0) {
+    for (int h = 0; h < halves; ++h)
+      SR_CHECK(on_stack_part(p, P, ths, halves, h, x, y, [&](const Geo& q, float2* xp, const float*, int) {
+        return first_pass(p, q, xp, 1.f, nullptr, 0);
+      }));
+    SR_CHECK(beside(p, halves, iters, [&](int it, int h) {
+      return on_stack_part(p, P, ths, halves, h, x, y, [&](const Geo& q, float2* xp, const float* yp, int lo) {
+        const int ni = it == 0 ? 1 : nq;  // the start vector has one partial a problem
+        return spec_steady(p, q, yp, xp, lambda, inv_mc, p->ysum + lo, parts[it & 1] + (size_t)lo * ni, ni,
+                           parts[(it + 1) & 1] + (size_t)lo * nq, it == iters - 1);
+      });
+    }));
+    npart = nq;
+  } else {
     StackScope sc(p, P, ths);
     p->stk.add(x, g.n, sizeof(float2), (int)g.n);
     p->stk.add(y, g.m, sizeof(float), (int)g.m);

@@ -53,6 +53,23 @@ def test_same_as_one_part(gpu, P, shared, iters, loss, trace, monkeypatch):
         assert tr is None or torch.equal(tr, outs[0][1])
 
 
+@pytest.mark.parametrize("P,shared", [(2, False), (5, False), (16, True)])
+@pytest.mark.parametrize("iters", (0, 1, 2, 64))
+def test_power_iteration(gpu, P, shared, iters, monkeypatch):
+    import torch
+    import paper_2409_05734_amd as srpr
+    monkeypatch.setenv("SR_TUNE_FORCE", "4,1,0")  # tiles that hold whole problems
+    plan, x0, y = _setup(gpu, P, shared)
+    outs = []
+    for parts in ("1", "2"):
+        monkeypatch.setenv("SR_STACK_PARTS", parts)
+        x = torch.empty_like(x0)
+        srpr.sr_spectral_init(plan, y, x0, iters, -1.0, x)
+        outs.append(torch.view_as_real(x))
+    srpr.sr_plan_sync(plan)
+    assert torch.equal(*outs)
+
+
 def test_captured(gpu, monkeypatch):
     import torch
     import paper_2409_05734_amd as srpr
