@@ -757,15 +757,22 @@ sr_status dense_lib_setup(sr_plan_s* p) {
         t.x = p->bufB;
         t.step = 1.f;
         float best = 1e30f;
+        int runs = 1;
         for (int rep = 0; rep < 4; ++rep) {
           (void)hipEventRecord(e0, p->stream);
-          const hipError_t e = g == 0 ? gemm<1, E1_STORE>(t, p->dsplit, p->stream, d)
-                                      : gemm<2, E2_STORE>(t, p->dsplit, p->stream, d);
+          hipError_t e = hipSuccess;
+          for (int i = 0; i < runs && e == hipSuccess; ++i)
+            e = g == 0 ? gemm<1, E1_STORE>(t, p->dsplit, p->stream, d) : gemm<2, E2_STORE>(t, p->dsplit, p->stream, d);
           (void)hipEventRecord(e1, p->stream);
           if (e != hipSuccess || hipEventSynchronize(e1) != hipSuccess) return 1e30f;
           float ms = 0.f;
           (void)hipEventElapsedTime(&ms, e0, e1);
-          if (rep > 0) best = std::min(best, ms);  // the first is a warm-up
+          if (rep > 0) best = std::min(best, ms / (float)runs);  // the first is a warm-up
+          // a short product several times in a row, as a solver queues it: alone
+          // it is also its launches, of which the candidates have two or three
+          // (3070 x 682 on 32 signals, A^H R: dense_mm_kernel won alone, and
+          // queued the library takes 22.1 us against 24.1)
+          else if (ms < 0.08f) runs = 6;
         }
         return best;
       };
