@@ -236,7 +236,6 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   float2 sv[E];   // saved intermediate
   float gt[E];    // phase-cotangent accumulator
   typename T::Twiddles w;
-  T::load_twiddles(w, EV ? a.tw_n : a.tw, t);
   const Rsrc r_in = rsrc(a.in - (IN_WIN ? m_cut : i_cut));
   const Rsrc r_out = rsrc(a.out - u_cut);
   const Rsrc r_pre = TAB ? rsrc(a.ep_pre) : rsrc(a.th_pre);
@@ -264,6 +263,11 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
 #pragma unroll
     for (int j = 0; j < E; ++j) v[j] = ld2(r_in, off(in_win(j), i_lane + o_in, 8), (unsigned)(j * i_step) * 8u);
   }
+  // Twiddles after what the first butterflies wait for, since loads return in
+  // order, and no arithmetic before the last load is issued (the barrier below):
+  // GD on a 512 x 512 grid 19.2 -> 18.6 us an iteration, power iteration 21.0 ->
+  // 20.6, a four-column store pass 0.17 us.
+  if constexpr (!PRE_PH) T::load_twiddles(w, EV ? a.tw_n : a.tw, t);
 #pragma unroll
   for (int j = 0; j < E; ++j) {
     if constexpr (PRE_PH) dp[j] = ld_phase(r_pre, in_win(j) ? p_all : kOob, j);
@@ -285,6 +289,8 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
       }
     }
   }
+  if constexpr (PRE_PH) T::load_twiddles(w, EV ? a.tw_n : a.tw, t);
+  __builtin_amdgcn_sched_barrier(0);  // no arithmetic, and so no wait, among the loads
   // phases -> diagonal entries where no table was given (the sixteen-
   // element shape forms the mid and post entries where they are used, so
   // that only the phases stay live across the first transform)
