@@ -82,8 +82,9 @@ typedef enum {
  * (one launch per pass level over all problems: A, A^H, GD, power
  * iteration and both derivatives, the latter where no two problems share
  * a phase block);
- * GD and power iteration run the problems with a 96-, 192- or 384-point axis
- * on a second stream beside the others; with SR_LDS_RESIDENT=1, problems
+ * GD and power iteration of 4M grid points and more run as two balanced
+ * groups, one on a second stream, and so do the halves of a stack of that
+ * size under GD of 16 iterations and more; with SR_LDS_RESIDENT=1, problems
  * whose grid fits one workgroup's LDS solve there instead, beside the
  * levels.                                                                   */
 typedef enum {
