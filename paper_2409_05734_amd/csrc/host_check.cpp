@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "../../include/sr.h"
+#include "schedule.hpp"
 
 namespace {
 
@@ -80,6 +81,35 @@ void argument_checks() {
   expect(sr_plan_set_workspace(nullptr, nullptr, 0) == SR_E_ARG, "set_workspace NULL");
   expect(sr_plan_destroy(nullptr) == SR_OK, "destroy NULL");
   for (int s = 1; s >= -7; --s) expect(sr_status_string((sr_status)s) != nullptr, "status string");
+}
+
+// The two parts of a stack's power iteration run beside each other: nothing
+// that one of them reads or writes in any iteration is written by the other in
+// any iteration, and each reads what it wrote last.
+void stack_norm_checks() {
+  bool apart = true, chained = true, inside = true;
+  for (int P = 4; P <= 9; ++P)
+    for (int nq = 1; nq <= 5; ++nq) {
+      const sr::StackNorms nm{(size_t)P, (size_t)nq};
+      auto first = [&](int h) { return sr::stack_part_first(P, 2, h); };
+      auto hits = [](size_t a, size_t na, size_t b, size_t nb) { return a < b + nb && b < a + na; };
+      for (int h = 0; h < 2; ++h) {
+        const int lo = first(h), cnt = first(h + 1) - lo, lo2 = first(1 - h), cnt2 = first(2 - h) - lo2;
+        inside = inside && nm.start(lo) + cnt <= nm.floats();
+        for (int i = 0; i < 4; ++i) {
+          const size_t w = nm.out(i, lo), wn = (size_t)cnt * nq;
+          inside = inside && w + wn <= nm.floats() && nm.in(i, lo) + (size_t)cnt * nm.in_count(i) <= nm.floats();
+          chained = chained && nm.in(i + 1, lo) == w && nm.in_count(i + 1) == nq;
+          apart = apart && !hits(w, wn, nm.in(i, lo), (size_t)cnt * nm.in_count(i));
+          for (int j = 0; j < 4; ++j)
+            apart = apart && !hits(w, wn, nm.out(j, lo2), (size_t)cnt2 * nq) &&
+                    !hits(w, wn, nm.in(j, lo2), (size_t)cnt2 * nm.in_count(j));
+        }
+      }
+    }
+  expect(apart, "norm partials of a stack's parts are apart");
+  expect(chained, "an iteration reads the partials of the one before");
+  expect(inside, "norm partials within the buffer");
 }
 
 template <class T>
@@ -196,6 +226,7 @@ int main(int argc, char** argv) {
   const bool no_gpu = argc > 1 && std::strcmp(argv[1], "--no-gpu") == 0;
   std::printf("argument checks\n");
   argument_checks();
+  stack_norm_checks();
   if (!no_gpu) {
     int count = 0;
     if (hipGetDeviceCount(&count) != hipSuccess || count == 0) {

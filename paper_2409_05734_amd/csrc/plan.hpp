@@ -127,7 +127,7 @@ struct sr_plan_s {
   size_t stk_elems = 0;
   float* stk_gth = nullptr;   // per-problem phase cotangents of a stack sharing its phases
   size_t stk_gth_elems = 0;
-  float* stk_part = nullptr;           // squared-norm partials of a stacked spectral solve (2 sets)
+  float* stk_part = nullptr;           // squared-norm partials of a stacked spectral solve (StackNorms), loss partials of a traced one
   size_t stk_part_elems = 0;
   float* stk_steps = nullptr;          // device: per-problem GD steps of a stack
   int stk_steps_cap = 0;

@@ -163,6 +163,28 @@ inline sr_status ensure_stack_parts(sr_plan_s* p, size_t elems) {
   return SR_OK;
 }
 
+// Where a stack's power iteration keeps its squared-norm partials (floats of
+// stk_part, P problems of nq partials each): two sets written in turn,
+// iteration `it` reading set it & 1 and writing the other, and behind them the
+// start vectors' norms, one a problem, which iteration 0 reads.  Two parts of
+// a stack iterate beside each other with nothing that orders one's iteration
+// after the other's, so a problem's entries have to be its own in every
+// iteration: the start norms share no set, in which their packing would put
+// one part's under the other's partials.
+struct StackNorms {
+  size_t P, nq;
+  size_t set() const { return P * std::max<size_t>(nq, 1); }
+  size_t floats() const { return 2 * set() + P; }
+  size_t start(int lo) const { return 2 * set() + lo; }
+  // iteration it of the problems from lo on: reads in_count(it) partials a
+  // problem at in(it, lo), writes nq a problem at out(it, lo)
+  size_t in(int it, int lo) const { return it == 0 ? start(lo) : (it & 1) * set() + lo * nq; }
+  int in_count(int it) const { return it == 0 ? 1 : (int)nq; }
+  size_t out(int it, int lo) const { return ((it + 1) & 1) * set() + lo * nq; }
+};
+// First problem of part h of a stack of P in `parts` parts.
+inline int stack_part_first(int P, int parts, int h) { return (int)((int64_t)P * h / parts); }
+
 // Runs a stack for the lifetime of the object: the plan's ping-pong buffers
 // are the stacked ones (registered with stride mg), restored afterwards.
 struct StackScope {

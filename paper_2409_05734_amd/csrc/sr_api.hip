@@ -643,7 +643,7 @@ static int stack_parts(const sr_plan_s* p, const Geo& g, int P, int iters) {
 // a stack.
 template <class F>
 static sr_status on_stack_part(sr_plan_s* p, int P, int ths, int parts, int h, float2* x, const float* y, F&& f) {
-  const int lo = (int)((int64_t)P * h / parts), cnt = (int)((int64_t)P * (h + 1) / parts) - lo;
+  const int lo = stack_part_first(P, parts, h), cnt = stack_part_first(P, parts, h + 1) - lo;
   StackScope sc(p, cnt, ths, lo, P);
   Geo q = p->geo[0];
   q.th_off += (int64_t)lo * ths;
@@ -1232,16 +1232,19 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
                                   float lambda, float2* x) {
   const Geo& g = p->geo[0];
   const float inv_mc = (float)((double)g.mg / (double)g.m);
-  const int nq = last_pass_groups(p, g);
-  const size_t pstride = (size_t)P * (size_t)std::max(nq, 1);
+  const StackNorms nm{(size_t)P, (size_t)last_pass_groups(p, g)};
   SR_CHECK(ensure_stack_bufs(p, 2 * (size_t)P * g.mg));
-  SR_CHECK(ensure_stack_parts(p, 2 * pstride));
-  float* parts[2] = {p->stk_part, p->stk_part + pstride};
+  SR_CHECK(ensure_stack_parts(p, nm.floats()));
+  float* part = p->stk_part;
   // sum(y) and the start vector's squared norm, per problem (one partial each)
   SR_HIP(hipMemcpyAsync(x, v0, sizeof(float2) * g.n * P, hipMemcpyDeviceToDevice, p->stream));
   SR_CHECK(sum_floats(p, y, g.m, p->ysum, P));
-  SR_CHECK(norm2_partial(p, x, g.n, parts[0], P));
-  int npart = 1;
+  SR_CHECK(norm2_partial(p, x, g.n, part + nm.start(0), P));
+  // iteration it of the problems from lo on
+  auto steady = [&](const Geo& q, float2* xp, const float* yp, int lo, int it) {
+    return spec_steady(p, q, yp, xp, lambda, inv_mc, p->ysum + lo, part + nm.in(it, lo), nm.in_count(it),
+                       part + nm.out(it, lo), it == iters - 1);
+  };
   if (const int halves = stack_parts(p, g, P, iters); halves > 1 && iters > 0) {
     for (int h = 0; h < halves; ++h)
       SR_CHECK(on_stack_part(p, P, ths, halves, h, x, y, [&](const Geo& q, float2* xp, const float*, int) {
@@ -1249,12 +1252,9 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
       }));
     SR_CHECK(beside(p, halves, iters, [&](int it, int h) {
       return on_stack_part(p, P, ths, halves, h, x, y, [&](const Geo& q, float2* xp, const float* yp, int lo) {
-        const int ni = it == 0 ? 1 : nq;  // the start vector has one partial a problem
-        return spec_steady(p, q, yp, xp, lambda, inv_mc, p->ysum + lo, parts[it & 1] + (size_t)lo * ni, ni,
-                           parts[(it + 1) & 1] + (size_t)lo * nq, it == iters - 1);
+        return steady(q, xp, yp, lo, it);
       });
     }));
-    npart = nq;
   } else {
     StackScope sc(p, P, ths);
     p->stk.add(x, g.n, sizeof(float2), (int)g.n);
@@ -1262,8 +1262,7 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
     int it = 0;
     if (iters > 0) SR_CHECK(first_pass(p, g, x, 1.f, nullptr, 0));
     if (iters > 1) {
-      SR_CHECK(spec_steady(p, g, y, x, lambda, inv_mc, p->ysum, parts[0], npart, parts[1], false));
-      npart = nq;
+      SR_CHECK(steady(g, x, y, 0, 0));
       it = 1;
     }
     if (graphs_enabled(p, P * g.mg) && iters - 1 - it >= kGraphChunk) {
@@ -1271,21 +1270,14 @@ static sr_status spectral_stacked(sr_plan_s* p, int P, int ths, const float* y, 
                               ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_part) + ":" + float_key(lambda);
       for (; it + kGraphChunk <= iters - 1; it += kGraphChunk)
         SR_CHECK(launch_captured(p, key, [&]() -> sr_status {
-          for (int c = 0; c < kGraphChunk; ++c) {
-            const int q = it + c;
-            SR_CHECK(spec_steady(p, g, y, x, lambda, inv_mc, p->ysum, parts[q & 1], nq, parts[(q + 1) & 1], false));
-          }
+          for (int c = 0; c < kGraphChunk; ++c) SR_CHECK(steady(g, x, y, 0, it + c));
           return SR_OK;
         }));
     }
-    for (; it < iters; ++it) {
-      SR_CHECK(spec_steady(p, g, y, x, lambda, inv_mc, p->ysum, parts[it & 1], npart, parts[(it + 1) & 1],
-                           it == iters - 1));
-      npart = nq;
-    }
+    for (; it < iters; ++it) SR_CHECK(steady(g, x, y, 0, it));
   }
   // x0 = sqrt(sum(y)/(m c)) u / ||u||, per problem
-  return final_scale(p, x, g.n, parts[iters & 1], npart, p->ysum, inv_mc, P);
+  return final_scale(p, x, g.n, part + nm.in(iters, 0), nm.in_count(iters), p->ysum, inv_mc, P);
 }
 
 sr_status sr_spectral_init(sr_plan p, const float* y, const void* v0, int32_t iters, float lambda, void* x0_out) {
