@@ -13,6 +13,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <string>
 #include <vector>
 
 #include "../../include/sr.h"
@@ -110,6 +111,28 @@ void stack_norm_checks() {
   expect(apart, "norm partials of a stack's parts are apart");
   expect(chained, "an iteration reads the partials of the one before");
   expect(inside, "norm partials within the buffer");
+}
+
+// Which stacks run in two parts, on both sides of each line (the counts of
+// tests/test_gpu_stack_rule.py among them).
+void stack_rule_checks() {
+  const char* was = std::getenv("SR_STACK_PARTS");
+  const std::string kept = was ? was : "";
+  unsetenv("SR_STACK_PARTS");
+  const int64_t mg = 256 * 256;
+  expect(sr::stack_parts_rule(62 * mg, 62, 16) == 2, "62 of 256 x 256, 16 iterations: two parts");
+  expect(sr::stack_parts_rule(62 * mg, 62, 15) == 1, "15 iterations: one part");
+  expect(sr::stack_parts_rule(60 * mg, 60, 16) == 2, "60 of 256 x 256: two parts");
+  expect(sr::stack_parts_rule(59 * mg, 59, 16) == 1, "59 of 256 x 256: one part");
+  expect(sr::stack_parts_rule(4 * 1024 * 1024, 4, 16) == 2, "4 of 1024 x 1024: two parts");
+  expect(sr::stack_parts_rule(3 * 2048 * 2048, 3, 16) == 1, "three problems: one part");
+  setenv("SR_STACK_PARTS", "1", 1);
+  expect(sr::stack_parts_rule(62 * mg, 62, 16) == 1, "one part by name");
+  setenv("SR_STACK_PARTS", "2", 1);
+  expect(sr::stack_parts_rule(4 * 256, 4, 1) == 2, "two parts by name");
+  expect(sr::stack_parts_rule(3 * 256, 3, 1) == 1, "two parts by name, three problems");
+  if (was) setenv("SR_STACK_PARTS", kept.c_str(), 1);
+  else unsetenv("SR_STACK_PARTS");
 }
 
 template <class T>
@@ -227,6 +250,7 @@ int main(int argc, char** argv) {
   std::printf("argument checks\n");
   argument_checks();
   stack_norm_checks();
+  stack_rule_checks();
   if (!no_gpu) {
     int count = 0;
     if (hipGetDeviceCount(&count) != hipSuccess || count == 0) {

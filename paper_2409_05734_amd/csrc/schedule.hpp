@@ -182,6 +182,31 @@ struct StackNorms {
   int in_count(int it) const { return it == 0 ? 1 : (int)nq; }
   size_t out(int it, int lo) const { return ((it + 1) & 1) * set() + lo * nq; }
 };
+// Parts of a stack whose iterations run beside each other, on streams of their
+// own.  A pass of a large stack spends its first and last microseconds
+// with the memory system idle, and its workgroups load and transform in step;
+// two halves fill each other's gaps.  60 iterations, one part -> two: 16 of 512
+// x 512, L = 2 (4.2M points) 3678 -> 3230 us, 64 (16.8M) 15050 -> 14160; 4.2M
+// points of 256 x 256 3550 -> 3140, of 1024 x 1024 4600 -> 4070, of 384 x 384
+// 3980 -> 3230, of 2048 x 512 6970 -> 6920, of 768 x 512 (3.9M) 4140 -> 3980;
+// below, halves are too short: 8 of 512 x 512 (2.1M) 2337 -> 2370, 16 of 256 x
+// 256 (1.0M) 1332 -> 1830.  Short solves (one iteration a call in unrolled
+// training) lose to the fork and the join: 64 of 256 x 256, 10 steps and their
+// reverse 5039 -> 5981 us.  The line lies at the smallest of the sizes measured
+// that gained at every shape; between it and 2.1M points, where one shape gained
+// (32 of 256 x 256, 2170 -> 1970) and one lost, nothing was measured.  Power
+// iteration as GD: 16 of 512 x 512, 300 iterations 18190 -> 15970 us.
+// SR_STACK_PARTS=1 / 2 sets it.
+constexpr int64_t kPartPoints = 3900000;
+constexpr int kPartIters = 16;
+// points: grid points of the P problems together.
+inline int stack_parts_rule(int64_t points, int P, int iters) {
+  if (P < 4) return 1;  // a part is a stack (reads its steps from the array): two problems at least
+  const char* env = std::getenv("SR_STACK_PARTS");
+  if (env != nullptr) return std::atoi(env) == 2 ? 2 : 1;
+  return iters >= kPartIters && points >= kPartPoints ? 2 : 1;
+}
+
 // First problem of part h of a stack of P in `parts` parts.
 inline int stack_part_first(int P, int parts, int h) { return (int)((int64_t)P * h / parts); }
 

@@ -614,29 +614,9 @@ static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, 
   return SR_OK;
 }
 
-// Parts of a stack whose iterations run beside each other, on streams of their
-// own.  A pass of a large stack spends its first and last microseconds
-// with the memory system idle, and its workgroups load and transform in step;
-// two halves fill each other's gaps.  60 iterations, one part -> two: 16 of 512
-// x 512, L = 2 (4.2M points) 3678 -> 3230 us, 64 (16.8M) 15050 -> 14160; 4.2M
-// points of 256 x 256 3550 -> 3140, of 1024 x 1024 4600 -> 4070, of 384 x 384
-// 3980 -> 3230, of 2048 x 512 6970 -> 6920, of 768 x 512 (3.9M) 4140 -> 3980;
-// below, halves are too short: 8 of 512 x 512 (2.1M) 2337 -> 2370, 16 of 256 x
-// 256 (1.0M) 1332 -> 1830.  Short solves (one iteration a call in unrolled
-// training) lose to the fork and the join: 64 of 256 x 256, 10 steps and their
-// reverse 5039 -> 5981 us.  SR_STACK_PARTS=1 / 2 sets it.
-constexpr int64_t kPartPoints = 3900000;
-constexpr int kPartIters = 16;
-static int stack_parts(const Geo& g, int P, int iters) {
-  if (P < 4) return 1;  // a part is a stack (reads its steps from the array): two problems at least
-  const char* env = std::getenv("SR_STACK_PARTS");
-  if (env != nullptr) return std::atoi(env) == 2 ? 2 : 1;
-  return iters >= kPartIters && (int64_t)P * g.mg >= kPartPoints ? 2 : 1;
-}
-
 static int stack_parts(const sr_plan_s* p, const Geo& g, int P, int iters) {
   if (p->aux_stream == nullptr && stream_capturing(p)) return 1;  // (no stream is made inside a capture)
-  return stack_parts(g, P, iters);
+  return stack_parts_rule(P * g.mg, P, iters);
 }
 
 // f(geometry, signals, measurements, number of its first problem) on part h of
