@@ -26,7 +26,9 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
+#include <string>
 
 #include "dense_bf16.hpp"
 #include "dense_rows.hpp"
@@ -531,7 +533,6 @@ struct DenseLib {
   hipblasLtMatrixLayout_t l1[3] = {nullptr, nullptr, nullptr};  // Bxt, At_cm, D1
   hipblasLtMatrixLayout_t l2[3] = {nullptr, nullptr, nullptr};  // At_cm, Br, D2
   hipblasLtMatmulAlgo_t algo[2];
-  bool ok[2] = {false, false};   // the product has a library algorithm
   bool use[2] = {false, false};  // the product runs on it (else dense_mm_kernel)
   void* ws = nullptr;
   size_t ws_bytes = 0;
@@ -666,46 +667,29 @@ static bool rows_plan(const sr_plan_s* p) {
   return (long long)nb * std::max(s.G, rows_update_groups((int)g.n)) <= 2LL * p->part_cap;
 }
 
-// Scratch layout for dense plans: bufA holds R (nb x m complex); fscratch
-// holds per-signal scalars; part holds per-signal partials.
-sr_status dense_lib_setup(sr_plan_s* p) {
-  const char* force = std::getenv("SR_DENSE_GEMM");
-  if (force == nullptr && rows_plan(p)) {  // every product runs on the row kernels: nothing to time
-    p->dense_rows = true;
-    return SR_OK;
-  }
-  if (force != nullptr && std::strcmp(force, "own") == 0) return SR_OK;
-  DenseArgs a = base(p);
-  // the bf16 products load A sixteen bytes at a time
-  const bool bf16_ok = (uintptr_t)a.A % 16 == 0;  // (n is even)
-  if (force != nullptr && std::strcmp(force, "bf16") == 0) {
-    p->dense_bf16 = bf16_ok ? 3 : 0;
-    return SR_OK;
-  }
+// The library's state for a plan's products: up to kLibCandidates of its
+// algorithms per product, in its heuristic's order.  Null where it cannot be
+// had (no handle, no algorithm, no memory).
+struct LibCandidates {
+  hipblasLtMatmulAlgo_t algo[2][kLibCandidates];
+  int n[2] = {0, 0};
+};
+static DenseLib* open_lib(const DenseArgs& a, LibCandidates* cand) {
+  std::unique_ptr<DenseLib> d(new (std::nothrow) DenseLib());
   const uint64_t q = 64 * (uint64_t)signal_tiles(a), m = (uint64_t)a.m, n2 = 2 * (uint64_t)a.n;
-  DenseLib* d = new (std::nothrow) DenseLib();
-  if (d == nullptr) return SR_OK;
-  auto give_up = [&]() {
-    delete d;
-    return SR_OK;  // the hand-written products serve every plan
-  };
-  if (hipblasLtCreate(&d->h) != HIPBLAS_STATUS_SUCCESS) return give_up();
-  if (hipblasLtMatmulDescCreate(&d->desc, HIPBLAS_COMPUTE_32F, HIP_R_32F) != HIPBLAS_STATUS_SUCCESS) return give_up();
-  if (hipblasLtMatrixLayoutCreate(&d->l1[0], HIP_R_32F, q, n2, (int64_t)q) != HIPBLAS_STATUS_SUCCESS ||
+  if (d == nullptr || hipblasLtCreate(&d->h) != HIPBLAS_STATUS_SUCCESS ||
+      hipblasLtMatmulDescCreate(&d->desc, HIPBLAS_COMPUTE_32F, HIP_R_32F) != HIPBLAS_STATUS_SUCCESS ||
+      hipblasLtMatrixLayoutCreate(&d->l1[0], HIP_R_32F, q, n2, (int64_t)q) != HIPBLAS_STATUS_SUCCESS ||
       hipblasLtMatrixLayoutCreate(&d->l1[1], HIP_R_32F, n2, m, (int64_t)n2) != HIPBLAS_STATUS_SUCCESS ||
       hipblasLtMatrixLayoutCreate(&d->l1[2], HIP_R_32F, q, m, (int64_t)q) != HIPBLAS_STATUS_SUCCESS ||
       hipblasLtMatrixLayoutCreate(&d->l2[0], HIP_R_32F, n2, m, (int64_t)n2) != HIPBLAS_STATUS_SUCCESS ||
       hipblasLtMatrixLayoutCreate(&d->l2[1], HIP_R_32F, m, q, (int64_t)m) != HIPBLAS_STATUS_SUCCESS ||
       hipblasLtMatrixLayoutCreate(&d->l2[2], HIP_R_32F, n2, q, (int64_t)n2) != HIPBLAS_STATUS_SUCCESS)
-    return give_up();
+    return nullptr;
   hipblasLtMatmulPreference_t pref = nullptr;
-  if (hipblasLtMatmulPreferenceCreate(&pref) != HIPBLAS_STATUS_SUCCESS) return give_up();
+  if (hipblasLtMatmulPreferenceCreate(&pref) != HIPBLAS_STATUS_SUCCESS) return nullptr;
   const uint64_t wmax = kLibWorkspace;
   (void)hipblasLtMatmulPreferenceSetAttribute(pref, HIPBLASLT_MATMUL_PREF_MAX_WORKSPACE_BYTES, &wmax, sizeof(wmax));
-  // up to kLibCandidates of the library's algorithms per product, in its
-  // heuristic's order
-  hipblasLtMatmulAlgo_t cand[2][kLibCandidates];
-  int ncand[2] = {0, 0};
   size_t need = 0;
   for (int g = 0; g < 2; ++g) {
     const hipblasLtMatrixLayout_t* l = g == 0 ? d->l1 : d->l2;
@@ -716,100 +700,128 @@ sr_status dense_lib_setup(sr_plan_s* p) {
       cnt = 0;
     for (int i = 0; i < cnt; ++i) {
       if (res[i].state != HIPBLAS_STATUS_SUCCESS) continue;
-      cand[g][ncand[g]++] = res[i].algo;
+      cand->algo[g][cand->n[g]++] = res[i].algo;
       need = std::max(need, res[i].workspaceSize);
     }
-    if (ncand[g] > 0) {
-      d->algo[g] = cand[g][0];
-      d->ok[g] = true;
-    }
+    if (cand->n[g] > 0) d->algo[g] = cand->algo[g][0];
   }
   (void)hipblasLtMatmulPreferenceDestroy(pref);
-  if (!d->ok[0] && !d->ok[1]) return give_up();
-  if (need > 0 && hipMalloc(&d->ws, need) != hipSuccess) return give_up();
+  if (cand->n[0] + cand->n[1] == 0) return nullptr;
+  if ((need > 0 && hipMalloc(&d->ws, need) != hipSuccess) ||
+      hipMalloc(&d->pack, sizeof(float) * std::max(q * n2, m * q)) != hipSuccess) {
+    (void)hipGetLastError();  // (the hand-written products' launches ask for the last error)
+    return nullptr;
+  }
   d->ws_bytes = need;
-  if (hipMalloc(&d->pack, sizeof(float) * std::max(q * n2, m * q)) != hipSuccess) return give_up();
-  // per product: the fastest of dense_mm_kernel, the bf16 products and the
-  // library's candidates (bf16 for the large ones, where A's stream bounds it:
-  // A X and A^H R of 16384 x 4096 on 32 signals 212 and 230 us in
-  // dense_mm_kernel, 158 and 171 us on the library, 141 and 127 us in bf16
-  // parts; dense_mm_kernel for the small ones, which are launches and
-  // latency: 1000 x 258 on 32 signals 12, 20 and 16 us; best of three applications each after a warm-up, on the plan's own
-  // matrix; the source is scratch of the right size, the epilogue writes
-  // nothing but scratch); SR_DENSE_GEMM=lib leaves the hand-written ones out
-  const bool all_lib = force != nullptr && std::strcmp(force, "lib") == 0;
+  return d.release();
+}
+
+// Scratch layout for dense plans: bufA holds R (nb x m complex); fscratch
+// holds per-signal scalars; part holds per-signal partials.
+//
+// Picks what runs each product: the fastest of dense_mm_kernel, the bf16
+// products and the library's candidates (bf16 for the large ones, where A's
+// stream bounds it: A X and A^H R of 16384 x 4096 on 32 signals 212 and 230 us
+// in dense_mm_kernel, 158 and 171 us on the library, 141 and 127 us in bf16
+// parts; dense_mm_kernel for the small ones, which are launches and latency:
+// 1000 x 258 on 32 signals 12, 20 and 16 us).  Each candidate runs once
+// untimed, then three times over timed on the plan's own matrix (the source is
+// scratch of the right size, the epilogue writes nothing but scratch) and its
+// best counts.  Products that stream A from memory in less than about 50 us
+// are timed six in a row, as a solver queues them: alone such a product is
+// also its launches, of which the candidates have two or three (3070 x 682 on
+// 32 signals, A^H R: dense_mm_kernel won alone, and queued the library takes
+// 22.1 us against 24.1).  The count follows from the shape, so that all
+// candidates are measured alike.
+//
+// SR_DENSE_GEMM=own / bf16 / lib pins one of the three, SR_DENSE_GEMM=hand
+// leaves the library out.
+constexpr long long kQueuedBytes = 1ll << 28;
+sr_status dense_lib_setup(sr_plan_s* p) {
+  const char* env = std::getenv("SR_DENSE_GEMM");
+  const std::string force = env != nullptr ? env : "";
+  if (env == nullptr && rows_plan(p)) {  // every product runs on the row kernels: nothing to time
+    p->dense_rows = true;
+    return SR_OK;
+  }
+  if (force == "own") return SR_OK;
+  DenseArgs a = base(p);
+  // the bf16 products load A sixteen bytes at a time
+  const bool bf16_ok = (uintptr_t)a.A % 16 == 0;  // (n is even)
+  if (force == "bf16") {
+    p->dense_bf16 = bf16_ok ? 3 : 0;
+    return SR_OK;
+  }
+  const bool all_lib = force == "lib";
   const bool can_time = (size_t)a.n <= (size_t)a.m;  // bufB (m x nb) holds the A^H R output
+  if (!can_time && !all_lib) return SR_OK;
+  LibCandidates cand;
+  std::unique_ptr<DenseLib> d(force == "hand" ? nullptr : open_lib(a, &cand));
+  if (all_lib && d == nullptr) return SR_OK;
   hipEvent_t e0 = nullptr, e1 = nullptr;
-  if (!can_time || hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
-    if (e0) (void)hipEventDestroy(e0);
-    if (!all_lib) return give_up();
-    for (int g = 0; g < 2; ++g) d->use[g] = d->ok[g];  // the heuristic's first choice, untimed
-    e0 = e1 = nullptr;
-  } else {
-    // (any finite source)
-    if (hipMemsetD32Async((hipDeviceptr_t)p->bufA, 0x3f800000, 2 * (size_t)a.m * a.nb, p->stream) != hipSuccess)
-      return give_up();
+  if (can_time && hipEventCreate(&e0) == hipSuccess && hipEventCreate(&e1) == hipSuccess &&
+      // (any finite source)
+      hipMemsetD32Async((hipDeviceptr_t)p->bufA, 0x3f800000, 2 * (size_t)a.m * a.nb, p->stream) == hipSuccess) {
+    const int runs = 8ll * a.m * a.n * signal_tiles(a) < kQueuedBytes ? 6 : 1;
     for (int g = 0; g < 2; ++g) {
-      if (!d->ok[g]) continue;
       auto time_it = [&]() -> float {
         DenseArgs t = a;
         t.src = p->bufA;
         t.x = p->bufB;
         t.step = 1.f;
         float best = 1e30f;
-        int runs = 1;
         for (int rep = 0; rep < 4; ++rep) {
-          (void)hipEventRecord(e0, p->stream);
-          hipError_t e = hipSuccess;
-          for (int i = 0; i < runs && e == hipSuccess; ++i)
-            e = g == 0 ? gemm<1, E1_STORE>(t, p->dsplit, p->stream, d) : gemm<2, E2_STORE>(t, p->dsplit, p->stream, d);
-          (void)hipEventRecord(e1, p->stream);
-          if (e != hipSuccess || hipEventSynchronize(e1) != hipSuccess) return 1e30f;
+          hipError_t e = hipEventRecord(e0, p->stream);
+          for (int i = 0; i < (rep == 0 ? 1 : runs) && e == hipSuccess; ++i)
+            e = g == 0 ? gemm<1, E1_STORE>(t, p->dsplit, p->stream, d.get())
+                       : gemm<2, E2_STORE>(t, p->dsplit, p->stream, d.get());
+          if (e == hipSuccess) e = hipEventRecord(e1, p->stream);
+          if (e == hipSuccess) e = hipEventSynchronize(e1);
           float ms = 0.f;
-          (void)hipEventElapsedTime(&ms, e0, e1);
-          if (rep > 0) best = std::min(best, ms / (float)runs);  // the first is a warm-up
-          // a short product several times in a row, as a solver queues it: alone
-          // it is also its launches, of which the candidates have two or three
-          // (3070 x 682 on 32 signals, A^H R: dense_mm_kernel won alone, and
-          // queued the library takes 22.1 us against 24.1)
-          else if (ms < 0.08f) runs = 6;
+          if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+          if (e != hipSuccess) return 1e30f;
+          if (rep > 0) best = std::min(best, ms);  // the first loads the kernel
         }
         return best;
       };
       float best = 1e30f;
       int pick = -1;  // -1: dense_mm_kernel, or the bf16 products
+      bool bf16 = false;
+      if (d != nullptr) d->use[g] = false;
       if (!all_lib) {
-        d->use[g] = false;
         best = time_it();
         if (bf16_ok) {
           a.bf16[g] = true;
           const float t = time_it();
-          a.bf16[g] = t < best;
+          a.bf16[g] = false;
+          bf16 = t < best;
           best = std::min(best, t);
         }
       }
-      const bool bf16 = a.bf16[g];
-      a.bf16[g] = false;
-      d->use[g] = true;
-      for (int c = 0; c < ncand[g]; ++c) {
-        d->algo[g] = cand[g][c];
+      for (int c = 0; c < cand.n[g]; ++c) {
+        d->use[g] = true;
+        d->algo[g] = cand.algo[g][c];
         const float t = time_it();
         if (t < best) {
           best = t;
           pick = c;
         }
       }
-      if (all_lib && pick < 0) pick = 0;
-      d->use[g] = pick >= 0;
+      if (all_lib && pick < 0 && cand.n[g] > 0) pick = 0;
       if (pick < 0 && bf16) p->dense_bf16 |= 1u << g;
-      if (pick >= 0) d->algo[g] = cand[g][pick];
+      if (d != nullptr) d->use[g] = pick >= 0;
+      if (pick >= 0) d->algo[g] = cand.algo[g][pick];
     }
+  } else if (all_lib) {
+    for (int g = 0; g < 2; ++g) d->use[g] = cand.n[g] > 0;  // the heuristic's first choice, untimed
   }
   if (e0) (void)hipEventDestroy(e0);
   if (e1) (void)hipEventDestroy(e1);
-  if (hipStreamSynchronize(p->stream) != hipSuccess) return give_up();
-  if (!d->use[0] && !d->use[1]) return give_up();
-  p->dense_lib = d;
+  if (hipStreamSynchronize(p->stream) != hipSuccess) {
+    p->dense_bf16 = 0;
+    return SR_OK;
+  }
+  if (d != nullptr && (d->use[0] || d->use[1])) p->dense_lib = d.release();
   return SR_OK;
 }
 

@@ -208,7 +208,8 @@ sr_status dense_adjoint(sr_plan_s* p, const float2* r, float2* x);
 sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const float* eta, float* loss_trace);
 sr_status dense_spectral(sr_plan_s* p, const float* y, const float2* v0, int iters, float lam, float2* x0);
 // bf16 parts or hipBLASLt for the dense products where they are faster (timed
-// per product at plan creation; SR_DENSE_GEMM=own / bf16 / lib pins the choice)
+// per product at plan creation; SR_DENSE_GEMM=own / bf16 / lib pins the choice,
+// SR_DENSE_GEMM=hand leaves the library out)
 sr_status dense_lib_setup(sr_plan_s* p);
 
 // fused2d.hip (LDS-resident solves of small 2D problems, one workgroup each)
