@@ -14,7 +14,9 @@
 // problems: 9.3 ms with tables, 9.0 ms with polynomials of the tables'
 // accuracy (7.8 ms with the hardware sine and cosine, which are eight times
 // less exact); 8.1 ms since the passes issue fewer instructions (passes.hpp).
-// Each problem owns private ping-pong buffers, so problems
+// Phases past the polynomials' range come from the tables (kPhasePolyMax; no
+// measurable cost), and all of them where SR_TUNE_FORCE or SR_PHASE_TABLE pins
+// the tables.  Each problem owns private ping-pong buffers, so problems
 // never share scratch.
 #include <hip/hip_runtime.h>
 
@@ -236,7 +238,7 @@ __device__ __forceinline__ void run_kind_vjp(const PassArgs& a, int kind, int ti
 }
 
 // LDS of one workgroup: two buffers of 256 threads' eight elements with one pad
-// in eight (the narrow and split shapes need no more).  Every length fits 125
+// in eight (the narrow and split shapes need no more).  Every length fits 110
 // VGPRs without spilling, so four workgroups share a CU.
 constexpr size_t kBatchLds = 2 * sizeof(float2) * kBatchThreads * 9;
 constexpr int kBatchGroups = 4;  // workgroups per CU
@@ -453,6 +455,10 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
       BatchDesc d;
       std::memset(&d, 0, sizeof(d));
       d.a = r.a;
+      d.a.ep_pre = table_of(p, r.a.th_pre);
+      d.a.ep_mid = table_of(p, r.a.th_mid);
+      d.a.ep_post = table_of(p, r.a.th_post);
+      d.a.th_poly_max = p->table_pinned ? -1.f : kPhasePolyMax;
       d.N = pass_len(g, r.k);
       d.col = pass_col(r.k);
       d.kind = r.kind;

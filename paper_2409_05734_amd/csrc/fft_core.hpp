@@ -66,7 +66,10 @@ __device__ __forceinline__ float2 phase_turns(float theta) {
 // of pi (in two parts, so that the difference keeps its last bits), sine and
 // cosine on [-pi/2, pi/2] by minimax fits of their even parts, and the sign of
 // the multiple.  About twice the issue time of the hardware pair; for kernels
-// where a table's memory traffic costs more than that.
+// where a table's memory traffic costs more than that.  The error stays there
+// up to kPhasePolyMax (1.7e-7 at most); from some 10^6 on the multiple itself
+// loses bits (2.8e-6 at 4 x 10^6, no phase at all at 10^8).
+constexpr float kPhasePolyMax = 131072.f;
 __device__ __forceinline__ float2 phase_poly(float theta) {
   constexpr double kPi = 3.141592653589793238462643383279502884;
   constexpr float kHi = (float)kPi, kLo = (float)(kPi - (double)kHi);

@@ -118,6 +118,9 @@ struct PassArgs {
   int stack, ntr_p;
   int s_in, s_out, s_out2, s_win, s_th, s_save, s_gth, s_xin;
   const float* step_v;  // GD update of a stack: each problem's step (nullable: `step` for all)
+  // POLY kernels: phases of larger magnitude are read from the tables (ep_*),
+  // where the polynomials' argument reduction would lose bits
+  float th_poly_max;
   // non-finite flag (nullable): the final update of a solve (POST_GD,
   // POST_SPEC) stores 1 here when an updated iterate entry is NaN or Inf
   unsigned* nf;
@@ -139,20 +142,13 @@ __device__ __forceinline__ float inv_norm_from_partials(const float* part, int n
   return (float)(1.0 / sqrt(block_sum_t<NTHREADS, double>(acc, redd)));
 }
 
-// A phase diagonal's entry evaluated on the fly: polynomials or the hardware
-// sine and cosine.
-template <bool POLY>
-__device__ __forceinline__ float2 phase_of(float theta) {
-  if constexpr (POLY) return phase_poly(theta);
-  else return phase_turns(theta);
-}
-
 // One tile (B transforms) of a fused pass.  `lds` holds 2*B*N complex
 // elements, `red` one float per thread.  part_in/npart/part_out override the
 // partial-sum pointers of `a` (persistent kernels alternate them per
 // iteration); partial sums are written at index `tile`.  TAB selects the
 // phase source: exp(i theta) tables (ep_*) or the phases themselves (th_*),
-// evaluated with the hardware's sine and cosine or (POLY) with polynomials.
+// evaluated with the hardware's sine and cosine or (POLY) with polynomials,
+// and read from the tables after all by a thread with a phase past th_poly_max.
 //
 // Every global load the tile needs (input, phases, measurements, twiddles,
 // the previous iterate) is issued up front, so a pass costs one memory
@@ -295,23 +291,40 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   // element shape forms the mid and post entries where they are used, so
   // that only the phases stay live across the first transform)
   constexpr bool LATE_PH = !TAB && E >= 16;
-  if constexpr (!TAB) {
+  // POLY: a diagonal's entries from its phases, or from its table where this
+  // thread has one past the polynomials' range
+  auto entries = [&](float2(&d)[E], const float2* tab, auto&& offset) {
+    float top = 0.f;
+#pragma unroll
+    for (int j = 0; j < E; ++j) top = fmaxf(top, fabsf(d[j].x));
+    if (top > a.th_poly_max) {
+#pragma unroll
+      for (int j = 0; j < E; ++j) d[j] = ld2(rsrc(tab), offset(j), (unsigned)(j * g_step) * 8u);
+    } else {
+#pragma unroll
+      for (int j = 0; j < E; ++j) d[j] = phase_poly(d[j].x);
+    }
+  };
+  const unsigned e_all = off(active, g_lane + o_th, 8);
+  static_assert(!POLY || (!TAB && !LATE_PH), "POLY kernels form the entries from phases");
+  if constexpr (POLY && PRE_PH) entries(dp, a.ep_pre, [&](int j) { return in_win(j) ? e_all : kOob; });
+  if constexpr (!TAB && !POLY) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
-      if constexpr (PRE_PH) dp[j] = phase_of<POLY>(dp[j].x);
-      if constexpr (MID_PH && !LATE_PH) dm[j] = phase_of<POLY>(dm[j].x);
-      if constexpr (POST_PH && !LATE_PH) dq[j] = phase_of<POLY>(dq[j].x);
+      if constexpr (PRE_PH) dp[j] = phase_turns(dp[j].x);
+      if constexpr (MID_PH && !LATE_PH) dm[j] = phase_turns(dm[j].x);
+      if constexpr (POST_PH && !LATE_PH) dq[j] = phase_turns(dq[j].x);
     }
   }
   // a weight of measurement j, zero outside the window (without WIN the lanes
   // outside hold zeros anyway: their loads returned none)
   auto in_weight = [&](int j, float wgt) -> float { return !WIN || m_in(j) ? wgt : 0.f; };
   auto Dm = [&](int j) -> float2 {
-    if constexpr (LATE_PH) return phase_of<POLY>(dm[j].x);
+    if constexpr (LATE_PH) return phase_turns(dm[j].x);
     else return dm[j];
   };
   auto Dq = [&](int j) -> float2 {
-    if constexpr (LATE_PH) return phase_of<POLY>(dq[j].x);
+    if constexpr (LATE_PH) return phase_turns(dq[j].x);
     else return dq[j];
   };
 
@@ -351,6 +364,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
   constexpr float kInvN = 1.f / (float)N;
   const float s_mid = a.scale_mid, s_out = a.scale_out;
   float acc = 0.f;
+  if constexpr (POLY && MID_PH) entries(dm, a.ep_mid, [&](int) { return e_all; });
   if constexpr (MID == MID_PHASE || MID == MID_PHASE_CONJ) {
 #pragma unroll
     for (int j = 0; j < E; ++j) {
@@ -450,6 +464,7 @@ __device__ __forceinline__ void pass_tile(const PassArgs& a, int tile, float2* l
       for (int j = 0; j < E; ++j) st2(r_out, off(out_win(j), u_lane + o_out, 8), (unsigned)(j * u_step) * 8u, val(j));
     }
   } else if constexpr (MID != MID_STORE) {
+    if constexpr (POLY) entries(dq, a.ep_post, [&](int j) { return out_win(j) ? e_all : kOob; });
     constexpr bool CHECK = (POST == POST_GD || POST == POST_SPEC);  // the last update of a solve
     bool bad = false;
     if constexpr (POST_IS_GD) {

@@ -94,6 +94,7 @@ struct sr_plan_s {
   float* theta = nullptr;  // device copy of the phases
   float2* eph = nullptr;   // exp(i theta), same layout (filled on device)
   bool use_table = false;  // passes read eph instead of evaluating sincos(theta)
+  bool table_pinned = false;  // ... by SR_TUNE_FORCE or SR_PHASE_TABLE: level launches too
   int64_t theta_len = 0;
   const float2* dense_A = nullptr;  // caller-owned dense matrix (SR_DENSE)
   sr::DenseLib* dense_lib = nullptr;  // library GEMM state of a dense plan (null: hand-written products only)

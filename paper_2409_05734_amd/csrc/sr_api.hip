@@ -353,12 +353,14 @@ static sr_status tune_plan(sr_plan_s* p) {
         p->tiles[{g.M1, 1}] = tile_offered(g.M1, true, c) ? c : default_tile(g.M1, true);
         p->tiles[{g.M2, 0}] = tile_offered(g.M2, false, r) ? r : default_tile(g.M2, false);
       }
-      p->use_table = t != 0;
+      p->use_table = p->table_pinned = t != 0;
       return SR_OK;
     }
   }
   const char* env = std::getenv("SR_TUNE");
   if (env != nullptr && std::atoi(env) == 0) return SR_OK;
+  const char* tab_env = std::getenv("SR_PHASE_TABLE");
+  p->table_pinned = tab_env != nullptr && std::atoi(tab_env) != 0;
   const char* cache = std::getenv("SR_TUNE_CACHE");
   // a plan that runs as a stack is timed as one (up to 2^23 grid points:
   // enough to fill the GPU), on zeroed stand-ins of that many problems
@@ -411,7 +413,6 @@ static sr_status tune_plan(sr_plan_s* p) {
         p->stk.add(x, g.n, sizeof(float2), (int)g.n);
         p->stk.add(y, g.m, sizeof(float), (int)g.m);
       }
-      const char* tab_env = std::getenv("SR_PHASE_TABLE");
       const int tab_lo = tab_env ? std::atoi(tab_env) : 0;
       const int tab_hi = tab_env ? std::atoi(tab_env) : 1;
       for (int tab = tab_lo; tab <= tab_hi; ++tab)
