@@ -636,35 +636,56 @@ int row_tiles_g2(const DenseArgs& a) { return (a.n + 31) / 32; }
 
 }  // namespace
 
-// Floats of split-reduction partials a dense plan of this shape needs: the
-// larger of the two products' S x (rows) x (64 per signal tile).
-size_t dense_split_floats(int m, int n, int nb) {
+// Whether a plan's products run on the row kernels: their shape, with room
+// for the per-signal partial sums of a solve.
+static bool rows_plan(const sr_plan_s* p, RowsShape* s) {
+  const Geo& g = p->geo[0];
+  const int nb = (int)p->geo.size();
+  if (g.m > (1 << 30) || g.n > 4096 || !rows_shape((int)g.m, (int)g.n, nb, s)) return false;
+  return (long long)nb * std::max(s->G, rows_update_groups((int)g.n)) <= 2LL * p->part_cap;
+}
+
+// What SR_DENSE_GEMM pins the products to ("" where it is not set).
+static std::string pinned_products() {
+  const char* env = std::getenv("SR_DENSE_GEMM");
+  return env != nullptr ? env : "";
+}
+
+// Whether a plan may run products in bf16 parts, which load A sixteen bytes at
+// a time (n is even).
+static bool bf16_plan(const sr_plan_s* p) {
+  const std::string pin = pinned_products();
+  if (p->dense_rows || pin == "own" || pin == "lib" || (uintptr_t)p->dense_A % 16 != 0) return false;
+  return pin == "bf16" || p->geo[0].n <= p->geo[0].m;  // (longer signals' products are not timed)
+}
+
+// Decides whether a dense plan runs on the row kernels, and what it needs
+// besides its vectors: floats of partial products, and bytes for the packed
+// small operand of the bf16 products.
+void dense_sizes(sr_plan_s* p, size_t* split, size_t* pack) {
+  const int m = (int)p->geo[0].m, n = (int)p->geo[0].n, nb = (int)p->geo.size();
+  RowsShape rs;
+  p->dense_rows = std::getenv("SR_DENSE_GEMM") == nullptr && rows_plan(p, &rs);
+  *pack = 0;
+  if (p->dense_rows) {
+    *split = 2 * (size_t)rs.G * nb * n;  // the workgroups' partials of A^H r
+    return;
+  }
   DenseArgs a{};
   a.m = m;
   a.n = n;
   a.nb = nb;
   const int st = signal_tiles(a);
-  int S1, S2, kc;
-  plan_split(((m + BT - 1) / BT) * st, 2 * n, &S1, &kc);
-  plan_split(((2 * n + BT - 1) / BT) * st, m, &S2, &kc);
-  const size_t f1 = (size_t)S1 * m * 64 * st;
-  const size_t f2 = (size_t)S2 * 2 * n * 64 * st;
-  RowsShape rs;
-  const size_t f3 = rows_shape(m, n, nb, &rs) ? 2 * (size_t)rs.G * nb * n : 0;  // the row kernels' partials of A^H r
-  int steps;
-  const size_t f4 = (size_t)bf16_splits(1, m, n, nb, &steps) * m * 64 * st;
-  const size_t f5 = (size_t)bf16_splits(2, m, n, nb, &steps) * 2 * n * 64 * st;
-  return std::max({f1, f2, f3, f4, f5});
-}
-
-// Whether a plan's products run on the row kernels: their shape, with room
-// for the per-signal partial sums of a solve.
-static bool rows_plan(const sr_plan_s* p) {
-  RowsShape s;
-  const Geo& g = p->geo[0];
-  const int nb = (int)p->geo.size();
-  if (g.m > (1 << 30) || g.n > 4096 || !rows_shape((int)g.m, (int)g.n, nb, &s)) return false;
-  return (long long)nb * std::max(s.G, rows_update_groups((int)g.n)) <= 2LL * p->part_cap;
+  // the larger of the two products' S x (rows) x (64 per signal tile)
+  int S1, S2, steps;
+  plan_split(((m + BT - 1) / BT) * st, 2 * n, &S1, &steps);
+  plan_split(((2 * n + BT - 1) / BT) * st, m, &S2, &steps);
+  if (bf16_plan(p)) {
+    S1 = std::max(S1, bf16_splits(1, m, n, nb, &steps));
+    S2 = std::max(S2, bf16_splits(2, m, n, nb, &steps));
+    *pack = bf16_pack_bytes(m, n, nb);
+  }
+  *split = std::max((size_t)S1 * m, (size_t)S2 * 2 * n) * 64 * st;
 }
 
 // The library's state for a plan's products: up to kLibCandidates of its
@@ -738,16 +759,11 @@ static DenseLib* open_lib(const DenseArgs& a, LibCandidates* cand) {
 // leaves the library out.
 constexpr long long kQueuedBytes = 1ll << 28;
 sr_status dense_lib_setup(sr_plan_s* p) {
-  const char* env = std::getenv("SR_DENSE_GEMM");
-  const std::string force = env != nullptr ? env : "";
-  if (env == nullptr && rows_plan(p)) {  // every product runs on the row kernels: nothing to time
-    p->dense_rows = true;
-    return SR_OK;
-  }
+  if (p->dense_rows) return SR_OK;  // every product runs on the row kernels
+  const std::string force = pinned_products();
   if (force == "own") return SR_OK;
   DenseArgs a = base(p);
-  // the bf16 products load A sixteen bytes at a time
-  const bool bf16_ok = (uintptr_t)a.A % 16 == 0;  // (n is even)
+  const bool bf16_ok = bf16_plan(p);
   if (force == "bf16") {
     p->dense_bf16 = bf16_ok ? 3 : 0;
     return SR_OK;

@@ -125,11 +125,9 @@ sr_status sr_plan_s::init(const float* theta_host) {
   size_t b_red = align256(sizeof(double) * 1024);
   size_t b_trace = kind == SR_DENSE ? 0 : align256(sizeof(float) * (size_t)sr::kTraceRows * (size_t)part_cap);
   int ngrid = (kind == SR_DENSE) ? 2 : 4;
-  size_t b_dsplit = 0;
-  if (kind == SR_DENSE)
-    b_dsplit = align256(sizeof(float) * sr::dense_split_floats((int)geo[0].m, (int)geo[0].n, (int)np));
-  const size_t b_dpack =
-      kind == SR_DENSE ? align256(sr::bf16_pack_bytes((int)geo[0].m, (int)geo[0].n, (int)np)) : 0;
+  size_t dsplit_floats = 0, dpack_bytes = 0;
+  if (kind == SR_DENSE) sr::dense_sizes(this, &dsplit_floats, &dpack_bytes);
+  const size_t b_dsplit = align256(sizeof(float) * dsplit_floats), b_dpack = align256(dpack_bytes);
   ws_bytes = b_theta + b_eph + b_tw + ngrid * b_grid + b_part + b_ysum + b_fs + b_sync + b_red + b_trace + b_dsplit + b_dpack;
   hipError_t e = hipMalloc(&ws, ws_bytes);
   if (e != hipSuccess) {

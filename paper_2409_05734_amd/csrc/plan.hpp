@@ -202,8 +202,7 @@ sr_status fill_phase_table(sr_plan_s* p);
 sr_status put_floats(sr_plan_s* p, float* dst, const float* host, int count);
 
 // dense.hip (i.i.d. complex Gaussian baseline)
-size_t dense_split_floats(int m, int n, int nb);
-size_t bf16_pack_bytes(int m, int n, int nb);
+void dense_sizes(sr_plan_s* p, size_t* split_floats, size_t* pack_bytes);
 sr_status dense_forward(sr_plan_s* p, const float2* x, float2* z, float* y);
 sr_status dense_adjoint(sr_plan_s* p, const float2* r, float2* x);
 sr_status dense_gd(sr_plan_s* p, const float* y, float2* x, int iters, const float* eta, float* loss_trace);

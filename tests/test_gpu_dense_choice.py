@@ -52,3 +52,25 @@ def test_same_answers(gpu, m, n, nb, shift, force, monkeypatch):
     A6 = A.to(torch.complex128)
     for got, want in ((z, X.to(torch.complex128) @ A6.T), (v, R.to(torch.complex128) @ A6.conj())):
         assert float((got - want).norm() / want.norm()) <= 2e-5
+
+
+def test_workspace_of_what_runs(gpu, monkeypatch):
+    """A plan holds the scratch of the kernels that it runs: one signal on the
+    row kernels 256 workgroups' partials of A^H r (8.4 MB) and the vectors; the
+    packed operand and the splits of the bf16 products only where they may run."""
+    import torch
+    import paper_2409_05734_amd as srpr
+
+    def size(m, n, nb, force=None):
+        if force is None:
+            monkeypatch.delenv("SR_DENSE_GEMM", raising=False)
+        else:
+            monkeypatch.setenv("SR_DENSE_GEMM", force)
+        A = torch.zeros(m, n, dtype=torch.complex64, device=gpu)
+        plan = srpr.Plan([srpr.Problem((n,), (m,), 1, kind=srpr.SR_DENSE) for _ in range(nb)], None, dense_A=A)
+        return srpr.sr_plan_workspace_size(plan)
+
+    assert size(16384, 4096, 1) <= 9_000_000
+    own, lib, bf16, free = (size(4096, 1024, 32, f) for f in ("own", "lib", "bf16", None))
+    assert own == lib < bf16 == free
+    assert size(300, 1024, 32) == size(300, 1024, 32, "own")  # n > m: the bf16 products are not considered
