@@ -855,16 +855,23 @@ static RowsArgs rows_base(const sr_plan_s* p, RowsShape* s) {
 }
 
 sr_status dense_forward(sr_plan_s* p, const float2* x, float2* z, float* y) {
+  const size_t xb = sizeof(float2) * (size_t)p->xoff.back(), zb = sizeof(float2) * (size_t)p->yoff.back();
+  const bool over = overlap(x, xb, z, zb) || overlap(x, xb, y, zb / 2);
   if (p->dense_rows) {
     RowsShape s;
     RowsArgs r = rows_base(p, &s);
     r.x = x;
+    if (over) {  // workgroups read x while others store: from a copy (the partials' buffer is idle, and as long)
+      DN_HIP(hipMemcpyAsync(r.part, x, xb, hipMemcpyDeviceToDevice, p->stream));
+      r.x = r.part;
+    }
     r.z_out = z;
     r.y_out = y;
     DN_HIP(launch_rows(ROWS_FWD, s, r, p->stream));
     return SR_OK;
   }
   DenseArgs a = base(p);
+  if (over) a.bf16[0] = false;  // (its epilogue reads x again where a product is not finite)
   a.src = x;
   a.z_out = z;
   a.y_out = y;
@@ -882,6 +889,8 @@ sr_status dense_adjoint(sr_plan_s* p, const float2* r, float2* x) {
     return SR_OK;
   }
   DenseArgs a = base(p);
+  if (overlap(r, sizeof(float2) * (size_t)p->yoff.back(), x, sizeof(float2) * (size_t)p->xoff.back()))
+    a.bf16[1] = false;  // (as above)
   a.src = r;
   a.x = x;
   a.step = 1.f;

@@ -34,6 +34,12 @@ struct Geo {
 // (the iterations of one captured graph).
 constexpr int kTraceRows = 50;
 
+// Whether two arrays of the caller share memory.
+inline bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t p = (uintptr_t)a, q = (uintptr_t)b;
+  return a != nullptr && b != nullptr && p < q + b_bytes && q < p + a_bytes;
+}
+
 sr_status fail(sr_status s, const std::string& msg);
 sr_status hip_fail(hipError_t e, const char* what);
 
