@@ -396,7 +396,10 @@ static sr_status tune_plan(sr_plan_s* p) {
     done.push_back(key);
     if (p->tiles.count({g.M1, 1}) && p->tiles.count({g.M2, 0})) continue;  // decided by an earlier shape
     int cb = 0, rb = 0, tb = 0;
-    if (!tune_cache_lookup(cache, key, &cb, &rb, &tb)) {
+    // (a file may hold tiles that this build does not have: thread shapes, and
+    // with them the tiles of a length, differ between builds)
+    if (!tune_cache_lookup(cache, key, &cb, &rb, &tb) || !tile_offered(g.M1, true, cb) ||
+        !tile_offered(g.M2, false, rb)) {
       int copt[16], ropt[16];
       const int nc = tile_options(g.M1, true, copt, 16);
       const int nr = tile_options(g.M2, false, ropt, 16);
