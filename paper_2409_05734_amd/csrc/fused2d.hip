@@ -25,6 +25,7 @@
 #include <vector>
 
 #include "launch.hpp"
+#include "lds_limit.hpp"
 #include "loss.hpp"
 #include "plan.hpp"
 
@@ -442,12 +443,8 @@ static sr_status f2_launch(sr_plan_s* p, const std::vector<F2Desc>& descs, size_
   std::memcpy(host.data(), descs.data(), bytes);
   hipError_t e = hipMemcpyAsync(p->f2_descs, host.data(), bytes, hipMemcpyHostToDevice, s);
   if (e != hipSuccess) return hip_fail(e, "descriptor upload");
-  static bool raised = false;
-  if (!raised) {
-    e = hipFuncSetAttribute((const void*)fused2d_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, kF2GridBytes);
-    if (e != hipSuccess) return hip_fail(e, "LDS attribute");
-    raised = true;
-  }
+  static LdsLimit limit;
+  if ((e = limit.raise((const void*)fused2d_kernel, kF2GridBytes)) != hipSuccess) return hip_fail(e, "LDS attribute");
   hipLaunchKernelGGL(fused2d_kernel, dim3((unsigned)descs.size()), dim3(kF2Threads), lds, s,
                      (const F2Desc*)p->f2_descs);
   e = hipGetLastError();

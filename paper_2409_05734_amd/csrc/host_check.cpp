@@ -17,6 +17,7 @@
 #include <vector>
 
 #include "../../include/sr.h"
+#include "lds_limit.hpp"
 #include "schedule.hpp"
 
 namespace {
@@ -135,6 +136,18 @@ void stack_rule_checks() {
   else unsetenv("SR_STACK_PARTS");
 }
 
+// Raising a kernel's LDS limit on one device leaves the others to be raised.
+void lds_limit_checks() {
+  sr::LdsLimit limit;
+  bool ok = limit.pending(0) && limit.pending(1);
+  limit.set(0);
+  ok = ok && !limit.pending(0) && limit.pending(1) && limit.pending(63);
+  limit.set(63);
+  limit.set(64);
+  ok = ok && limit.pending(1) && !limit.pending(63) && limit.pending(64);
+  expect(ok, "LDS limits are kept per device");
+}
+
 template <class T>
 T* dev_alloc(size_t n, float fill = 0.f) {
   T* p = nullptr;
@@ -251,6 +264,7 @@ int main(int argc, char** argv) {
   argument_checks();
   stack_norm_checks();
   stack_rule_checks();
+  lds_limit_checks();
   if (!no_gpu) {
     int count = 0;
     if (hipGetDeviceCount(&count) != hipSuccess || count == 0) {

@@ -23,6 +23,7 @@
 #include "op_small.hpp"
 
 #include "fft_core.hpp"
+#include "lds_limit.hpp"
 
 namespace sr {
 
@@ -171,12 +172,8 @@ hipError_t go(const OpSmallArgs& a, int problems, hipStream_t s) {
   constexpr size_t lds = 2 * sizeof(float2) * (size_t)Tile<M1, M2, true>::BUF;
   auto kern = op_small_kernel<M1, M2, ADJ>;
   if (lds > 65536) {
-    static bool raised = false;  // once per instantiation
-    if (!raised) {
-      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
+    static LdsLimit limit;  // (one per instantiation)
+    if (hipError_t e = limit.raise((const void*)kern, lds); e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3(problems), dim3(M1 * M2 / 8), lds, s, a);
   return hipGetLastError();

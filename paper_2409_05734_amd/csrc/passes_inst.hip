@@ -3,6 +3,7 @@
 // reverse-mode passes; the build compiles every (length, set) pair as its own
 // translation unit so they compile in parallel.
 #include "launch.hpp"
+#include "lds_limit.hpp"
 
 #ifndef SR_FFT_N
 #error "compile with -DSR_FFT_N=<length>"
@@ -27,12 +28,8 @@ hipError_t go_src(const PassArgs& a, hipStream_t s) {
   auto kern = pass_kernel<N, B, COL, PRE, MID, FFT2, INV1, INV2, POST, DB, EV, TAB, WIN>;
   const size_t lds = T::NBUF * sizeof(float2) * (size_t)T::BUF;
   if (lds > 65536) {
-    static bool raised = false;  // once per instantiation
-    if (!raised) {
-      hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      raised = true;
-    }
+    static LdsLimit limit;  // (one per instantiation)
+    if (hipError_t e = limit.raise((const void*)kern, lds); e != hipSuccess) return e;
   }
   const int groups = (a.ntr + B - 1) / B;
   if (groups <= 0) return hipSuccess;
