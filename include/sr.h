@@ -84,7 +84,7 @@ typedef enum {
  * a phase block);
  * GD and power iteration of 4M grid points and more run as two balanced
  * groups, one on a second stream, and so do the halves of a stack of that
- * size under GD of 16 iterations and more; with SR_LDS_RESIDENT=1, problems
+ * size (four problems or more) under 16 iterations and more of either; with SR_LDS_RESIDENT=1, problems
  * whose grid fits one workgroup's LDS solve there instead, beside the
  * levels.                                                                   */
 typedef enum {

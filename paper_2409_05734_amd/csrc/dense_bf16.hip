@@ -22,12 +22,13 @@
 // 64 tile; two workgroups a CU, from reduction splits where the tiles are
 // fewer.  The row tiles of A X start at steps of their own: rows lie a power
 // of two of bytes apart in the shapes of use, and all tiles at one column would
-// meet on the same few memory channels (the product alone 155 -> 110 us).
+// meet on the same few memory channels (the product alone 155 us then).
 //
-// Measured (16384 x 4096 on 32 signals, A X and A^H R, packing and epilogue
-// included): 141 and 127 us, 3.8 and 4.2 TB/s of A; the library's FP32 product
-// 158 and 171 us, dense_mm_kernel 212 and 230 us.  Error against 64 bits 5.1e-7
-// and 7.5e-7; the library 1.6e-6 and 2.3e-6, dense_mm_kernel 8.1e-7 and 8.1e-7.
+// Measured (16384 x 4096 on 32 signals, A X and A^H R): the products 123 to 137
+// and 122 us, 3.9 to 4.4 TB/s of A; with packing and epilogue 141 to 144 and 127
+// to 130 us; the library's FP32 product 158 and 171 us, dense_mm_kernel 212 and
+// 230 us.  Error against 64 bits 5.1e-7 and 5.3e-7; the library 1.6e-6 and
+// 2.3e-6, dense_mm_kernel 8.1e-7 and 8.1e-7.
 #include "dense_bf16.hpp"
 
 #include <algorithm>

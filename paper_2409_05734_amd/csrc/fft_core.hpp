@@ -64,8 +64,10 @@ __device__ __forceinline__ float2 phase_turns(float theta) {
 // e^{i theta} from polynomials, close to sincosf's accuracy (3.6e-8 rms, 1.5e-7
 // at most over [0, 2 pi); sincosf 2.1e-8 rms): theta less the nearest multiple
 // of pi (in two parts, so that the difference keeps its last bits), sine and
-// cosine on [-pi/2, pi/2] by minimax fits of their even parts, and the sign of
-// the multiple.  About twice the issue time of the hardware pair; for kernels
+// cosine on [-pi/2, pi/2] by polynomials of least maximum absolute error there
+// (the leading terms x and 1 - z/2 fixed, the other four coefficients by
+// reweighted least squares; 4.6e-9 and 4e-10, with the coefficients rounded to
+// float 1.5e-8 and 6.3e-9), and the sign of the multiple.  About twice the issue time of the hardware pair; for kernels
 // where a table's memory traffic costs more than that.  The error stays there
 // up to kPhasePolyMax (1.7e-7 at most); from some 10^6 on the multiple itself
 // loses bits (2.8e-6 at 4 x 10^6, no phase at all at 10^8).
@@ -92,8 +94,9 @@ __device__ __forceinline__ float2 phase_poly(float theta) {
 
 // Deterministic workgroup sum: a fixed shuffle tree inside each wave, lane
 // 0's total broadcast to the wave, then the wave totals added in wave order.
-// Every thread gets the same value.  NTHREADS must be a power of two and
-// equal blockDim.x; `red` holds at least NTHREADS / 64 values.
+// Every thread gets the same value.  NTHREADS equals blockDim.x and is a whole
+// number of waves, or a power of two below one; `red` holds at least NTHREADS /
+// 64 values.
 template <int NTHREADS, class V>
 __device__ __forceinline__ V block_sum_t(V v, V* red) {
   constexpr int W = NTHREADS < 64 ? NTHREADS : 64;

@@ -225,8 +225,8 @@ void gpu_checks() {
   }
   run_plan(uneven, std::vector<float>((size_t)off, 1.f), "uneven, batched levels", SR_SCHED_BATCHED);
   run_plan({prob(1, 64, 1, 256, 1, 2)}, std::vector<float>(512, 1.f), "1D", SR_SCHED_AUTO);
-  // level problems of both length classes beside a 1D problem and a 2D
-  // length the level kernel does not take (the level tuner skips those two)
+  // level problems of powers of two and of lengths with a factor of three
+  // beside a 1D problem and a 2D length that the level kernel does not take
   run_plan({prob(2, 20, 20, 32, 64, 1, SR_STRUCTURED, 0), prob(2, 40, 36, 96, 64, 3, SR_STRUCTURED, 2048),
             prob(2, 30, 30, 64, 64, 2, SR_STRUCTURED, 2048 + 3 * 6144), prob(1, 16, 1, 64, 1, 2, SR_STRUCTURED, 28672),
             prob(2, 60, 20, 768, 32, 1, SR_STRUCTURED, 28800)},

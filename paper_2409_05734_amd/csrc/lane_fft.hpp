@@ -149,7 +149,6 @@ struct LaneTile {
   __device__ __forceinline__ static float2 turn(float2 y, float2 t) {
     return INV ? cmulc(y, t) : cmul(y, t);
   }
-  // two radix-2 steps, i.e. a radix-4 one across four lanes
   // this wave's output of the W-point transform, as sums of the halves'
   // outputs while the count is even: H inputs are left, W/H steps of W/H apart
   template <bool INV, int H>
