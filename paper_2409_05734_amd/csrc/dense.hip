@@ -748,12 +748,13 @@ static DenseLib* open_lib(const DenseArgs& a, LibCandidates* cand) {
 // 1000 x 258 on 32 signals 12, 20 and 16 us).  Each candidate runs once
 // untimed, then three times over timed on the plan's own matrix (the source is
 // scratch of the right size, the epilogue writes nothing but scratch) and its
-// best counts.  Products that stream A from memory in less than about 50 us
-// are timed six in a row, as a solver queues them: alone such a product is
-// also its launches, of which the candidates have two or three (3070 x 682 on
-// 32 signals, A^H R: dense_mm_kernel won alone, and queued the library takes
-// 22.1 us against 24.1).  The count follows from the shape, so that all
-// candidates are measured alike.
+// best counts; one that is half as slow again as the best so far is timed once.
+// Products that stream A from memory in less than about 50 us are timed six in
+// a row, as a solver queues them: alone such a product is also its launches, of
+// which the candidates have two or three (3070 x 682 on 32 signals, A^H R:
+// dense_mm_kernel won alone, and queued the library takes 22.1 us against
+// 24.1).  The count follows from the shape, so that all candidates are measured
+// alike.
 //
 // SR_DENSE_GEMM=own / bf16 / lib pins one of the three, SR_DENSE_GEMM=hand
 // leaves the library out.
@@ -780,13 +781,14 @@ sr_status dense_lib_setup(sr_plan_s* p) {
       hipMemsetD32Async((hipDeviceptr_t)p->bufA, 0x3f800000, 2 * (size_t)a.m * a.nb, p->stream) == hipSuccess) {
     const int runs = 8ll * a.m * a.n * signal_tiles(a) < kQueuedBytes ? 6 : 1;
     for (int g = 0; g < 2; ++g) {
+      float best = 1e30f;
       auto time_it = [&]() -> float {
         DenseArgs t = a;
         t.src = p->bufA;
         t.x = p->bufB;
         t.step = 1.f;
-        float best = 1e30f;
-        for (int rep = 0; rep < 4; ++rep) {
+        float least = 1e30f;
+        for (int rep = 0; rep < 4 && !(least > 1.5f * best && rep > 1); ++rep) {
           hipError_t e = hipEventRecord(e0, p->stream);
           for (int i = 0; i < (rep == 0 ? 1 : runs) && e == hipSuccess; ++i)
             e = g == 0 ? gemm<1, E1_STORE>(t, p->dsplit, p->stream, d.get())
@@ -796,11 +798,10 @@ sr_status dense_lib_setup(sr_plan_s* p) {
           float ms = 0.f;
           if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
           if (e != hipSuccess) return 1e30f;
-          if (rep > 0) best = std::min(best, ms);  // the first loads the kernel
+          if (rep > 0) least = std::min(least, ms);  // the first loads the kernel
         }
-        return best;
+        return least;
       };
-      float best = 1e30f;
       int pick = -1;  // -1: dense_mm_kernel, or the bf16 products
       bool bf16 = false;
       if (d != nullptr) d->use[g] = false;
