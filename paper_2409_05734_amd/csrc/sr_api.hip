@@ -590,14 +590,17 @@ static bool stream_capturing(const sr_plan_s* p) {
 // kTraceRows rows (= the chunk), summed by one launch per chunk
 // (flush(first iteration, rows)); a traced solve under the caller's own stream
 // capture launches every pass directly.  chunk(rows, last) runs that many
-// iterations, the last of them the solve's last if `last`, on `points` grid points a pass.
-template <class Chunk, class Flush>
-static sr_status gd_iterations(sr_plan_s* p, const std::string& key, int iters, bool trace, Chunk&& chunk,
-                               Flush&& flush, int64_t points) {
+// iterations, the last of them the solve's last if `last`, on `points` grid
+// points a pass.  key_of() gives the graphs' key: only where graphs are used,
+// since printing it takes 0.5 us of a one-iteration solve's 23.
+template <class Key, class Chunk, class Flush>
+static sr_status gd_iterations(sr_plan_s* p, Key&& key_of, int iters, bool trace, Chunk&& chunk, Flush&& flush,
+                               int64_t points) {
   static_assert(kTraceRows == kGraphChunk, "a chunk's iterations have a row each");
   int it = 0;
   auto steady = [&](int rows) { return [&, rows]() -> sr_status { return chunk(rows, false); }; };
-  if (graphs_enabled(p, points) && iters - 1 >= kGraphChunk && !(trace && stream_capturing(p))) {
+  if (iters - 1 >= kGraphChunk && graphs_enabled(p, points) && !(trace && stream_capturing(p))) {
+    const std::string key = key_of();
     for (; it + kGraphChunk <= iters - 1; it += kGraphChunk) {
       SR_CHECK(launch_captured(p, key, steady(kGraphChunk)));
       if (trace) SR_CHECK(flush(it, kGraphChunk));
@@ -1081,10 +1084,11 @@ static sr_status gd_stacked(sr_plan_s* p, int P, int ths, const float* y, float2
       return first_pass(p, q, xp, 1.f, nullptr, 0);
     }));
   const float step = steps[0];  // (unused by the stacked update, which reads the array)
-  const std::string key = "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" +
-                          ptr_key(p->stk_buf) + ":" + ptr_key(p->stk_steps) +
-                          (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) +
-                          (parts > 1 ? ":parts" : "") + loss_key(p);
+  auto key = [&]() {
+    return "gdstack:" + std::to_string(P) + ":" + ptr_key(y) + ":" + ptr_key(x) + ":" + ptr_key(p->stk_buf) + ":" +
+           ptr_key(p->stk_steps) + (loss_trace ? ":" + ptr_key(p->stk_part) : std::string()) +
+           (parts > 1 ? ":parts" : "") + loss_key(p);
+  };
   return gd_iterations(
       p, key, iters, loss_trace != nullptr,
       [&](int rows, bool last) -> sr_status {
@@ -1144,8 +1148,10 @@ sr_status sr_gd_solve(sr_plan p, const float* y, void* x_inout, int32_t iters, c
     }
     const int nparts = turn_groups(p, g);
     SR_CHECK(first_pass(p, g, xi, 1.f, nullptr, 0));
-    const std::string key = "gd:" + std::to_string(i) + ":" + ptr_key(yi) + ":" + ptr_key(xi) + ":" +
-                            float_key(step) + (lt ? ":tr" : "") + loss_key(p);
+    auto key = [&]() {
+      return "gd:" + std::to_string(i) + ":" + ptr_key(yi) + ":" + ptr_key(xi) + ":" + float_key(step) +
+             (lt ? ":tr" : "") + loss_key(p);
+    };
     SR_CHECK(gd_iterations(
         p, key, iters, lt != nullptr,
         [&](int rows, bool last) -> sr_status {
