@@ -169,11 +169,21 @@ static sr_status adjoint_body(sr_plan_s* p, const Geo& g, float2* cur, int last_
 }
 
 // The turnaround pass (index L+1): from the forward result `cur` through the
-// epilogue and back; writes into the other ping-pong buffer.
+// epilogue and back.  In place, since input and output have one layout, except
+// for a problem by itself on compact rows (L = 1) that are not whole cache
+// lines: there neighbouring rows share lines, which in place one XCD writes
+// while another reads, and the column pass after it would work in place on them
+// too (60 GD iterations, in place -> other buffer: 2048 x 1024 grid, 511 columns
+// 1753 -> 1610 us, 512 columns 1667 -> 1670; 1024 x 1024, 511 columns 1068 ->
+// 1056; 512 x 512, 255 columns 546 -> 541).  Stacks and level launches are
+// bound by memory and gain more from the smaller working set (16 of 512 x 512,
+// 255 columns 1908 -> 1968; 40 of 256 x 256, 101 columns 1270 -> 1286).
 static sr_status turnaround(sr_plan_s* p, const Geo& g, float2* cur, int kind, const float* y, float lam,
                             const double* ysum, float* part_out, float2** out) {
   const int k = g.L + 1;
-  float2* other = cur;  // in place: input and output have one layout (compact for k = 2, else full)
+  constexpr int kLine = 128 / sizeof(float2);
+  const bool apart = k == 2 && g.N2 % kLine != 0 && p->stk.P == 1 && g_recording == nullptr;
+  float2* other = apart ? (cur == p->bufA ? p->bufB : p->bufA) : cur;
   PassArgs a = base_args(p, g, k);
   set_in(a, g, k, cur);
   set_out(a, g, k, other);
