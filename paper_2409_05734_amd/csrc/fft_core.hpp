@@ -453,10 +453,18 @@ struct Tile {
   __device__ __forceinline__ static int lidx(int b, int k) { return COL ? (padk(k) * B + b) : (b * LD + padk(k)); }
   // lidx(b, k + C) from at = lidx(b, k), for a constant C.  Where C is a whole
   // number of pad periods the sum is a constant too, which goes into the LDS
-  // instruction.
+  // instruction (SHIFTS).  That saves instructions, but of accesses at constant
+  // distances the compiler merges two into one, which makes rows of 128 to 1024
+  // and of 4096 points wait longer for their exchanges than they save: 1000
+  // one-dimensional solves of 1024 points 850 us with, 780 us without; 60 GD
+  // iterations on 1024 x 1024 2380 and 2303, 16 of 512 x 512 3246 and 3209.
+  // Columns (2048 x 2048, 129 -> 122 us an iteration), rows of 2048 points and the
+  // split shapes (768 x 384, 1314 us without, 1283 with) gain, short rows are as
+  // fast either way.
+  static constexpr bool SHIFTS = COL || N % 3 == 0 || N <= 64 || N == 2048;
   template <int C>
   static constexpr bool shifts_whole() {
-    return PADSHIFT == 0 || C % (1 << PADSHIFT) == 0;
+    return SHIFTS && (PADSHIFT == 0 || C % (1 << PADSHIFT) == 0);
   }
   template <int C>
   static constexpr int shift_of() {
@@ -587,7 +595,7 @@ struct Tile {
   }
   template <int R, int P, int J>
   __device__ __forceinline__ static void write_one(float2 u, float2* at, float2* dst, int base, int b) {
-    if constexpr (P == 1 && PADSHIFT && R == (1 << PADSHIFT)) at[J * (COL ? B : 1)] = u;
+    if constexpr (SHIFTS && P == 1 && PADSHIFT && R == (1 << PADSHIFT)) at[J * (COL ? B : 1)] = u;
     else if constexpr (shifts_whole<J * P>()) at[shift_of<J * P>()] = u;
     else dst[lidx(b, base + J * P)] = u;
   }
