@@ -12,8 +12,8 @@
 // Bound by the stream of A from HBM: the next batch of rows is loaded into a
 // second register set before the current one is reduced, so 64 to 128 KB per
 // CU are in flight across the two barriers of a batch.  16384 x 4096, one
-// signal: A x 92 us, A^H r 94 us, a GD iteration 99 us (5.4 TB/s), against
-// 139, 155 and 283 us on the matrix-core path (two products over A with their
+// signal: A x 90 us, A^H r 92 us, a GD iteration 98 us (5.5 TB/s), against
+// 133, 151 and 279 us on the matrix-core path (two products over A with their
 // packing and epilogue kernels, four launches more).
 #include "dense_rows.hpp"
 
@@ -39,9 +39,11 @@ __device__ __forceinline__ float wave_sum_many(float (&v)[V], int lane) {
     const bool up = (lane & mask) != 0;
 #pragma unroll
     for (int i = 0; i < h; ++i) {
-      const float send = up ? v[i] : v[i + h];
-      const float keep = up ? v[i + h] : v[i];
-      v[i] = keep + __shfl_xor(send, mask);
+      // (values first: a choice between the elements themselves is an index
+      // that the compiler searches the registers for, 1754 instructions a kernel
+      // of four signals against 413; A x of 20000 x 100 74 -> 17 us)
+      const float lo = v[i], hi = v[i + h];
+      v[i] = (up ? hi : lo) + __shfl_xor(up ? lo : hi, mask);
     }
   }
   for (; mask >= 1; mask /= 2) v[0] += __shfl_xor(v[0], mask);
@@ -318,13 +320,13 @@ constexpr int batch_rows(int T, int J, int NB) {
 
 // One to four signals of up to 4096 entries: x and the partial sums of A^H r
 // fit a workgroup's registers (16 values each per thread and signal at 1024
-// threads).  One GD iteration on 16384 x 4096: 99 / 126 / 206 us for 1 / 2 / 4
-// signals against 282-285 us on the matrix cores.  Up to eight go in two
+// threads).  One GD iteration on 16384 x 4096: 98 / 106 / 142 us for 1 / 2 / 4
+// signals against 279-285 us on the matrix cores.  Up to eight go in two
 // groups of four where the whole product is small (kSmallProduct) and launches
-// and latency, not arithmetic, set the time: 1000 x 258 x 8 18 us against 33,
-// but 4096 x 1024 x 8 53 against 47, and 1000 x 258 x 16 (four groups) 27
-// against 31 with its A x alone no faster.  Longer signals and larger batches
-// stay on the matrix cores.
+// and latency, not arithmetic, set the time: 1000 x 258 x 8 12 us against 33.
+// The line was drawn when the sums still took twice as long (then 4096 x 1024 x
+// 8 53 against 47, and 1000 x 258 x 16, in four groups, 27 against 31 with its A x
+// alone no faster).  Longer signals and larger batches stay on the matrix cores.
 bool rows_shape(int m, int n, int nb, RowsShape* s) {
   if (nb < 1 || n < 1 || n > 4096) return false;
   if (nb > 4 && (nb > kSmallBatch || (long long)m * n * nb > kSmallProduct)) return false;
@@ -332,9 +334,20 @@ bool rows_shape(int m, int n, int nb, RowsShape* s) {
   s->T = n <= 256 ? 64 : n <= 1024 ? 256 : 1024;
   s->J = n <= s->T * 2 ? 1 : 2;
   s->R = batch_rows(s->T, s->J, s->NB);
-  // 1024 threads: one workgroup per CU; a batch's groups share the count (and
-  // the partial-sum buffers, which hold 2 m values)
-  const int cap = std::max(1, std::min(s->T == 1024 ? 256 : 512, 2 * m / nb));
+  // Workgroups: 1024 threads are one a CU.  Smaller ones do little between the
+  // loads of one batch and the next, so tall matrices take more of them, some
+  // ten rows apiece for one wave and twenty for four (three signals, 512 -> the
+  // count here, A x and a GD iteration: 100000 x 100 72.6 and 115 -> 23.7 and 43
+  // us, 20000 x 100 16.9 and 27.2 -> 7.0 and 21.0, 100000 x 512 115 and 153 -> 86
+  // and 98); fewer rows apiece cost more in partials to sum (2000 x 100 10.4 ->
+  // 12.2, 6000 x 512 17.2 -> 18.7), and so do more of the longest signals of four
+  // waves (20000 x 1000 42.6 -> 46.0).  A batch's groups share the count (and the
+  // partial-sum buffers, which hold 2 m values).
+  const int want = s->T == 1024 ? 256
+                   : s->T == 64 ? std::clamp(m / 10, 512, 2048)
+                   : s->J == 1 ? std::clamp(m / 20, 512, 1024)
+                               : 512;
+  const int cap = std::max(1, std::min(want, 2 * m / nb));
   const int batches = (m + s->R - 1) / s->R;
   const int per = (batches + cap - 1) / cap;
   s->rows = per * s->R;
