@@ -61,6 +61,9 @@ def build(verbose: bool = False, jobs: int | None = None) -> str:
     for k in range(4):  # the level kernel, one pass set per translation unit
         tasks.append((os.path.join(CSRC, "batched.hip"), os.path.join(BUILD, f"batched_set{k}.o"),
                       [f"-DSR_LEVEL_SET={k}"]))
+    for k in (0, 1):  # GD and power iteration on the narrow shapes
+        tasks.append((os.path.join(CSRC, "batched.hip"), os.path.join(BUILD, f"batched_narrow{k}.o"),
+                      [f"-DSR_LEVEL_SET={k}", "-DSR_LEVEL_EV=1"]))
     jobs = jobs or min(16, os.cpu_count() or 4)
     failures = []
     with cf.ThreadPoolExecutor(max_workers=jobs) as ex:
@@ -106,6 +109,7 @@ def build_host_check(jobs: int | None = None) -> str:
                   SAN_FLAGS + ["-x", "hip"]))
     plain = [os.path.join(BUILD, f"passes_{n}_{pset}.o") for n in FFT_LENGTHS for pset in (0, 1)]
     plain += [os.path.join(BUILD, f"batched_set{k}.o") for k in range(4)]
+    plain += [os.path.join(BUILD, f"batched_narrow{k}.o") for k in (0, 1)]
     missing = [o for o in plain if not os.path.exists(o)]
     if missing:
         raise RuntimeError("run build() first: missing " + ", ".join(missing[:3]))

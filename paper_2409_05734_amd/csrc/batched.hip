@@ -7,10 +7,11 @@
 // of every problem that has one.  A launch is a flat list of work items
 // (descriptor, tile); all tiles are 256-thread workgroups, the tile width of
 // each length chosen so that its transforms fill 256 threads (the default
-// thread shapes; four elements per thread take 10.3 against 8.7 ms on the
-// measure below).  The passes evaluate the phases themselves: many problems
-// together are bound by memory traffic as much as by arithmetic, and a table
-// costs 8 bytes an element against 4.  20 power and 40 GD iterations of 256
+// thread shapes, or the narrow ones for the solvers of small plans: level_ev;
+// on the measure below four elements per thread take 10.3 against 8.7 ms).  The
+// passes evaluate the phases themselves: many problems together are bound by
+// memory traffic as much as by arithmetic, and a table costs 8 bytes an element
+// against 4.  20 power and 40 GD iterations of 256
 // problems: 9.3 ms with tables, 9.0 ms with polynomials of the tables'
 // accuracy (7.8 ms with the hardware sine and cosine, which are eight times
 // less exact); 8.1 ms since the passes issue fewer instructions (passes.hpp).
@@ -47,33 +48,40 @@ struct BatchItem {
   int tile;
 };
 
-template <int N>
+// Thread shape of length N in a set of shape EV (0 default, 1 narrow: four
+// elements per thread), and the transforms that fill a workgroup.
+template <int N, int EV>
+constexpr int shape_of() {
+  return EV == 1 && HasNarrow<N>::value ? 1 : 0;
+}
+template <int N, int EV = 0>
 constexpr int batch_b() {
-  return kBatchThreads / TileV<N, 1, true>::TPT;
+  return kBatchThreads / TileV<N, 1, true, true, shape_of<N, EV>()>::TPT;
 }
 
 // One tile of a pass, window-aware (one kernel serves every geometry), phases
 // evaluated by polynomials.
-template <int N, int B, bool COL, int PRE, int MID, bool FFT2, bool INV1, bool INV2, int POST>
+template <int N, int B, bool COL, int PRE, int MID, bool FFT2, bool INV1, bool INV2, int POST, int EV = 0>
 __device__ __forceinline__ void level_tile(const PassArgs& a, int tile, float2* lds, float* red, const float* part_in,
                                            int npart, float* part_out) {
-  pass_tile<N, B, COL, PRE, MID, FFT2, INV1, INV2, POST, true, 0, false, true, true>(a, tile, lds, red, part_in, npart, part_out);
+  pass_tile<N, B, COL, PRE, MID, FFT2, INV1, INV2, POST, true, shape_of<N, EV>(), false, true, true>(
+      a, tile, lds, red, part_in, npart, part_out);
 }
 
-template <int N, bool COL>
+template <int N, bool COL, int EV>
 __device__ __forceinline__ void run_kind_gd(const PassArgs& a, int kind, int tile, float2* lds, float* red) {
-  constexpr int B = batch_b<N>();
+  constexpr int B = batch_b<N, EV>();
   if constexpr (COL) {
     switch (kind) {
       case PK_FIRST_FWD:
-        level_tile<N, B, COL, PRE_PHASE, MID_NONE, false, false, false, POST_STORE>(a, tile, lds, red, nullptr, 0,
+        level_tile<N, B, COL, PRE_PHASE, MID_NONE, false, false, false, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                    nullptr);
         return;
       case PK_LAST_GD:
-        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_GD>(a, tile, lds, red, nullptr, 0, nullptr);
+        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_GD, EV>(a, tile, lds, red, nullptr, 0, nullptr);
         return;
       case PK_LAST_GD_FWD:
-        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_GD_FWD>(a, tile, lds, red, nullptr, 0,
+        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_GD_FWD, EV>(a, tile, lds, red, nullptr, 0,
                                                                                   nullptr);
         return;
       default:
@@ -82,19 +90,19 @@ __device__ __forceinline__ void run_kind_gd(const PassArgs& a, int kind, int til
   }
   switch (kind) {
     case PK_MID_FWD:
-      level_tile<N, B, COL, PRE_NONE, MID_PHASE, true, false, false, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_PHASE, true, false, false, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                 nullptr);
       return;
     case PK_TURN_GD:  // (loss partials where the descriptor asks for a trace)
-      level_tile<N, B, COL, PRE_NONE, MID_GD, true, false, true, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_GD, true, false, true, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                             a.part_out);
       return;
     case PK_TURN_GD_POIS:
-      level_tile<N, B, COL, PRE_NONE, MID_GD_POIS, true, false, true, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_GD_POIS, true, false, true, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                  a.part_out);
       return;
     case PK_MID_ADJ:
-      level_tile<N, B, COL, PRE_NONE, MID_PHASE_CONJ, true, true, true, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_PHASE_CONJ, true, true, true, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                    nullptr);
       return;
     default:
@@ -106,21 +114,21 @@ __device__ __forceinline__ void run_kind_gd(const PassArgs& a, int kind, int til
 // The passes of a power iteration (deferred normalisation: the last pass
 // reads the previous iterate's squared-norm partials and writes the new
 // ones, each problem's own, through its descriptor).
-template <int N, bool COL>
+template <int N, bool COL, int EV>
 __device__ __forceinline__ void run_kind_spec(const PassArgs& a, int kind, int tile, float2* lds, float* red) {
-  constexpr int B = batch_b<N>();
+  constexpr int B = batch_b<N, EV>();
   if constexpr (COL) {
     switch (kind) {
       case PK_FIRST_FWD:
-        level_tile<N, B, COL, PRE_PHASE, MID_NONE, false, false, false, POST_STORE>(a, tile, lds, red, nullptr, 0,
+        level_tile<N, B, COL, PRE_PHASE, MID_NONE, false, false, false, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                    nullptr);
         return;
       case PK_LAST_SPEC:
-        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_SPEC>(a, tile, lds, red, a.part_in, a.npart,
+        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_SPEC, EV>(a, tile, lds, red, a.part_in, a.npart,
                                                                                 a.part_out);
         return;
       case PK_LAST_SPEC_FWD:
-        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_SPEC_FWD>(a, tile, lds, red, a.part_in,
+        level_tile<N, B, COL, PRE_NONE, MID_NONE, false, true, false, POST_SPEC_FWD, EV>(a, tile, lds, red, a.part_in,
                                                                                     a.npart, a.part_out);
         return;
       default:
@@ -129,14 +137,14 @@ __device__ __forceinline__ void run_kind_spec(const PassArgs& a, int kind, int t
   }
   switch (kind) {
     case PK_MID_FWD:
-      level_tile<N, B, COL, PRE_NONE, MID_PHASE, true, false, false, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_PHASE, true, false, false, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                 nullptr);
       return;
     case PK_TURN_SPEC:
-      level_tile<N, B, COL, PRE_NONE, MID_SPEC, true, false, true, POST_STORE>(a, tile, lds, red, nullptr, 0, nullptr);
+      level_tile<N, B, COL, PRE_NONE, MID_SPEC, true, false, true, POST_STORE, EV>(a, tile, lds, red, nullptr, 0, nullptr);
       return;
     case PK_MID_ADJ:
-      level_tile<N, B, COL, PRE_NONE, MID_PHASE_CONJ, true, true, true, POST_STORE>(a, tile, lds, red, nullptr, 0,
+      level_tile<N, B, COL, PRE_NONE, MID_PHASE_CONJ, true, true, true, POST_STORE, EV>(a, tile, lds, red, nullptr, 0,
                                                                                    nullptr);
       return;
     default:
@@ -247,13 +255,13 @@ constexpr int kBatchGroups = 4;  // workgroups per CU
 // carries the registers of the others).
 enum LevelSetKind : int { LS_GD = 0, LS_SPEC = 1, LS_OP = 2, LS_VJP = 3 };
 
-template <int N, int SET>
+template <int N, int SET, int EV>
 __device__ __forceinline__ void run_len(const BatchDesc& d, int tile, float2* lds, float* red) {
-  static_assert(TileV<N, batch_b<N>(), true>::THREADS == kBatchThreads, "batched tiles are 256 threads");
-  static_assert(2 * sizeof(float2) * TileV<N, batch_b<N>(), true>::BUF <= kBatchLds, "batched LDS budget");
+  static_assert(TileV<N, batch_b<N, EV>(), true, true, shape_of<N, EV>()>::THREADS == kBatchThreads, "batched tiles are 256 threads");
+  static_assert(2 * sizeof(float2) * TileV<N, batch_b<N, EV>(), true, true, shape_of<N, EV>()>::BUF <= kBatchLds, "batched LDS budget");
   if constexpr (SET == LS_SPEC) {
-    if (d.col) run_kind_spec<N, true>(d.a, d.kind, tile, lds, red);
-    else run_kind_spec<N, false>(d.a, d.kind, tile, lds, red);
+    if (d.col) run_kind_spec<N, true, EV>(d.a, d.kind, tile, lds, red);
+    else run_kind_spec<N, false, EV>(d.a, d.kind, tile, lds, red);
   } else if constexpr (SET == LS_OP) {
     if (d.col) run_kind_op<N, true>(d.a, d.kind, tile, lds, red);
     else run_kind_op<N, false>(d.a, d.kind, tile, lds, red);
@@ -261,12 +269,12 @@ __device__ __forceinline__ void run_len(const BatchDesc& d, int tile, float2* ld
     if (d.col) run_kind_vjp<N, true>(d.a, d.kind, tile, lds, red);
     else run_kind_vjp<N, false>(d.a, d.kind, tile, lds, red);
   } else {
-    if (d.col) run_kind_gd<N, true>(d.a, d.kind, tile, lds, red);
-    else run_kind_gd<N, false>(d.a, d.kind, tile, lds, red);
+    if (d.col) run_kind_gd<N, true, EV>(d.a, d.kind, tile, lds, red);
+    else run_kind_gd<N, false, EV>(d.a, d.kind, tile, lds, red);
   }
 }
 
-template <int SET>
+template <int SET, int EV>
 __global__ void __launch_bounds__(kBatchThreads, kBatchGroups)
     batched_level_kernel(const BatchItem* __restrict__ items, const BatchDesc* __restrict__ descs) {
   extern __shared__ float2 lds[];
@@ -274,31 +282,28 @@ __global__ void __launch_bounds__(kBatchThreads, kBatchGroups)
   const BatchItem it = items[xcd_tile(blockIdx.x, gridDim.x)];
   const BatchDesc& d = descs[it.desc];
   switch (d.N) {
-    case 16: run_len<16, SET>(d, it.tile, lds, red); break;
-    case 32: run_len<32, SET>(d, it.tile, lds, red); break;
-    case 64: run_len<64, SET>(d, it.tile, lds, red); break;
-    case 96: run_len<96, SET>(d, it.tile, lds, red); break;
-    case 128: run_len<128, SET>(d, it.tile, lds, red); break;
-    case 192: run_len<192, SET>(d, it.tile, lds, red); break;
-    case 256: run_len<256, SET>(d, it.tile, lds, red); break;
-    case 384: run_len<384, SET>(d, it.tile, lds, red); break;
-    case 512: run_len<512, SET>(d, it.tile, lds, red); break;
+    case 16: run_len<16, SET, EV>(d, it.tile, lds, red); break;
+    case 32: run_len<32, SET, EV>(d, it.tile, lds, red); break;
+    case 64: run_len<64, SET, EV>(d, it.tile, lds, red); break;
+    case 96: run_len<96, SET, EV>(d, it.tile, lds, red); break;
+    case 128: run_len<128, SET, EV>(d, it.tile, lds, red); break;
+    case 192: run_len<192, SET, EV>(d, it.tile, lds, red); break;
+    case 256: run_len<256, SET, EV>(d, it.tile, lds, red); break;
+    case 384: run_len<384, SET, EV>(d, it.tile, lds, red); break;
+    case 512: run_len<512, SET, EV>(d, it.tile, lds, red); break;
     default: break;
   }
 }
 
-// Transforms per 256-thread tile (0: length not taken by the level kernel).
-int batch_tile_width(int N) {
+// Transforms per 256-thread tile in a set of shape ev (0: length not taken by
+// the level kernel).
+int batch_tile_width(int N, int ev = 0) {
   switch (N) {
-    case 16: return batch_b<16>();
-    case 32: return batch_b<32>();
-    case 64: return batch_b<64>();
-    case 96: return batch_b<96>();
-    case 128: return batch_b<128>();
-    case 192: return batch_b<192>();
-    case 256: return batch_b<256>();
-    case 384: return batch_b<384>();
-    case 512: return batch_b<512>();
+#define SR_CASE(n) \
+  case n:          \
+    return ev ? batch_b<n, 1>() : batch_b<n>();
+    SR_CASE(16) SR_CASE(32) SR_CASE(64) SR_CASE(96) SR_CASE(128) SR_CASE(192) SR_CASE(256) SR_CASE(384) SR_CASE(512)
+#undef SR_CASE
     default: return 0;
   }
 }
@@ -313,11 +318,19 @@ hipError_t launch_level_set0(dim3 grid, hipStream_t s, const void* items, const 
 hipError_t launch_level_set1(dim3 grid, hipStream_t s, const void* items, const void* descs);
 hipError_t launch_level_set2(dim3 grid, hipStream_t s, const void* items, const void* descs);
 hipError_t launch_level_set3(dim3 grid, hipStream_t s, const void* items, const void* descs);
+// GD and power iteration on the narrow shapes (SR_LEVEL_EV=1)
+hipError_t launch_level_narrow0(dim3 grid, hipStream_t s, const void* items, const void* descs);
+hipError_t launch_level_narrow1(dim3 grid, hipStream_t s, const void* items, const void* descs);
 #if defined(SR_LEVEL_SET)
+#if defined(SR_LEVEL_EV)
+#define SR_LAUNCHER_NAME(k) launch_level_narrow##k
+#else
+#define SR_LEVEL_EV 0
 #define SR_LAUNCHER_NAME(k) launch_level_set##k
+#endif
 #define SR_LAUNCHER(k) SR_LAUNCHER_NAME(k)
 hipError_t SR_LAUNCHER(SR_LEVEL_SET)(dim3 grid, hipStream_t s, const void* items, const void* descs) {
-  hipLaunchKernelGGL((batched_level_kernel<SR_LEVEL_SET>), grid, dim3(kBatchThreads), kBatchLds, s,
+  hipLaunchKernelGGL((batched_level_kernel<SR_LEVEL_SET, SR_LEVEL_EV>), grid, dim3(kBatchThreads), kBatchLds, s,
                      (const BatchItem*)items, (const BatchDesc*)descs);
   return hipGetLastError();
 }
@@ -327,6 +340,7 @@ hipError_t SR_LAUNCHER(SR_LEVEL_SET)(dim3 grid, hipStream_t s, const void* items
 // Level lists of one recorded pass sequence (device descriptors and items).
 struct LevelSet {
   int set = LS_GD;  // pass set (which instantiation of the level kernel)
+  int ev = 0;       // ... on the narrow shapes (GD and power iteration)
   BatchDesc* d_descs = nullptr;
   BatchItem* d_items = nullptr;
   std::vector<int> level_off, level_cnt;  // item ranges per level
@@ -414,6 +428,31 @@ __global__ void __launch_bounds__(64) batch_loss_reduce(const float* __restrict_
   if (threadIdx.x == 0) out[(long long)i * ostride] = (float)acc;
 }
 
+// Whether GD and power iteration run on the narrow thread shapes (four elements
+// per thread, twice the threads).  Levels of few points leave SIMDs empty and
+// last as long as one wave's chain, which the narrow shape shortens; larger
+// ones are bound by memory and arithmetic, and so is a single large problem
+// among small ones.  60 GD iterations, default -> narrow: 8 of 128 x 128 (0.13M
+// points) 1852 -> 1573 us, 2 of 256 to 512 points an axis (0.20M) 1949 -> 1755,
+// 50 of 128 x 128 (0.82M) 2104 -> 1929, 120 of 64 to 128 (1.13M) 2207 -> 2110; but
+// 20 of 256 x 256 (1.31M) 2393 -> 2398, 120 of 128 x 128 (1.97M) 2967 -> 3228, 2 of
+// 512 x 512 (0.52M) 2300 -> 2314, 8 of 16 to 512 (0.41M, one of 512 x 512) 2162 ->
+// 2261, 20 of them (0.64M, largest 0.13M) 2193 -> 2253.  SR_BATCH_EV=0 / 1 pins
+// the default / the narrow shape.  Decided on a plan's first use, for its life:
+// its partial sums are laid out for the tiles of one shape.
+constexpr int64_t kNarrowPoints = 1200000, kNarrowLargest = 65536, kNarrowAnyway = 300000;
+static int level_ev(sr_plan_s* p) {
+  if (p->level_ev >= 0) return p->level_ev;
+  if (const char* env = std::getenv("SR_BATCH_EV"); env != nullptr) return p->level_ev = std::atoi(env) != 0 ? 1 : 0;
+  int64_t points = 0, largest = 0;
+  for (const Geo& g : p->geo)
+    if (batch_level_capable(g)) {
+      points += g.mg;
+      largest = std::max(largest, g.mg);
+    }
+  return p->level_ev = points < kNarrowAnyway || (points < kNarrowPoints && largest <= kNarrowLargest) ? 1 : 0;
+}
+
 // Turn per-problem pass recordings into levels (level q = pass q of every
 // problem that has one) and upload them.
 static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRecord>>& recs, LevelSet& ls) {
@@ -421,6 +460,7 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
   for (const auto& r : recs) max_levels = std::max(max_levels, r.size());
   std::vector<BatchDesc> descs;
   std::vector<BatchItem> items;
+  ls.ev = ls.set == LS_GD || ls.set == LS_SPEC ? level_ev(p) : 0;
   ls.level_off.assign(max_levels, 0);
   ls.level_cnt.assign(max_levels, 0);
   // a problem with fewer passes than the deepest starts at the level that
@@ -462,7 +502,7 @@ static sr_status build_levels(sr_plan_s* p, const std::vector<std::vector<PassRe
       d.N = pass_len(g, r.k);
       d.col = pass_col(r.k);
       d.kind = r.kind;
-      const int B = batch_tile_width(d.N);
+      const int B = batch_tile_width(d.N, ls.ev);
       const int di = (int)descs.size();
       descs.push_back(d);
       for (int t = 0; t * B < r.a.ntr; ++t) items.push_back({di, t});
@@ -552,7 +592,7 @@ static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const fl
       const Geo& g = p->geo[i];
       const int k = g.L + 1;
       const int ntr = (k == 2) ? g.M1 : (pass_col(k) ? g.M2 : g.M1);
-      const int bt = batch_tile_width(pass_len(g, k));
+      const int bt = batch_tile_width(pass_len(g, k), level_ev(p));
       pd[i] = make_int2(tot, bt > 0 ? (ntr + bt - 1) / bt : 0);
       tot += pd[i].y;
     }
@@ -569,7 +609,7 @@ static sr_status batch_prepare(sr_plan_s* p, const float* y, float2* x, const fl
       const Geo& g = p->geo[i];
       const int k = g.L + 1;
       const int ntr = (k == 2) ? g.M1 : (pass_col(k) ? g.M2 : g.M1);
-      const int bt = batch_tile_width(pass_len(g, k));
+      const int bt = batch_tile_width(pass_len(g, k), level_ev(p));
       poff[i] = tot;
       tot += bt > 0 ? (ntr + bt - 1) / bt : 0;
     }
@@ -643,7 +683,9 @@ static sr_status run_levels(sr_plan_s* p, const LevelSet& ls) {
     const dim3 grid(ls.level_cnt[q]);
     const BatchItem* items = ls.d_items + ls.level_off[q];
     hipError_t e;
-    if (ls.set == LS_SPEC) e = launch_level_set1(grid, p->stream, items, ls.d_descs);
+    if (ls.set == LS_SPEC && ls.ev) e = launch_level_narrow1(grid, p->stream, items, ls.d_descs);
+    else if (ls.set == LS_GD && ls.ev) e = launch_level_narrow0(grid, p->stream, items, ls.d_descs);
+    else if (ls.set == LS_SPEC) e = launch_level_set1(grid, p->stream, items, ls.d_descs);
     else if (ls.set == LS_OP) e = launch_level_set2(grid, p->stream, items, ls.d_descs);
     else if (ls.set == LS_VJP) e = launch_level_set3(grid, p->stream, items, ls.d_descs);
     else e = launch_level_set0(grid, p->stream, items, ls.d_descs);
@@ -973,7 +1015,7 @@ static sr_status spec_prepare(sr_plan_s* p, const std::vector<int>& which, const
       const Geo& g = p->geo[i];
       st->part_off[i] = pelems;
       if (!batch_level_capable(g)) continue;
-      const int bq = batch_tile_width(g.M1);  // the last (column) pass's tiles
+      const int bq = batch_tile_width(g.M1, level_ev(p));  // the last (column) pass's tiles
       st->nq[i] = (g.N2 + bq - 1) / bq;
       pelems += 2 * (size_t)std::max(st->nq[i], 1);
     }

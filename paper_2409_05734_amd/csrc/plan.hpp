@@ -152,6 +152,7 @@ struct sr_plan_s {
   float2* step_buf = nullptr;  // the reverse GD step inside the passes: z and the saved q_k, grid layout
   size_t step_elems = 0;
   std::vector<size_t> lvl_off;
+  int level_ev = -1;  // thread shape of the level launches' solvers (1: narrow; -1: not decided yet)
   size_t vjp_elems = 0;
 
   // LDS-resident small-problem solver (fused2d.hip): device descriptors, their
