@@ -52,12 +52,7 @@ template <int N>
 using F1Tile = typename std::conditional<
     HasLane<N>::value, F1Lane<N>,
     typename std::conditional<HasNarrow<N>::value, TileSel<N, 1, false, true, 1>, F1Full<N>>::type>::type::type;
-// its table (sr_plan_s::twiddles)
-template <class P>
-inline const float2* twiddles_1d(const P* p, int N) {
-  if (const float2* lane = p->twiddles(N, 4)) return lane;
-  return p->twiddles(N, 1) ? p->twiddles(N, 1) : p->twiddles_resident(N);
-}
+// (its table: sr_plan_s::twiddles_1d)
 
 template <int N, int OP>
 __device__ __forceinline__ void fused1d_body(const Fused1DArgs& a) {

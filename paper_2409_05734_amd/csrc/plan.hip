@@ -168,6 +168,11 @@ sr_status sr_plan_s::init(const float* theta_host) {
   if (b_dpack) dpack = c;
 
   for (const auto& ta : tw_at) tw[ta.first] = twbuf + ta.second;
+  for (int N : lens_1d) {
+    const float2* lane = twiddles(N, 4);
+    const float2* narrow = twiddles(N, 1);
+    tw_1d[N] = lane ? lane : narrow ? narrow : twiddles_resident(N);
+  }
   if (tw_elems) {
     e = hipMemcpy(twbuf, host_tw.data(), sizeof(float2) * tw_elems, hipMemcpyHostToDevice);
     if (e != hipSuccess) return sr::hip_fail(e, "twiddle upload");

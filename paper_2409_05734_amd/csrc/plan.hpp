@@ -110,6 +110,7 @@ struct sr_plan_s {
   bool dense_rows = false;  // dense products on the row kernels (few short signals; dense_rows.hip)
 
   std::map<std::pair<int, int>, float2*> tw;  // (FFT length, thread shape) -> device twiddle table
+  std::map<int, const float2*> tw_1d;                          // the 1D lengths' tables among them
   float2* twbuf = nullptr;
 
   // workspace carved out of one allocation
@@ -185,6 +186,8 @@ struct sr_plan_s {
   // an element a lane (4; lengths of 1D problems)
   const float2* twiddles(int N, int shape = 0) const;
   const float2* twiddles_resident(int N) const { return twiddles(N, 3) ? twiddles(N, 3) : twiddles(N, 0); }
+  // table of the 1D kernels' shape (F1Tile), which is looked up per problem of a call
+  const float2* twiddles_1d(int N) const { return tw_1d.find(N)->second; }
   const float* theta_l(const sr::Geo& g, int l) const;
   ~sr_plan_s();
 };

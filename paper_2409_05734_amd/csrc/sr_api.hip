@@ -537,7 +537,7 @@ static Fused1DArgs args_1d(const sr_plan_s* p, const Geo& g, Fused1DArgs a) {
   a.mw = g.W1;
   a.moff = g.c1;
   a.theta = p->theta_l(g, 1);
-  a.tw = twiddles_1d(p, g.M1);
+  a.tw = p->twiddles_1d(g.M1);
   a.loss = p->loss;
   a.loss_eps = p->loss_eps;
   a.nf = p->sync + 2;
@@ -854,6 +854,7 @@ sr_status sr_plan_set_workspace(sr_plan p, void* dev_ptr, size_t bytes) {
   mv(p->dsplit);
   mv(p->dpack);
   for (auto& t : p->tw) mv(t.second);
+  for (auto& t : p->tw_1d) mv(t.second);
   // recorded schedules and captured graphs hold the old addresses
   for (auto& g : p->graphs) (void)hipGraphExecDestroy(g.second);
   p->graphs.clear();
