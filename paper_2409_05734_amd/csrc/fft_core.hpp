@@ -457,7 +457,9 @@ struct Tile {
   // distances the compiler merges two into one, which makes rows of 128 to 1024
   // and of 4096 points wait longer for their exchanges than they save: 1000
   // one-dimensional solves of 1024 points 850 us with, 780 us without; 60 GD
-  // iterations on 1024 x 1024 2380 and 2303, 16 of 512 x 512 3246 and 3209.
+  // iterations on 1024 x 1024 2380 and 2303, 16 of 512 x 512 3246 and 3209 (one
+  // 512 x 512 by itself, 200 iterations, 3673 and 3695: a wave to a SIMD pays
+  // for the instructions instead).
   // Columns (2048 x 2048, 129 -> 122 us an iteration), rows of 2048 points and the
   // split shapes (768 x 384, 1314 us without, 1283 with) gain, short rows are as
   // fast either way.
